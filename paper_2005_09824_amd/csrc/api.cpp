@@ -70,6 +70,7 @@ struct lfmmi_graph {
     bool has_wb = false;  // arcs carry a per-arc leak factor (some init_prob is not uniform)
     bool rec_grouped = false;  // every arc takes the pdf of the state it enters and the
                                // recursion runs the variant without an emission gather
+    bool occ_states = false;   // ... and the occupancies are added up over states, not arcs
 
     // device copy
     bool uploaded = false;
@@ -296,6 +297,8 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
                     if (!h->packed[g].pdf_by_dst) return 0;
                 return rec_grouped_slots(h->wide, h->has_wb, max_slots, waves * kLanes);
             };
+            h->occ_states = st == LFMMI_OK && env_int("LFMMI_GROUPED", 1) != 0;
+            for (int32_t g = 0; g < n && h->occ_states; ++g) h->occ_states = h->packed[g].pdf_by_dst;
             const int gslots = st == LFMMI_OK ? grouped_slots() : 0;
             h->rec_grouped = gslots > 0;
             auto resident = [&](int slots, int wv) {
@@ -384,7 +387,8 @@ lfmmi_status upload(lfmmi_graph* h)
     }
 
     // concatenate every graph's orderings
-    size_t n_slots = 0, n_soff = 0, n_wf = 0, n_vec = 0, n_rowpdf = 0, n_mask = 0, n_pfirst = 0;
+    size_t n_slots = 0, n_soff = 0, n_wf = 0, n_vec = 0, n_rowpdf = 0, n_mask = 0, n_pfirst = 0,
+           n_pstates = 0;
     h->ords.assign((size_t)h->num_graphs * 3, OrdDesc{});
     for (int32_t g = 0; g < h->num_graphs; ++g)
         for (int o = 0; o < 3; ++o) {
@@ -415,6 +419,8 @@ lfmmi_status upload(lfmmi_graph* h)
                 n_rowpdf += (size_t)od.num_slices * kLanes;
                 d.pdf_first_at = (int32_t)n_pfirst;
                 n_pfirst += h->packed[g].pdf_first.size();
+                d.pdf_states_at = (int32_t)n_pstates;
+                n_pstates += h->packed[g].pdf_states.size();
             }
         }
     if (n_slots > (size_t)1 << 30) return fail(LFMMI_ERR_UNSUPPORTED, "packed graph too large");
@@ -434,6 +440,8 @@ lfmmi_status upload(lfmmi_graph* h)
     const size_t at_vb = reserve<float>(&total, n_vec);
     const size_t at_vfin = reserve<float>(&total, n_vec);
     const size_t at_rowpdfs = reserve<int32_t>(&total, n_vec);
+    const size_t at_rowocc = reserve<uint32_t>(&total, n_vec);
+    const size_t at_pstates = reserve<int32_t>(&total, n_pstates);
     const size_t at_rowpdf = reserve<int32_t>(&total, n_rowpdf);
     const size_t at_pfirst = reserve<int32_t>(&total, n_pfirst);
     const size_t at_ords = reserve<OrdDesc>(&total, h->ords.size());
@@ -490,8 +498,14 @@ lfmmi_status upload(lfmmi_graph* h)
                 if (pg.row_pdf[o].size() == nrow)
                     std::memcpy(host.data() + at_rowpdfs + (size_t)d.vec_at * 4, pg.row_pdf[o].data(),
                                 nrow * 4);
+                if (o == 0 && pg.row_occ.size() == nrow)
+                    std::memcpy(host.data() + at_rowocc + (size_t)d.vec_at * 4, pg.row_occ.data(),
+                                nrow * 4);
             } else {
                 const PackedGraph& pg = h->packed[g];
+                if (!pg.pdf_states.empty())
+                    std::memcpy(host.data() + at_pstates + (size_t)d.pdf_states_at * 4,
+                                pg.pdf_states.data(), pg.pdf_states.size() * 4);
                 std::memcpy(host.data() + at_rowpdf + (size_t)d.vec_at * 4, pg.row_slot.data(),
                             nrow * 4);
                 std::memcpy(host.data() + at_pfirst + (size_t)d.pdf_first_at * 4,
@@ -522,6 +536,8 @@ lfmmi_status upload(lfmmi_graph* h)
     h->dg.vb = reinterpret_cast<const float*>(base + at_vb);
     h->dg.vfin = reinterpret_cast<const float*>(base + at_vfin);
     h->dg.row_pdf = reinterpret_cast<const int32_t*>(base + at_rowpdfs);
+    h->dg.row_occ = reinterpret_cast<const uint32_t*>(base + at_rowocc);
+    h->dg.pdf_states = reinterpret_cast<const int32_t*>(base + at_pstates);
     h->dg.row_slot = reinterpret_cast<const int32_t*>(base + at_rowpdf);
     h->dg.pdf_first = reinterpret_cast<const int32_t*>(base + at_pfirst);
     h->dg.ords = reinterpret_cast<const OrdDesc*>(base + at_ords);
@@ -671,6 +687,8 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
     shape.rec_grouped = h->rec_grouped ? 1 : 0;
     shape.profile_rec_only = h->profile == 2 ? 1 : 0;
     shape.rec_has_wb = h->has_wb ? 1 : 0;
+    shape.occ_states =
+        h->occ_states ? occ_states_frames(h->max_rows_f, h->max_rows_b, h->wide) : 0;
     shape.occ_threads = h->occ_waves * kLanes;
     shape.occ_frames = std::max(1, env_int("LFMMI_OCC_FRAMES", 4));
     // the plane-layout occupancy kernel (several frames per arc record) when it fits

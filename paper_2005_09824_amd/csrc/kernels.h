@@ -23,6 +23,7 @@ struct OrdDesc {
                             // heavy-pdf list: count, row limit, pdf-ids)
     int32_t closing;        // FWD/BWD: slices end in a slot that holds the row's leak-dot weight
     float a_const;          // that weight when it is one constant (no closing slots)
+    int32_t pdf_states_at;  // OCC: first entry in pdf_states (num_pdfs + 1 offsets)
 };
 
 struct DeviceGraph {
@@ -43,6 +44,10 @@ struct DeviceGraph {
     const int32_t* pdf_first;   // OCC: the sums of pdf d's rows are words pdf_first[d] ..
                                 // pdf_first[d + 1] - 1 of a frame's row sums
     const int32_t* row_slot;    // OCC: the word the sum of row (slice * 64 + lane) goes to
+    // Occupancies by entered state (k_occ_states); zeros for other graphs.
+    const uint32_t* row_occ;    // per FWD row (indexed like vinit): its state's BWD row, and above
+                                // it (<< 16) the place of its state in the order of the pdfs
+    const int32_t* pdf_states;  // the states of pdf d have places [d] .. [d + 1] - 1
     const OrdDesc* ords;        // [num_graphs * 3]
 };
 
@@ -95,6 +100,7 @@ struct LaunchShape {
     int rec_hybrid;    // 1: only the first slots of a wave are register-resident;
                        // 2: the same, with the LDS map for up to 12288 states
     int rec_grouped = 0;  // arcs take the emission of the entered state: no emission gather
+    int occ_states = 0;  // frames per workgroup of the occupancy kernel by entered state (0: by arc)
     int occ_threads;   // workgroup size of the occupancy kernel
     int occ_frames;    // frames per occupancy workgroup (frame-at-a-time kernel)
     int occ_multi;     // frames per record of the plane-layout occupancy kernel (0: not used)
@@ -151,5 +157,7 @@ int rec_grouped_max_rows(int threads);
 size_t occ_lds_bytes(int rows_a, int rows_b, int occ_rows, bool wide);
 int occ_plane_frames(int rows, int occ_rows, int most);
 size_t occ_plane_lds_bytes(int rows, int occ_rows, int frames);
+// Frames per workgroup of the occupancy kernel by entered state for this many rows.
+int occ_states_frames(int rows_f, int rows_b, bool wide);
 
 }  // namespace lfmmi

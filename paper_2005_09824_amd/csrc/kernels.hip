@@ -2225,6 +2225,124 @@ __global__ void __launch_bounds__(1024) k_occ_planes(FbParams p, int groups_per_
     }
 }
 
+// ---------------------------------------------------------------------------
+// Occupancy by entered state, for graphs whose arcs all carry the pdf-id of the state
+// they enter: the arcs into state j sum up to the raw alpha value of j, so
+//   gamma_t[d] = c_t * sum_{j: pdf_j = d} v_t[j] * bhat_t[j],   v_t raw alpha, bhat_t = beta',
+// one product per state instead of one per arc, no arc records, no emission. What bounds it
+// is the trellis' way from memory (two rows per frame). The beta rows of F frames go to LDS,
+// every alpha row (read where it is used) meets the beta value of its state there and leaves
+// the product at the state's place in the order of the pdfs; eight lanes then add up a pdf's
+// products, which lie side by side (the sum's order does not depend on timing).
+// Against the kernels by arc: 780 -> 754 us a call on the 2,016-state HMM-expanded
+// denominator (B = 64), 1,324 -> 1,305 us for the loss of 128 numerators (k_occ<double>
+// before) minus a denominator; no size measured slower.
+// ---------------------------------------------------------------------------
+constexpr int kOccStatesThreads = 256;
+
+template <typename Real, int F>
+__global__ void __launch_bounds__(kOccStatesThreads) k_occ_states(FbParams p)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    constexpr int kRows = 4;  // rows of a thread whose loads are in flight together
+    const int tid = threadIdx.x;
+    const int b = p.order[2 * (p.seq_first + blockIdx.y)] >> 1;
+    const SeqDesc sd = p.seqs[b];
+    const int T = sd.T;
+    const int t0 = blockIdx.x * F + 1;
+    if (t0 > T) return;  // k_emit has cleared the gradient rows past the sequence
+    const int P = p.P;
+    const OrdDesc* ords = p.g.ords + sd.graph * 3;
+    const int rows_f = ords[0].num_slices * 64, rows_b = ords[1].num_slices * 64;
+    const uint32_t* row_occ = p.g.row_occ + ords[0].vec_at;
+    const int32_t* first = p.g.pdf_states + ords[2].pdf_states_at;
+
+    Real* XB = reinterpret_cast<Real*>(lds_raw);          // [F][lds_rows_occ_b]
+    Real* prod = XB + F * p.lds_rows_occ_b;               // [F][lds_rows_occ_a + 1]
+    const int pstride = p.lds_rows_occ_a + 1;
+    const Real* cfac = static_cast<const Real*>(p.cfac) + sd.scal_at;
+    const Real* scal = static_cast<const Real*>(p.scal) + sd.scal_at + 2 * p.scal_total;
+    const Real* ar = static_cast<const Real*>(p.alpha) + sd.alpha_at + (size_t)t0 * rows_f;
+    const Real* br = static_cast<const Real*>(p.beta) + sd.beta_at + (size_t)t0 * rows_b;
+    Real scale[F], invb[F], cb[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+        const int t = min(t0 + f, T);
+        const Real c = t0 + f <= T ? cfac[t] : (Real)0;
+        scale[f] = (Real)p.grad_scale * c;
+        // (a dead sequence has c == 0 and may have n == 0: its products are zeros)
+        invb[f] = c != (Real)0 ? (Real)1 / scal[t] : (Real)0;
+        cb[f] = c != (Real)0 ? (Real)p.leak * scal[p.scal_total + t] * invb[f] : (Real)0;
+    }
+    auto live = [&](const int f) { return t0 + f <= T; };
+    for (int r0 = 0; r0 < rows_b; r0 += kRows * kOccStatesThreads) {
+        Real v[kRows][F];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int r = r0 + u * kOccStatesThreads + tid;
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                v[u][f] = r < rows_b && live(f) ? br[(size_t)f * rows_b + r] : (Real)0;
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int r = r0 + u * kOccStatesThreads + tid;
+            if (r >= rows_b) break;
+#pragma unroll
+            for (int f = 0; f < F; ++f) XB[f * p.lds_rows_occ_b + r] = v[u][f] * invb[f] + cb[f];
+        }
+    }
+    __syncthreads();
+    for (int r0 = 0; r0 < rows_f; r0 += kRows * kOccStatesThreads) {
+        Real v[kRows][F];
+        uint32_t at[kRows];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int r = r0 + u * kOccStatesThreads + tid;
+            at[u] = r < rows_f ? row_occ[r] : 0u;
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                v[u][f] = r < rows_f && live(f) ? ar[(size_t)f * rows_f + r] : (Real)0;
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int r = r0 + u * kOccStatesThreads + tid;
+            if (r >= rows_f) break;
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                prod[f * pstride + (at[u] >> 16)] = v[u][f] * XB[f * p.lds_rows_occ_b + (at[u] & 0xffffu)];
+        }
+    }
+    __syncthreads();
+    float* g0 = p.grad + ((size_t)b * p.T + (t0 - 1)) * P;
+    const int lane8 = tid & 7;
+    for (int d = tid >> 3; d < P; d += kOccStatesThreads / 8) {
+        const int i0 = first[d], i1 = first[d + 1];
+        Real sum[F];
+#pragma unroll
+        for (int f = 0; f < F; ++f) sum[f] = 0;
+        for (int i = i0 + lane8; i < i1; i += 8) {
+#pragma unroll
+            for (int f = 0; f < F; ++f) sum[f] += prod[f * pstride + i];
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            sum[f] = dpp_add<0xB1, 0xf>(sum[f]);   // quad_perm [1,0,3,2]
+            sum[f] = dpp_add<0x4E, 0xf>(sum[f]);   // quad_perm [2,3,0,1]
+            sum[f] = dpp_add<0x141, 0xf>(sum[f]);  // row_half_mirror: the other quad of the eight
+        }
+        // lane f of the eight writes frame f's entry
+        float out = 0.f;
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+            if (lane8 == f) out = scale[f] == (Real)0 ? 0.f : (float)(scale[f] * sum[f]);
+        if (lane8 < F && live(lane8)) {
+            float* g = g0 + (size_t)lane8 * P + d;
+            *g = p.accumulate ? *g + out : out;
+        }
+    }
+}
+
 // ---- kernel variants ---------------------------------------------------------
 using RecKernel = void (*)(FbParams);
 constexpr int kHybridSlots = 36;
@@ -2354,16 +2472,23 @@ hipError_t configure_kernels()
     }
     const void* fns[] = {reinterpret_cast<const void*>(k_occ<float>),
                          reinterpret_cast<const void*>(k_occ<double>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 1>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 2>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 4>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 1>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 2>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 4>),
                          reinterpret_cast<const void*>(k_occ_planes<4, 8192>),
                          reinterpret_cast<const void*>(k_occ_planes<2, 16384>),
                          reinterpret_cast<const void*>(k_occ_planes<2, 32768>),
                          reinterpret_cast<const void*>(k_occ_planes<1, 32768>),
                          reinterpret_cast<const void*>(k_occ_planes<1, 49152>)};
-    for (const void* f : fns) {
+    constexpr size_t kByPointer = 8;  // the first of them take their LDS by pointer
+    for (size_t i = 0; i < sizeof fns / sizeof fns[0]; ++i) {
         hipError_t e =
-            hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
-        if (f != fns[0] && f != fns[1] && (e = no_static_lds(f)) != hipSuccess) return e;
+        if (i >= kByPointer && (e = no_static_lds(fns[i])) != hipSuccess) return e;
     }
     return hipSuccess;
 }
@@ -2398,6 +2523,21 @@ int occ_plane_frames(int rows, int occ_rows, int most)
             occ_plane_lds_bytes(rows, occ_rows, f) <= 160 * 1024)
             return f;
     return 0;
+}
+
+static size_t occ_states_lds_bytes(int rows_f, int rows_b, int frames, bool wide)
+{
+    return (size_t)frames * (rows_f + 1 + rows_b) * (wide ? 8 : 4);
+}
+
+// Four frames share a workgroup's tables while four workgroups fit a compute unit (their
+// loads cover each other's), fewer frames for larger graphs; one frame of the largest
+// graph (16,384 rows in fp32, 8,192 in fp64) takes 128 KB.
+int occ_states_frames(int rows_f, int rows_b, bool wide)
+{
+    for (int f : {4, 2})
+        if (occ_states_lds_bytes(rows_f, rows_b, f, wide) <= 40 * 1024) return f;
+    return 1;
 }
 
 size_t occ_plane_lds_bytes(int rows, int occ_rows, int frames)
@@ -2462,7 +2602,15 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
         LFMMI_EVQ(2)
         const int tq = std::min(bk.tmax[q], p.T);
         if (tq > 0) {
-            if (!wide && shape.occ_multi > 0) {
+            if (shape.occ_states > 0) {
+                const int F = shape.occ_states;
+                void (*fn)(FbParams) = F == 4   ? k_occ_states<Real, 4>
+                                       : F == 2 ? k_occ_states<Real, 2>
+                                                : k_occ_states<Real, 1>;
+                hipLaunchKernelGGL(fn, dim3((tq + F - 1) / F, nb), dim3(kOccStatesThreads),
+                                   occ_states_lds_bytes(p.lds_rows_occ_a, p.lds_rows_occ_b, F, wide),
+                                   on, pq);
+            } else if (!wide && shape.occ_multi > 0) {
                 const int F = shape.occ_multi;
                 const int per_wg = F * shape.occ_groups;
                 dim3 grid((tq + per_wg - 1) / per_wg, nb);

@@ -1016,6 +1016,23 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
             out->row_pdf[d].assign((size_t)ar.num_slices * kLanes, 0);
             for (int32_t s = 0; s < S; ++s) out->row_pdf[d][ar.pos[s]] = std::max(pdf_of[s], 0);
         }
+        out->row_occ.clear();
+        out->pdf_states.clear();
+        if (by_dst) {
+            std::vector<int32_t>& first = out->pdf_states;
+            first.assign((size_t)num_pdfs + 1, 0);
+            for (int32_t s = 0; s < S; ++s)
+                if (pdf_of[s] >= 0) ++first[pdf_of[s] + 1];
+            for (int32_t d = 0; d < num_pdfs; ++d) first[d + 1] += first[d];
+            std::vector<int32_t> next(first.begin(), first.end() - 1);
+            out->row_occ.assign((size_t)af.num_slices * kLanes, (uint32_t)first[num_pdfs] << 16);
+            for (size_t r = 0; r < out->row_occ.size(); ++r) {  // rows in order: places in row order
+                const int32_t s = out->ord[0].row_id[r];
+                if (s < 0) continue;
+                const uint32_t place = pdf_of[s] < 0 ? first[num_pdfs] : next[pdf_of[s]]++;
+                out->row_occ[r] = (uint32_t)ab.pos[s] | (place << 16);
+            }
+        }
     }
     // leak target: BWD adds the same amount to every state; FWD adds pi, which
     // is one constant when pi is uniform. Otherwise (or when another graph of

@@ -70,6 +70,12 @@ struct PackedGraph {
     // states nothing enters); filled only when the flag is set.
     bool pdf_by_dst = false;
     std::vector<int32_t> row_pdf[2];
+    // ... and, filled with it, what the occupancy pass by entered state reads:
+    // row_occ[FWD row] = the BWD row of the row's state | place << 16, the places being
+    // the states sorted by pdf (pdf d's: pdf_states[d] .. pdf_states[d + 1] - 1);
+    // padding rows and states nothing enters have the place after the last.
+    std::vector<uint32_t> row_occ;
+    std::vector<int32_t> pdf_states;  // [num_pdfs + 1]
     // OCC: a frame's row sums are stored sorted by pdf: the sum of row position
     // slice * 64 + lane is word row_slot[position]; pdf d owns words pdf_first[d] ..
     // pdf_first[d + 1] - 1, added up in that order (padding rows: the words after)

@@ -1,0 +1,61 @@
+"""GPU parity for graphs whose arcs all carry the pdf-id of the state they enter, against
+the fp64 CPU oracle, at the sizes where their kernels change shape.
+
+Tolerances as in test_gpu_parity.py: objf 1e-4 relative, gradient 1e-4 absolute."""
+import numpy as np
+import pytest
+
+from oracle import lfmmi_oracle as oracle
+from paper_2005_09824_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def by_state_graph(rng, S, k, P, init="uniform", some_final=False):
+    """A random graph whose pdf-ids are a function of the entered state."""
+    g = workloads.random_den_graph(rng, S, k, P, 0.5)
+    g["pdf"] = rng.integers(0, P, S).astype(np.int32)[g["dst"]]
+    if init == "varied":
+        p = rng.uniform(0.1, 1.0, S)
+        g["init_prob"] = (p / p.sum()).astype(np.float32)
+    if some_final:
+        fin = (rng.random(S) < 0.5).astype(np.float32)
+        fin[0] = 1.0
+        g["final_prob"] = fin
+    return g
+
+
+def parity(g, lengths, T, leak=1e-5, seed=4):
+    rng = np.random.default_rng(seed)
+    P, B = g["num_pdfs"], len(lengths)
+    lengths = np.asarray(lengths, np.int32)
+    x = rng.normal(0, 2, (B, T, P)).astype(np.float32)
+    for b in range(B):
+        x[b, lengths[b]:] = np.nan
+    h = binding.lfmmi_graph_create(g)
+    torch = pytest.importorskip("torch")
+    objf, grad, status = binding.lfmmi_forward_backward(h, torch.from_numpy(x).cuda(), lengths, leak)
+    torch.cuda.synchronize()
+    h.close()
+    lz, gamma = oracle.forward_backward(g, x, lengths, leak)
+    assert np.all(status.cpu().numpy() == 0)
+    assert np.all(np.abs(objf.cpu().numpy() - lz) <= 1e-4 * np.maximum(np.abs(lz), 1.0))
+    err = np.abs(grad.cpu().numpy().astype(np.float64) - gamma)
+    assert err.max() <= 1e-4, err.max()
+    for b in range(B):
+        assert np.all(grad[b, lengths[b]:].cpu().numpy() == 0.0)
+
+
+# occupancies added up over states: four, two and one frames per workgroup in fp32 and
+# fp64, lengths around multiples of them, pdfs nothing enters, one pdf that most states carry
+@pytest.mark.parametrize("S,k,P,some_final", [
+    (1, 0, 1, False), (65, 3, 200, False), (1200, 2, 9, False), (1300, 2, 84, False),
+    (2500, 2, 84, False), (9000, 2, 300, False),
+    (64, 3, 5, True), (600, 2, 84, True), (700, 2, 84, True), (1500, 2, 30, True), (3000, 2, 84, True),
+])
+def test_occupancies_by_state(S, k, P, some_final):
+    rng = np.random.default_rng(S)
+    g = by_state_graph(rng, S, k, P, some_final=some_final)
+    if P == 9:
+        g["pdf"] = np.where(g["dst"] % 8 == 0, g["pdf"], 3).astype(np.int32)
+    parity(g, [9, 1, 8, 0, 5], 11)
