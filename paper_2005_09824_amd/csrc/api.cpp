@@ -70,6 +70,7 @@ struct lfmmi_graph {
     bool has_wb = false;  // arcs carry a per-arc leak factor (some init_prob is not uniform)
     bool rec_grouped = false;  // every arc takes the pdf of the state it enters and the
                                // recursion runs the variant without an emission gather
+    bool rec_short = false;    // ... and its variant for waves that own one short slice
     bool occ_states = false;   // ... and the occupancies are added up over states, not arcs
 
     // device copy
@@ -279,28 +280,35 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
                 h->rec_yrep = false;
             // Graphs whose arcs all take the pdf of the state they enter: the variant
             // without an emission gather, when every wave's arcs fit its registers
-            // (two per slot), the workgroup's threads can stage an emission value per row
-            // in the passes that variant has, and the rows leave the last slice of the
-            // LDS map to the zero word.
-            // It pays from about a dozen slots per wave on: what it saves grows with the
-            // arcs, what beta's second barrier costs does not (the 128 numerator graphs
-            // of the e2e workload, 4 slots per wave: 366 us with it, 314 us without).
+            // (two per slot) and the workgroup's threads can stage an emission value per row
+            // in the passes that variant has. From about a dozen slots per wave on: what it
+            // saves grows with the arcs, staging an emission per row does not.
             // LFMMI_GROUPED=0 never takes it, 2 takes it whenever it applies.
             auto grouped_slots = [&]() {
                 const int want = env_int("LFMMI_GROUPED", 1);
                 if (want == 0 || h->rec_hubs) return 0;
                 if (want != 2 && max_slots < 16) return 0;
                 const int rows_most = std::max(h->max_rows_f, h->max_rows_b);
-                if (rows_most > (h->wide ? 4096 : 8192) - kLanes) return 0;
-                if (rows_most > rec_grouped_max_rows(waves * kLanes)) return 0;
+                if (rows_most > rec_grouped_max_rows(h->wide, waves * kLanes)) return 0;
                 for (int32_t g = 0; g < n; ++g)
                     if (!h->packed[g].pdf_by_dst) return 0;
                 return rec_grouped_slots(h->wide, h->has_wb, max_slots, waves * kLanes);
             };
+            // Such graphs with at most one slice of few slots per wave (per-utterance
+            // numerators): the straight-line variant.
+            auto short_slots = [&]() {
+                if (env_int("LFMMI_GROUPED", 1) != 1 || h->rec_hubs || !h->occ_states) return 0;
+                for (int32_t g = 0; g < n; ++g)
+                    for (int o = 0; o < 2; ++o)
+                        if (h->packed[g].ord[o].num_slices > waves) return 0;
+                return rec_short_slots(h->wide, max_slots - (h->has_wb ? 1 : 0), waves * kLanes);
+            };
             h->occ_states = st == LFMMI_OK && env_int("LFMMI_GROUPED", 1) != 0;
             for (int32_t g = 0; g < n && h->occ_states; ++g) h->occ_states = h->packed[g].pdf_by_dst;
-            const int gslots = st == LFMMI_OK ? grouped_slots() : 0;
-            h->rec_grouped = gslots > 0;
+            int gslots = st == LFMMI_OK ? short_slots() : 0;
+            h->rec_short = gslots > 0;
+            if (st == LFMMI_OK && gslots == 0) gslots = grouped_slots();
+            h->rec_grouped = gslots > 0 && !h->rec_short;
             auto resident = [&](int slots, int wv) {
                 return rec_register_slots(h->wide, h->has_wb, h->rec_yrep, h->rec_hubs, slots,
                                           wv * kLanes);
@@ -440,6 +448,8 @@ lfmmi_status upload(lfmmi_graph* h)
     const size_t at_vb = reserve<float>(&total, n_vec);
     const size_t at_vfin = reserve<float>(&total, n_vec);
     const size_t at_rowpdfs = reserve<int32_t>(&total, n_vec);
+    const size_t at_inw = reserve<double>(&total, n_vec);
+    const size_t at_inwpi = reserve<double>(&total, n_vec);
     const size_t at_rowocc = reserve<uint32_t>(&total, n_vec);
     const size_t at_pstates = reserve<int32_t>(&total, n_pstates);
     const size_t at_rowpdf = reserve<int32_t>(&total, n_rowpdf);
@@ -498,6 +508,11 @@ lfmmi_status upload(lfmmi_graph* h)
                 if (pg.row_pdf[o].size() == nrow)
                     std::memcpy(host.data() + at_rowpdfs + (size_t)d.vec_at * 4, pg.row_pdf[o].data(),
                                 nrow * 4);
+                if (pg.in_w[o].size() == nrow) {
+                    std::memcpy(host.data() + at_inw + (size_t)d.vec_at * 8, pg.in_w[o].data(), nrow * 8);
+                    std::memcpy(host.data() + at_inwpi + (size_t)d.vec_at * 8, pg.in_wpi[o].data(),
+                                nrow * 8);
+                }
                 if (o == 0 && pg.row_occ.size() == nrow)
                     std::memcpy(host.data() + at_rowocc + (size_t)d.vec_at * 4, pg.row_occ.data(),
                                 nrow * 4);
@@ -536,6 +551,8 @@ lfmmi_status upload(lfmmi_graph* h)
     h->dg.vb = reinterpret_cast<const float*>(base + at_vb);
     h->dg.vfin = reinterpret_cast<const float*>(base + at_vfin);
     h->dg.row_pdf = reinterpret_cast<const int32_t*>(base + at_rowpdfs);
+    h->dg.in_w = reinterpret_cast<const double*>(base + at_inw);
+    h->dg.in_wpi = reinterpret_cast<const double*>(base + at_inwpi);
     h->dg.row_occ = reinterpret_cast<const uint32_t*>(base + at_rowocc);
     h->dg.pdf_states = reinterpret_cast<const int32_t*>(base + at_pstates);
     h->dg.row_slot = reinterpret_cast<const int32_t*>(base + at_rowpdf);
@@ -685,6 +702,7 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
     shape.rec_hybrid = h->rec_hybrid;
     shape.rec_hubs = h->rec_hubs ? 1 : 0;
     shape.rec_grouped = h->rec_grouped ? 1 : 0;
+    shape.rec_short = h->rec_short ? 1 : 0;
     shape.profile_rec_only = h->profile == 2 ? 1 : 0;
     shape.rec_has_wb = h->has_wb ? 1 : 0;
     shape.occ_states =

@@ -44,6 +44,11 @@ struct DeviceGraph {
     const int32_t* pdf_first;   // OCC: the sums of pdf d's rows are words pdf_first[d] ..
                                 // pdf_first[d + 1] - 1 of a frame's row sums
     const int32_t* row_slot;    // OCC: the word the sum of row (slice * 64 + lane) goes to
+    // Sums over the arcs into a row's state (graphs whose pdf belongs to the entered state,
+    // zeros for others; indexed like vinit): in_w their weights, in_wpi their weights times
+    // the initial probability of the state they leave.
+    const double* in_w;
+    const double* in_wpi;
     // Occupancies by entered state (k_occ_states); zeros for other graphs.
     const uint32_t* row_occ;    // per FWD row (indexed like vinit): its state's BWD row, and above
                                 // it (<< 16) the place of its state in the order of the pdfs
@@ -100,6 +105,7 @@ struct LaunchShape {
     int rec_hybrid;    // 1: only the first slots of a wave are register-resident;
                        // 2: the same, with the LDS map for up to 12288 states
     int rec_grouped = 0;  // arcs take the emission of the entered state: no emission gather
+    int rec_short = 0;    // ... and every wave owns one short slice (RecShort)
     int occ_states = 0;  // frames per workgroup of the occupancy kernel by entered state (0: by arc)
     int occ_threads;   // workgroup size of the occupancy kernel
     int occ_frames;    // frames per occupancy workgroup (frame-at-a-time kernel)
@@ -153,7 +159,10 @@ int rec_hybrid_slots(bool wide, bool has_wb, bool yrep, bool hubs, int map /* 1:
 // Slots of the variant for graphs whose arcs take the pdf of the entered state
 // (0: none for this shape), and the rows it stages emissions for with this many threads.
 int rec_grouped_slots(bool wide, bool has_wb, int max_wave_slots, int threads);
-int rec_grouped_max_rows(int threads);
+int rec_grouped_max_rows(bool wide, int threads);
+// Arc slots per wave of the variant for graphs as above whose waves own one slice each
+// (0: none for this shape).
+int rec_short_slots(bool wide, int max_wave_slots, int threads);
 size_t occ_lds_bytes(int rows_a, int rows_b, int occ_rows, bool wide);
 int occ_plane_frames(int rows, int occ_rows, int most);
 size_t occ_plane_lds_bytes(int rows, int occ_rows, int frames);

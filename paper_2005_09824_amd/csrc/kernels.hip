@@ -112,6 +112,30 @@ __device__ __forceinline__ const float2* wb_pairs(const FbParams& p, const OrdDe
 __device__ __forceinline__ uint2 rec_lo(const uint4 r) { return make_uint2(r.x, r.y); }
 __device__ __forceinline__ uint2 rec_hi(const uint4 r) { return make_uint2(r.z, r.w); }
 
+// The records of slots first .. first + NSLOT - 1 (`first` even) of this lane into keys and
+// weights: all loads go out before any is waited for (one after the other they took 10 us of a
+// launch with 24 slots). Slots from `count` on are empty.
+template <int NSLOT>
+__device__ __forceinline__ void load_records(const FbParams& p, const OrdDesc& od, const int lane,
+                                             const int first, const int count, uint32_t (&key)[NSLOT],
+                                             float (&w)[NSLOT])
+{
+    const uint4* recs = rec_pairs(p, od, lane);
+    const int last = max((od.total_slots >> 1) - 1, 0);  // (a load past it fetches it again)
+    uint4 r[NSLOT / 2];
+#pragma unroll
+    for (int q = 0; q < NSLOT / 2; ++q)
+        r[q] = od.total_slots > 0 ? recs[(size_t)min((first >> 1) + q, last) * 64] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < NSLOT / 2; ++q) {
+        const bool on0 = 2 * q < count, on1 = 2 * q + 1 < count;
+        key[2 * q] = on0 ? r[q].x : 0u;
+        w[2 * q] = on0 ? __uint_as_float(r[q].y) : 0.f;
+        key[2 * q + 1] = on1 ? r[q].z : 0u;
+        w[2 * q + 1] = on1 ? __uint_as_float(r[q].w) : 0.f;
+    }
+}
+
 // The recursion of one (sequence, direction).
 //
 // Real   float when every state of the graph is final (denominator-like: the
@@ -387,6 +411,14 @@ __device__ __forceinline__ double lane_value(double v, int l)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// v with lane L holding `value` (wave-uniform) instead.
+template <int L>
+__device__ __forceinline__ int write_lane(int v, const int value)
+{
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(value), "n"(L));
+    return v;
+}
+
 // Sum over the 64 lanes, returned as a wave-uniform value.
 template <typename Real>
 __device__ __forceinline__ Real wave_sum_uniform(Real v)
@@ -407,7 +439,7 @@ __device__ __forceinline__ float half_wave_sums(float a, float b)
                                                      false, false);
     float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     v = row16_allsum(v);
-    return dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x142, 0xf>(v);  // row_bcast:15: row 1 gets row 0's sum, row 3 row 2's
 }
 __device__ __forceinline__ double half_wave_sums(double a, double b)
 {
@@ -418,7 +450,7 @@ __device__ __forceinline__ double half_wave_sums(double a, double b)
     double v = __longlong_as_double(((long long)hi[0] << 32) | lo[0]) +
                __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
     v = row16_allsum(v);
-    return dpp_add<0x142, 0xa>(v);
+    return dpp_add<0x142, 0xf>(v);
 }
 
 // Lane 63 returns the sum over the wave (other lanes: partial sums).
@@ -426,8 +458,8 @@ template <typename Real>
 __device__ __forceinline__ Real wave_sum_lane63(Real v)
 {
     v = row16_allsum(v);
-    v = dpp_add<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
-    return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    v = dpp_add<0x142, 0xf>(v);     // row_bcast:15: rows 1 and 3 get the sums of 0 and 2
+    return dpp_add<0x143, 0xf>(v);  // row_bcast:31: row 3 gets the sum of rows 0 and 1
 }
 
 // ---------------------------------------------------------------------------
@@ -441,7 +473,7 @@ __device__ __forceinline__ Real wave_sum_lane63(Real v)
 constexpr uint32_t kRegX1 = 32768, kRegY0 = 65536, kRegY1 = 98304, kRegPart = 131072;
 constexpr uint32_t kRegYZero = 32764;  // byte offset of the zero word inside a Y buffer
 
-__host__ __device__ constexpr size_t reg_lds_bytes() { return kRegPart + 3 * 32 * sizeof(double); }
+__host__ __device__ constexpr size_t reg_lds_bytes() { return kRegPart + 4 * 32 * sizeof(double); }
 
 // LDS access by absolute byte address (the kernel's dynamic LDS starts at 0: it
 // declares no static LDS), so that the address register goes straight into the
@@ -994,9 +1026,6 @@ struct RecRegs {
                      (dir == 0 ? sd.alpha_at : sd.beta_at);
         Real* scalN = static_cast<Real*>(p.scal) + (size_t)(dir * 2) * p.scal_total + sd.scal_at;
         Real* scalS = scalN + p.scal_total;
-        const uint4* recs = rec_pairs(p, od, lane);
-        // one record: slot s of this lane is the (s & 1)-th half of pair s >> 1
-        const uint2* rec1 = reinterpret_cast<const uint2*>(recs);
         const float* wb1 = reinterpret_cast<const float*>(wb_pairs(p, od, lane));
         const int32_t* so = p.g.slice_off + od.slice_off_at;
         const Real eps = (Real)p.leak;
@@ -1036,16 +1065,19 @@ struct RecRegs {
             so_tab = so[max(min(sl_stream + lane, s1 - 1), 0) + 1];
             stream_end = so[s1];
         }
+        load_records<NSLOT>(p, od, lane, first, nsl, ya, wr);
+        if constexpr (HAS_WB) {
+#pragma unroll
+            for (int i = 0; i < NSLOT; ++i)
+                wbr[i] = i < nsl ? wb1[(size_t)((first + i) >> 1) * 128 + ((first + i) & 1)] : 0.f;
+        }
 #pragma unroll
         for (int i = 0; i < NSLOT; ++i) {
-            const bool on = i < nsl;
             const bool closing = HAS_WB && ((mask >> i) & 1);  // holds a[row], no arc
-            const size_t at = (size_t)((first + i) >> 1) * 128 + ((first + i) & 1);
-            const uint2 r = on ? rec1[at] : make_uint2(0u, 0u);
-            const uint32_t x_addr = (r.x & 0xffffu) * (kRB / 4u);
-            const uint32_t y_addr = kRegY0 + ((on && !closing) ? y_offset(r.x) : kRegYZero);
-            wr[i] = __uint_as_float(r.y);
-            if (HAS_WB) wbr[i] = (on && !closing) ? wb1[at] : 0.f;
+            const uint32_t key = ya[i];
+            const uint32_t x_addr = (key & 0xffffu) * (kRB / 4u);
+            const uint32_t y_addr = kRegY0 + ((i < nsl && !closing) ? y_offset(key) : kRegYZero);
+            if (HAS_WB && closing) wbr[HAS_WB ? i : 0] = 0.f;
             // opaque from here on: the values stay in their registers for the whole
             // time loop instead of being re-derived from the record each frame
             if constexpr (kPacked) {
@@ -1189,51 +1221,75 @@ struct RecRegs {
 // ---------------------------------------------------------------------------
 // The register-resident recursion for graphs whose arcs all take the emission of
 // the state they enter (PackedGraph::pdf_by_dst; graphs expanded from HMMs whose
-// states emit, Section 4.2): no emission gather per arc.
+// states emit, Section 4.2): no emission gather per arc, one barrier per step.
 //   alpha (rows = to-states): the emission is a function of the row,
-//       v_t[j] = e_t[pdf_j] * ((1/n) sum_a w_a v[from_a] + (eps s / n) sum_a w_a b[from_a]),
-//     one gather per arc and one multiply where a slice ends (normalisation is lazy
-//     as in RecRegs; the second sum does not depend on the frame).
-//   beta (rows = from-states): the emission is a function of the gathered state, so
-//     it is folded into the stored vector: after the barrier that ends a step every
-//     lane rewrites its own rows, u[j] = e[pdf_j] * (v[j] / n + eps s / n), a second
-//     barrier follows, then v_new[i] = sum_a w_a u[to_a], one gather per arc.
-// What is staged per step is the emission per row, EY[row] = e[pdf_row] (thread i
-// fetches the values of rows i, i + threads, ... two steps ahead and stores them
-// one step ahead), not a replicated emission row.
-// LDS map: X0 [0, 32K)  X1 [32K, 64K)  EY0 [64K, 96K)  EY1 [96K, 128K)  partial sums.
-// The last value of each X buffer is a zero nobody writes: closing slots gather it
-// (rows <= capacity - 64 is checked on the host).
+//       v_t[j] = e_t[pdf_j] * (sum_a w_a v[from_a] / n + (eps s / n) * in_wpi[j])
+//     (normalisation is lazy as in RecRegs; the leak's share of a row, the sum of
+//     w_a pi[from_a], does not depend on the frame).
+//   beta (rows = from-states): the emission is a function of the gathered state, so what
+//     LDS holds is u_t[j] = e_t[pdf_j] * (v_t[j] / n_t + eps s_t / n_t), and
+//     v_{t-1}[i] = sum_a w_a u_t[to_a]. A row can only be stored that way at once if
+//     n_{t-1} and s_{t-1} are known before the rows are: they are linear in u_t,
+//       n_{t-1} = sum_j in_w[j] u_t[j],   s_{t-1} = sum_j in_wpi[j] u_t[j],
+//     so every step adds up those products of the vector it stores, as alpha adds up its
+//     values, and the next step has both scalars by the time its first row is done.
+// n is kept as the power of two below the sum: any positive scale cancels, and its
+// inverse is then one subtraction of exponents.
+// Bound by the gathers and the issue of a step (16 waves, up to 36 slots each). The launch of
+// the eight longest sequences (500 frames) of an HMM-expanded denominator of 2,016 states whose
+// fullest wave has 36 slots: 617 us; 837 us with the hybrid recursion, which such a graph took
+// before (the variant with two barriers in beta held 32 slots).
 // ---------------------------------------------------------------------------
+// N: the largest power of two not above n (0 below the normal range, and nothing beyond 2^126,
+// 2^1022 in fp64); inv: its inverse, without a test for totals that are zero or not finite:
+// they leave log Z at -inf or NaN whatever the scale is, and the rows that follow at zero
+// or not finite.
+__device__ __forceinline__ void pow2_scale(const float n, float* N, float* inv)
+{
+    const uint32_t e = min(__float_as_uint(n) & 0x7f800000u, 0x7e800000u);
+    *N = __uint_as_float(e);
+    *inv = __uint_as_float(0x7f000000u - e);
+}
+__device__ __forceinline__ void pow2_scale(const double n, double* N, double* inv)
+{
+    const uint32_t hi = (uint32_t)((unsigned long long)__double_as_longlong(n) >> 32);
+    const uint32_t e = min(hi & 0x7ff00000u, 0x7fd00000u);
+    *N = __longlong_as_double((long long)((unsigned long long)e << 32));
+    *inv = __longlong_as_double((long long)((unsigned long long)(0x7fe00000u - e) << 32));
+}
+
+// LDS map: X0 [0, 32K)  X1 [32K, 64K)  EY0 [64K, 80K)  EY1 [96K, 112K)  partial sums at
+// 128K; the sums per row behind the EY buffers (in_wpi for alpha; in_w and in_wpi for beta).
+// EY[row] = e[pdf_row]: thread i fetches the values of rows i, i + threads, ... two steps
+// ahead and stores them one step ahead.
 constexpr int kGroupedPasses = 4;  // rows <= kGroupedPasses * threads in this variant
+constexpr uint32_t kRowSums0 = kRegY0 + 16384u, kRowSums1 = kRegY1 + 16384u;
+__host__ __device__ constexpr int grouped_rows(bool wide) { return wide ? 2048 : 4096; }
 
 template <typename Real, bool HAS_WB, int NSLOT, int NT>
 struct RecGrouped {
     static constexpr uint32_t kRB = sizeof(Real);
     static constexpr int kYPass = kGroupedPasses;
-    static constexpr int kChunk = 4;  // beta: slices whose rows are folded at a time
     static constexpr int kPrefetch = NT >= 1024 ? 2 : 4;  // (twice the depth measured no faster)
     static constexpr int kBurst = (kPrefetch == 2 && NSLOT >= 8) ? 4 : kPrefetch;  // see RecRegs
     static constexpr int kTailSlots = 4;
     static constexpr int kStageAt = NSLOT - kTailSlots > 4 ? 4 : 0;
-    static constexpr uint32_t kZeroX = kRegX1 - kRB;  // byte offset of the zero inside an X buffer
     static_assert(NSLOT % 2 == 0 && kPrefetch % 2 == 0, "slots are handled in pairs");
     static_assert(NSLOT <= 64, "one bit per resident slot in the 64-bit slice-end mask");
 
     uint32_t xa[NSLOT];  // byte address of the gathered state value inside X0
-    float wr[NSLOT];     // arc weight; closing slots: the row's leak-dot weight
-    float wbr[HAS_WB ? NSLOT : 1];
+    float wr[NSLOT];     // arc weight (0 in closing slots: their row weight is not used here)
     float yreg[kYPass];     // emission values of rows tid + i * threads, two steps ahead
     uint32_t ysrc[kYPass];  // byte offset of such a row's pdf inside an emission row
     uint32_t ydst[kYPass];  // byte offset of the row inside an EY buffer
     int ypasses;            // passes in which this wave holds any row (wave-uniform)
-    int nslices;            // slices this wave owns (wave-uniform)
 
     const float* e2;
     Real* trow;
     Real* sN;
     Real* sS;
     ptrdiff_t estep, tstep, sstep;
+    Real inv, c;  // beta: scale and leak of the last vector (its rows end up in the trellis only)
 
     __device__ __forceinline__ void load_y()
     {
@@ -1253,79 +1309,35 @@ struct RecGrouped {
     // DIR 0: alpha, 1: beta. PAR = k & 1 as in RecRegs.
     template <int PAR, int DIR>
     __device__ __forceinline__ void step(const int k, const int T, const int tid, const int lane,
-                                         const Real eps, const Real aconst, const Real bconst,
-                                         const uint64_t mask, const uint32_t row4_first,
-                                         const uint32_t ey_first, const uint32_t part_at,
-                                         const int nsl)
+                                         const Real eps, const Real aconst, const uint64_t mask,
+                                         const uint32_t row4_first, const uint32_t ey_first,
+                                         const uint32_t part_at, const int nsl)
     {
         constexpr uint32_t xc = PAR ? 0u : kRegX1, xn = PAR ? kRegX1 : 0u;
         constexpr uint32_t eyc = PAR ? kRegY0 : kRegY1, eyn = PAR ? kRegY1 : kRegY0;
         constexpr uint32_t pc = kRegPart + (PAR ? 0u : 32u * kRB), pn = kRegPart + (PAR ? 32u * kRB : 0u);
         constexpr int kp = kPrefetch, kr = kBurst;
+        // alpha: s is n. beta: s is a constant times n when pi is uniform
+        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
 
-        Real pv = lds_ldr<Real>(pc + (lane & (HAS_WB ? 31 : 15)) * kRB);
+        Real pv = lds_ldr<Real>(pc + (lane & (kTwoSums ? 31 : 15)) * kRB);
         Real xv[kr];
-        Real own[DIR == 1 ? kChunk : 1];
-        float eown[DIR == 1 ? kChunk : 1];
-        float e_close = 0.f;  // alpha: emission of the row whose slice ends next
-        if constexpr (DIR == 0) {
 #pragma unroll
-            for (int i = 0; i < kr && i < NSLOT; ++i) xv[i] = lds_ldr<Real>(xc + xa[i]);
-            e_close = lds_ld(eyc + ey_first);
-        } else {
-            // this lane's own rows of the vector the last step wrote, and their
-            // emissions: the first kChunk slices now, with the partial sums
-#pragma unroll
-            for (int q = 0; q < kChunk; ++q)
-                if (q < nslices) {
-                    own[q] = lds_ldr<Real>(xc + row4_first + (uint32_t)q * 64u * kRB);
-                    eown[q] = lds_ld(eyc + ey_first + (uint32_t)q * 256u);
-                }
-        }
+        for (int i = 0; i < kr && i < NSLOT; ++i) xv[i] = lds_ldr<Real>(xc + xa[i]);
+        // emission and sums of the row whose slice ends next
+        float e_close = lds_ld(eyc + ey_first);
+        Real r_close = lds_ldr<Real>(kRowSums0 + row4_first);
+        Real g_close = 0;
+        if (kTwoSums) g_close = lds_ldr<Real>(kRowSums1 + row4_first);
         asm volatile("" ::: "memory");
         pv = row16_allsum(pv);
-        const Real N = lane_value(pv, 0);
-        const Real Sd = HAS_WB ? lane_value(pv, 16) : aconst * N;
-        Real inv = 0;
-        if (N > 0) {
-            if constexpr (sizeof(Real) == 4) {
-                inv = __builtin_amdgcn_rcpf(N);
-                inv = fmaf(fmaf(-N, inv, 1.f), inv, inv);
-            } else {
-                inv = __builtin_amdgcn_rcp((double)N);
-                inv = fma(fma(-N, inv, (Real)1), inv, inv);
-                inv = fma(fma(-N, inv, (Real)1), inv, inv);
-            }
-        }
-        const Real c = eps * Sd * inv;
-        const Real cb = HAS_WB ? c : c * bconst;
-        if constexpr (DIR == 1) {
-            // fold normalisation, leak and emission into the stored vector, in place
-#pragma unroll
-            for (int q = 0; q < kChunk; ++q)
-                if (q < nslices)
-                    lds_st(xc + row4_first + (uint32_t)q * 64u * kRB,
-                           (Real)eown[q] * (own[q] * inv + cb));
-            for (int q0 = kChunk; q0 < nslices; q0 += kChunk) {  // a wave with many slices
-#pragma unroll
-                for (int q = 0; q < kChunk; ++q)
-                    if (q0 + q < nslices) {
-                        own[q] = lds_ldr<Real>(xc + row4_first + (uint32_t)(q0 + q) * 64u * kRB);
-                        eown[q] = lds_ld(eyc + ey_first + (uint32_t)(q0 + q) * 256u);
-                    }
-#pragma unroll
-                for (int q = 0; q < kChunk; ++q)
-                    if (q0 + q < nslices)
-                        lds_st(xc + row4_first + (uint32_t)(q0 + q) * 64u * kRB,
-                               (Real)eown[q] * (own[q] * inv + cb));
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < kr && i < NSLOT; ++i) xv[i] = lds_ldr<Real>(xc + xa[i]);
-            asm volatile("" ::: "memory");
-        }
+        const Real nr = lane_value(pv, 0);
+        const Real Sd = kTwoSums ? lane_value(pv, 16) : (DIR == 0 ? nr : aconst * nr);
+        Real N;
+        pow2_scale(nr, &N, &inv);
+        c = eps * Sd * inv;
 
-        Real acc1 = 0, acc2 = 0, n = 0, s = 0;
+        Real acc = 0, n = 0, s = 0;
         uint64_t left = mask;
         int next_close = left ? __builtin_ctzll(left) : 64;
         uint32_t row4 = row4_first;  // byte offset of this lane's row in a state vector
@@ -1343,7 +1355,7 @@ struct RecGrouped {
             else if (i == (NSLOT / 3) * 2) __builtin_amdgcn_s_setprio(0);
             if (i == kStageAt) {
                 // emission values of step k + 1 (loaded a step ago) into the other EY
-                // buffer, the loads for step k + 2, and the scalars of step k - 1
+                // buffer, the loads for step k + 2, and the scalars
                 store_y(eyn);
                 load_y();
                 if (tid == 0) {
@@ -1358,42 +1370,45 @@ struct RecGrouped {
             }
             asm volatile("" : "+v"(x0) : "v"(x1));  // one wait for the pair
             if constexpr (sizeof(Real) == 4) {
-                acc1 = fmaf(wr[i], x0, acc1);
-                acc1 = fmaf(wr[i + 1], x1, acc1);
+                acc = fmaf(wr[i], x0, acc);
+                acc = fmaf(wr[i + 1], x1, acc);
             } else {
-                acc1 += (Real)wr[i] * x0;
-                acc1 += (Real)wr[i + 1] * x1;
+                acc += (Real)wr[i] * x0;
+                acc += (Real)wr[i + 1] * x1;
             }
-            if constexpr (DIR == 0)  // the leak's share of the row: frame-independent
-                acc2 += HAS_WB ? (Real)(wbr[HAS_WB ? i : 0] + wbr[HAS_WB ? i + 1 : 0])
-                               : (Real)(wr[i] + wr[i + 1]);
             if (__builtin_expect(i + 1 == next_close, 0)) {  // wave-uniform: a slice ends
-                Real v;
-                if constexpr (DIR == 0) v = (Real)e_close * (inv * acc1 + cb * acc2);
-                else v = acc1;
-                lds_st(xn + row4, v);
+                Real v, x;
+                if constexpr (DIR == 0) {
+                    v = x = (Real)e_close * (inv * acc + c * r_close);
+                    n += v;
+                } else {
+                    v = acc;
+                    x = (Real)e_close * (inv * acc + c);
+                    n += r_close * x;
+                    if (kTwoSums) s += g_close * x;
+                }
+                lds_st(xn + row4, x);
                 *reinterpret_cast<Real*>(tr + row4) = v;
-                n += v;
-                if (HAS_WB) s += (Real)wr[i + 1] * v;  // the closing slot's w is a[row]
-                acc1 = 0;
-                acc2 = 0;
+                acc = 0;
                 row4 += 64 * kRB;
                 ey4 += 256u;
                 left &= left - 1;
                 next_close = left ? __builtin_ctzll(left) : 64;
-                // (past the wave's last slice this reads a word nobody uses)
-                if constexpr (DIR == 0) e_close = lds_ld(eyc + ey4);
+                // (past the wave's last slice these read words nobody uses)
+                e_close = lds_ld(eyc + ey4);
+                r_close = lds_ldr<Real>(kRowSums0 + row4);
+                if (kTwoSums) g_close = lds_ldr<Real>(kRowSums1 + row4);
             }
         }
         __builtin_amdgcn_s_setprio(3);
-        if constexpr (HAS_WB) {
+        if constexpr (kTwoSums) {
             const Real ns = half_wave_sums(n, s);
             if ((lane & 31) == 31) lds_st(pn + part_at, ns);
         } else {
             const Real ns = wave_sum_lane63(n);
             if (lane == 63) lds_st(pn + part_at, ns);
         }
-        if (k + 2 < T) e2 += estep;
+        if (k + 2 + DIR < T) e2 += estep;
         trow += tstep;
         sN += sstep;
         sS += sstep;
@@ -1401,40 +1416,25 @@ struct RecGrouped {
     }
 
     template <int DIR>
-    __device__ __forceinline__ void loop(const int T, const int tid, const int lane, const Real eps,
-                                         const Real aconst, const Real bconst, const uint64_t mask,
-                                         const uint32_t row4_first, const uint32_t ey_first,
-                                         const uint32_t part_at, const int nsl)
-    {
-        int k = 1;
-        for (; k + 1 <= T; k += 2) {
-            step<1, DIR>(k, T, tid, lane, eps, aconst, bconst, mask, row4_first, ey_first, part_at, nsl);
-            step<0, DIR>(k + 1, T, tid, lane, eps, aconst, bconst, mask, row4_first, ey_first, part_at, nsl);
-        }
-        if (k <= T)
-            step<1, DIR>(k, T, tid, lane, eps, aconst, bconst, mask, row4_first, ey_first, part_at, nsl);
-    }
-
     __device__ __forceinline__ void run(const FbParams& p, const SeqDesc& sd, const OrdDesc& od,
-                                        const int b, const int dir)
+                                        const int b)
     {
+        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
         const int tid = threadIdx.x;
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int nthreads = blockDim.x;
+        const int nwaves = nthreads >> 6;
         const int T = sd.T;
         const int P = p.P;
         const int rows = od.num_slices * 64;
-        Real* trel = static_cast<Real*>(dir == 0 ? p.alpha : p.beta) +
-                     (dir == 0 ? sd.alpha_at : sd.beta_at);
-        Real* scalN = static_cast<Real*>(p.scal) + (size_t)(dir * 2) * p.scal_total + sd.scal_at;
+        Real* trel = static_cast<Real*>(DIR == 0 ? p.alpha : p.beta) +
+                     (DIR == 0 ? sd.alpha_at : sd.beta_at);
+        Real* scalN = static_cast<Real*>(p.scal) + (size_t)(DIR * 2) * p.scal_total + sd.scal_at;
         Real* scalS = scalN + p.scal_total;
-        const uint2* rec1 = reinterpret_cast<const uint2*>(rec_pairs(p, od, lane));
-        const float* wb1 = reinterpret_cast<const float*>(wb_pairs(p, od, lane));
         const int32_t* so = p.g.slice_off + od.slice_off_at;
         const Real eps = (Real)p.leak;
         const Real aconst = (Real)od.a_const;
-        const Real bconst = (Real)od.b_const;
         const float* erows = p.emis + (size_t)b * p.T * P;
 
         int s0 = 0, s1 = 0;
@@ -1446,16 +1446,12 @@ struct RecGrouped {
         }
         const int first = so[s0];
         const int nsl = so[s1] - first;
-        nslices = s1 - s0;
+        load_records<NSLOT>(p, od, lane, first, nsl, xa, wr);
 #pragma unroll
         for (int i = 0; i < NSLOT; ++i) {
-            const bool on = i < nsl;
-            const bool closing = HAS_WB && ((mask >> i) & 1);  // holds a[row], no arc
-            const size_t at = (size_t)((first + i) >> 1) * 128 + ((first + i) & 1);
-            const uint2 r = on ? rec1[at] : make_uint2(0u, 0u);
-            xa[i] = (on && !closing) ? (r.x & 0xffffu) * (kRB / 4u) : kZeroX;
-            wr[i] = __uint_as_float(r.y);
-            if (HAS_WB) wbr[i] = (on && !closing) ? wb1[at] : 0.f;
+            const bool closing = HAS_WB && ((mask >> i) & 1);  // holds no arc
+            xa[i] = (xa[i] & 0xffffu) * (kRB / 4u);
+            if (closing) wr[i] = 0.f;
             asm volatile("" : "+v"(xa[i]), "+v"(wr[i]));
         }
         // emission staging: row tid + i * threads in pass i (rows <= kYPass * threads is
@@ -1468,19 +1464,33 @@ struct RecGrouped {
             ydst[i] = (uint32_t)row * 4u;
             yreg[i] = 0.f;
         }
-        if (tid == 0) {
-            lds_st(kZeroX, (Real)0);
-            lds_st(kRegX1 + kZeroX, (Real)0);
+        // (a wave reads back only the sums of its own rows)
+        for (int sl = s0; sl < s1; ++sl) {
+            const int row = sl * 64 + lane;
+            lds_st(kRowSums0 + (uint32_t)row * kRB,
+                   (Real)(DIR == 0 ? p.g.in_wpi : p.g.in_w)[od.vec_at + row]);
+            if (kTwoSums) lds_st(kRowSums1 + (uint32_t)row * kRB, (Real)p.g.in_wpi[od.vec_at + row]);
         }
         if (tid < 64) lds_st(kRegPart + tid * kRB, (Real)0);
         __syncthreads();
 
         const uint32_t row4_first = (uint32_t)(s0 * 64 + lane) * kRB;
         const uint32_t ey_first = (uint32_t)(s0 * 64 + lane) * 4u;
-        // ---- step 0: v_0 = init into X0, partials into slot set 0
+        // Frame whose emissions meet the rows that step k stores: alpha k - 1; beta T - k - 1
+        // (folded into the vector the next step gathers). Kept inside the sequence.
+        auto frame_of = [&](int k) { return max(0, min(DIR == 0 ? k - 1 : T - k - 1, T - 1)); };
+        auto total = [&](Real a, Real bsum, const uint32_t at) {  // this wave's partial sums
+            a = wave_sum_uniform(a);
+            bsum = wave_sum_uniform(bsum);
+            if (lane == 0) {
+                lds_st(at + wave * kRB, a);
+                lds_st(at + (16 + wave) * kRB, bsum);
+            }
+        };
+        // ---- step 0: v_0 = init into X0, partial sums into set 0
         {
             Real n = 0, s = 0;
-            const int ti = dir == 0 ? 0 : T;
+            const int ti = DIR == 0 ? 0 : T;
             for (int sl = s0; sl < s1; ++sl) {
                 const int row = sl * 64 + lane;
                 const Real v = (Real)p.g.vinit[od.vec_at + row];
@@ -1489,16 +1499,8 @@ struct RecGrouped {
                 n += v;
                 s += (Real)p.g.va[od.vec_at + row] * v;
             }
-            n = wave_sum_uniform(n);
-            s = wave_sum_uniform(s);
-            if (lane == 0) {
-                lds_st(kRegPart + wave * kRB, n);
-                lds_st(kRegPart + (16 + wave) * kRB, s);
-            }
-            auto frame_of = [&](int k) {  // FWD k - 1, BWD T - k, kept inside the sequence
-                const int fr = dir == 0 ? k - 1 : T - k;
-                return max(0, min(fr, T - 1));
-            };
+            // beta: into set 1 first, the vector itself needs the totals
+            total(n, s, kRegPart + (DIR == 0 ? 0u : 32u * kRB));
             if (T > 0) {
                 e2 = erows + (size_t)frame_of(1) * P;
                 load_y();
@@ -1508,38 +1510,64 @@ struct RecGrouped {
                 e2 = erows + (size_t)frame_of(3) * P;
             }
             __syncthreads();
+            if constexpr (DIR == 1) {
+                Real pv = row16_allsum(lds_ldr<Real>(kRegPart + (32u + (lane & 31)) * kRB));
+                const Real nr = lane_value(pv, 0), Sd = lane_value(pv, 16);
+                Real N;
+                pow2_scale(nr, &N, &inv);
+                c = eps * Sd * inv;
+                if (tid == 0) {
+                    scalN[T] = N;
+                    scalS[T] = Sd;
+                }
+                n = s = 0;
+                const float* e = erows + (size_t)max(T - 1, 0) * P;
+                for (int sl = s0; sl < s1 && T > 0; ++sl) {
+                    const int row = sl * 64 + lane;
+                    const Real v = lds_ldr<Real>(row * kRB);
+                    const Real u = (Real)e[p.g.row_pdf[od.vec_at + row]] * (inv * v + c);
+                    lds_st(row * kRB, u);
+                    n += lds_ldr<Real>(kRowSums0 + (uint32_t)row * kRB) * u;
+                    if (kTwoSums) s += lds_ldr<Real>(kRowSums1 + (uint32_t)row * kRB) * u;
+                }
+                total(n, s, kRegPart);
+                __syncthreads();
+            }
         }
-        estep = dir == 0 ? (ptrdiff_t)P : -(ptrdiff_t)P;
-        tstep = dir == 0 ? (ptrdiff_t)rows : -(ptrdiff_t)rows;
-        sstep = dir == 0 ? 1 : -1;
-        trow = trel + (size_t)(dir == 0 ? 1 : T - 1) * rows;
-        sN = scalN + (dir == 0 ? 0 : T);
-        sS = scalS + (dir == 0 ? 0 : T);
-        const uint32_t part_at = ((uint32_t)wave + (HAS_WB && lane >= 32 ? 16u : 0u)) * kRB;
-        if (dir == 0) loop<0>(T, tid, lane, eps, aconst, bconst, mask, row4_first, ey_first, part_at, nsl);
-        else loop<1>(T, tid, lane, eps, aconst, bconst, mask, row4_first, ey_first, part_at, nsl);
+        estep = DIR == 0 ? (ptrdiff_t)P : -(ptrdiff_t)P;
+        tstep = DIR == 0 ? (ptrdiff_t)rows : -(ptrdiff_t)rows;
+        sstep = DIR == 0 ? 1 : -1;
+        trow = trel + (size_t)(DIR == 0 ? 1 : T - 1) * rows;
+        sN = scalN + (DIR == 0 ? 0 : T - 1);  // alpha: of step k - 1; beta: of the rows of step k
+        sS = scalS + (DIR == 0 ? 0 : T - 1);
+        const uint32_t part_at = ((uint32_t)wave + (kTwoSums && lane >= 32 ? 16u : 0u)) * kRB;
+        int k = 1;
+        for (; k + 1 <= T; k += 2) {
+            step<1, DIR>(k, T, tid, lane, eps, aconst, mask, row4_first, ey_first, part_at, nsl);
+            step<0, DIR>(k + 1, T, tid, lane, eps, aconst, mask, row4_first, ey_first, part_at, nsl);
+        }
+        if (k <= T) step<1, DIR>(k, T, tid, lane, eps, aconst, mask, row4_first, ey_first, part_at, nsl);
 
-        // ---- last scalars and the closing dot product (the vector of step T is raw:
-        // beta's in-place folding happens at the start of a step that does not come)
+        // ---- last scalars (alpha) and the closing dot product; beta's last rows are read
+        // back from the trellis, each by the thread that stored it
         {
             const uint32_t xc = (T & 1) ? kRegX1 : 0u;
-            const uint32_t pc = kRegPart + ((T & 1) ? 32u * kRB : 0u);
-            Real pv = lds_ldr<Real>(pc + (lane & (HAS_WB ? 31 : 15)) * kRB);
-            pv = row16_allsum(pv);
-            const Real N = lane_value(pv, 0);
-            const Real Sd = HAS_WB ? lane_value(pv, 16) : aconst * N;
-            const Real inv = N > 0 ? (Real)1 / N : (Real)0;
-            const Real c = eps * Sd * inv;
-            if (tid == 0) {
-                const int tp = dir == 0 ? T : 0;
-                scalN[tp] = N;
-                scalS[tp] = Sd;
+            if constexpr (DIR == 0) {
+                const uint32_t pc = kRegPart + ((T & 1) ? 32u * kRB : 0u);
+                const Real nr = lane_value(row16_allsum(lds_ldr<Real>(pc + (lane & 15) * kRB)), 0);
+                Real N;
+                pow2_scale(nr, &N, &inv);
+                c = eps * nr * inv;
+                if (tid == 0) {
+                    scalN[T] = N;
+                    scalS[T] = nr;
+                }
             }
             Real z = 0;
             for (int sl = s0; sl < s1; ++sl) {
                 const int row = sl * 64 + lane;
-                const Real v = lds_ldr<Real>(xc + row * kRB) * inv +
-                               c * (Real)p.g.vb[od.vec_at + row];
+                const Real raw = DIR == 0 ? lds_ldr<Real>(xc + row * kRB) : trel[row];
+                const Real v = raw * inv + c * (Real)p.g.vb[od.vec_at + row];
                 z += (Real)p.g.vfin[od.vec_at + row] * v;
             }
             z = wave_sum_uniform(z);
@@ -1548,10 +1576,279 @@ struct RecGrouped {
             __syncthreads();
             if (tid == 0) {
                 Real Z = 0;
-                for (int w = 0; w < (nthreads >> 6); ++w)
-                    Z += lds_ldr<Real>(kRegPart + (64 + w) * kRB);
-                static_cast<Real*>(p.zfin)[(size_t)dir * p.B + b] = Z;
+                for (int w = 0; w < nwaves; ++w) Z += lds_ldr<Real>(kRegPart + (64 + w) * kRB);
+                static_cast<Real*>(p.zfin)[(size_t)DIR * p.B + b] = Z;
             }
+        }
+    }
+};
+
+// ---------------------------------------------------------------------------
+// The same recursion for workgroups whose waves own at most one slice of at most NS slots
+// (per-utterance numerator graphs: a few hundred states, two or three arcs into each).
+// Such a step is bound by the instructions of one wave from a barrier to the next (a wave
+// issues one about every 4.6 clocks), so it is straight-line and short: no slice masks, no
+// counts, no lane-dependent branches (a lane with nothing to say stores to a word nobody
+// reads), waves that own no slice do nothing but wait, and the scalars of a block of steps
+// collect in the lanes of three registers. 72 instructions a step; the launch of the 16
+// longest of 128 numerators (up to 119 phones, 600 frames): 275 us, 379 us with RecRegs,
+// which gathers an emission per arc and waits for its loads at every step.
+// LDS map: X0, X1 as above; emissions [64K, 96K); partial sums at kRegPart, n of wave w at
+// value 16 * set * 2 + w, s 16 further; unused words behind them.
+// ---------------------------------------------------------------------------
+template <typename Real, int NS, int NT>
+struct RecShort {
+    static constexpr uint32_t kRB = sizeof(Real);
+    static constexpr uint32_t kSet = 32u * kRB;             // one set of partial sums
+    static constexpr uint32_t kDump = kRegPart + 64u * kRB;  // words nobody reads
+    // Emission values come in blocks of kBlock steps: those of the block after the current one
+    // are fetched while its steps run and go to LDS at its end ([step][row] from kRegY0 on; a
+    // lane reads back only what it wrote). A value that stayed in a register across the steps
+    // would be copied at the end of the loop, and the copy would wait for the load.
+    static constexpr int kBlock = 8;
+    static constexpr uint32_t kEStride = NT * 4u;
+
+    uint32_t xa[NS];
+    Real wr[NS];
+    Real r0, r1;      // alpha: in_wpi of the row; beta: in_w, in_wpi
+    Real* trow;       // this lane's value in the trellis row the next step writes
+    Real* sN;         // where the scalars of the block's first step go
+    Real* sS;
+    Real inv, c;      // scale and leak of the vector the last step read
+    int keep_n;       // lane q: high half of N of the block's step q, and both halves of s
+    int keep_s[sizeof(Real) / 4];
+
+    // The totals of a set of partial sums: n, and for beta s.
+    template <int DIR>
+    __device__ __forceinline__ void totals(Real pv, Real* n, Real* s) const
+    {
+        pv = dpp_add<0xB1, 0xf>(pv);   // quad_perm [1,0,3,2]
+        pv = dpp_add<0x4E, 0xf>(pv);   // quad_perm [2,3,0,1]
+        pv = dpp_add<0x141, 0xf>(pv);  // row_half_mirror
+        if (NT > 512) pv = dpp_add<0x140, 0xf>(pv);  // row_mirror: more than eight waves
+        *n = lane_value(pv, 0);
+        *s = DIR == 0 ? *n : lane_value(pv, NT > 512 ? 16 : 8);
+    }
+    // Lanes 0.. read n of wave 0.., the next 8 or 16 lanes s.
+    __device__ __forceinline__ uint32_t part_read_at(const int lane) const
+    {
+        return NT > 512 ? (uint32_t)(lane & 31) * kRB
+                        : (uint32_t)((lane & 7) + (lane & 8) * 2) * kRB;
+    }
+    template <int Q>
+    __device__ __forceinline__ void keep(const Real N, const Real s)
+    {
+        if constexpr (sizeof(Real) == 8) {
+            const long long nb = __double_as_longlong(N), sb = __double_as_longlong(s);
+            keep_n = write_lane<Q>(keep_n, (int)(nb >> 32));
+            keep_s[0] = write_lane<Q>(keep_s[0], (int)sb);
+            keep_s[1] = write_lane<Q>(keep_s[1], (int)(sb >> 32));
+        } else {
+            keep_n = write_lane<Q>(keep_n, __float_as_int(N));
+            keep_s[0] = write_lane<Q>(keep_s[0], __float_as_int(s));
+        }
+    }
+
+    // Q: step of the block
+    template <int Q, int DIR>
+    __device__ __forceinline__ void step(const Real eps, const uint32_t row_at, const uint32_t e_at,
+                                         const uint32_t read_at, const uint32_t write_at,
+                                         const ptrdiff_t tstep)
+    {
+        constexpr int PAR = (Q & 1) ^ 1;  // k & 1: blocks start at odd steps
+        constexpr uint32_t xc = PAR ? 0u : kRegX1, xn = PAR ? kRegX1 : 0u;
+        constexpr uint32_t pc = kRegPart + (PAR ? 0u : kSet), pn = PAR ? kSet : 0u;
+        const Real pv = lds_ldr<Real>(pc + read_at);
+        Real xv[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) xv[i] = lds_ldr<Real>(xc + xa[i]);
+        const Real e = (Real)lds_ld(kRegY0 + Q * kEStride + e_at);
+        asm volatile("" ::: "memory");
+        Real nr, Sd, N;
+        totals<DIR>(pv, &nr, &Sd);
+        pow2_scale(nr, &N, &inv);
+        c = eps * Sd * inv;
+        Real acc = wr[0] * xv[0];
+#pragma unroll
+        for (int i = 1; i < NS; ++i) acc = fma(wr[i], xv[i], acc);
+        const Real x = inv * (e * acc) + c * (DIR == 0 ? e * r0 : e);
+        lds_st(xn + row_at, x);
+        *trow = DIR == 0 ? x : acc;
+        const Real ns = DIR == 0 ? wave_sum_lane63(x) : half_wave_sums(r0 * x, r1 * x);
+        lds_st(pn + write_at, ns);
+        keep<Q>(N, Sd);
+        trow += tstep;
+        __syncthreads();
+    }
+
+    template <int DIR>
+    __device__ __forceinline__ void run(const FbParams& p, const SeqDesc& sd, const OrdDesc& od,
+                                        const int b)
+    {
+        const int tid = threadIdx.x;
+        const int lane = tid & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int nwaves = blockDim.x >> 6;
+        const int T = sd.T;
+        const int P = p.P;
+        const int rows = od.num_slices * 64;
+        Real* trel = static_cast<Real*>(DIR == 0 ? p.alpha : p.beta) +
+                     (DIR == 0 ? sd.alpha_at : sd.beta_at);
+        Real* scalN = static_cast<Real*>(p.scal) + (size_t)(DIR * 2) * p.scal_total + sd.scal_at;
+        Real* scalS = scalN + p.scal_total;
+        const Real eps = (Real)p.leak;
+        const float* erows = p.emis + (size_t)b * p.T * P;
+
+        // this wave's slice and its arcs
+        int sl = 0, first = 0, nsl = 0;
+        bool owns = false;
+        if (wave < od.num_waves) {
+            const int32_t* so = p.g.slice_off + od.slice_off_at;
+            sl = p.g.wave_first[od.wave_first_at + wave];
+            owns = p.g.wave_first[od.wave_first_at + wave + 1] > sl;
+            first = so[sl];
+            if (owns) nsl = so[sl + 1] - first - od.closing;
+        }
+        const int row = sl * 64 + lane;
+        const int vec = od.vec_at + row;
+        float wf[NS];
+        load_records<NS>(p, od, lane, first, nsl, xa, wf);
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            xa[i] = (xa[i] & 0xffffu) * (kRB / 4u);
+            wr[i] = (Real)wf[i];
+            asm volatile("" : "+v"(xa[i]), "+v"(wr[i]));
+        }
+        const uint32_t ysrc = owns ? (uint32_t)p.g.row_pdf[vec] * 4u : 0u;
+        r0 = owns ? (Real)(DIR == 0 ? p.g.in_wpi : p.g.in_w)[vec] : (Real)0;
+        r1 = owns ? (Real)p.g.in_wpi[vec] : (Real)0;
+        if (tid < 64) lds_st(kRegPart + (uint32_t)tid * kRB, (Real)0);
+        // Frame whose emissions meet the rows that step k stores, as in RecGrouped
+        auto frame_of = [&](int k) { return max(0, min(DIR == 0 ? k - 1 : T - k - 1, T - 1)); };
+        const uint32_t e_at = (uint32_t)tid * 4u;
+        float ahead[kBlock];
+        auto fetch_block = [&](const int k0) {  // of steps k0 ..; past the end the last row again
+#pragma unroll
+            for (int q = 0; q < kBlock; ++q) {
+                const float* er = erows + (size_t)frame_of(k0 + q) * P;
+                ahead[q] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(er) + ysrc);
+            }
+        };
+        auto store_block = [&]() {
+#pragma unroll
+            for (int q = 0; q < kBlock; ++q) lds_st(kRegY0 + q * kEStride + e_at, ahead[q]);
+        };
+        if (T > 0) {
+            fetch_block(1);
+            store_block();
+        }
+        __syncthreads();
+        const uint32_t row_at = (uint32_t)row * kRB;
+        const uint32_t read_at = part_read_at(lane);
+        // where the end-of-step sums go: alpha n from lane 63; beta n from lane 31, s from 63
+        const bool says = DIR == 0 ? lane == 63 : (lane & 31) == 31;
+        const uint32_t write_at =
+            says ? kRegPart + ((uint32_t)wave + (DIR == 1 && lane == 63 ? 16u : 0u)) * kRB
+                 : kDump + (uint32_t)lane * kRB;
+        auto put = [&](const Real n, const Real s, const uint32_t set) {
+            const Real nn = half_wave_sums(n, s);
+            if ((lane & 31) == 31)
+                lds_st(kRegPart + set + ((uint32_t)wave + (lane >> 5) * 16u) * kRB, nn);
+        };
+        // ---- step 0
+        {
+            const Real v = owns ? (Real)p.g.vinit[vec] : (Real)0;
+            if (owns) {
+                lds_st(row_at, v);
+                trel[(size_t)(DIR == 0 ? 0 : T) * rows + row] = v;
+            }
+            put(v, owns ? (Real)p.g.va[vec] * v : (Real)0, DIR == 0 ? 0u : kSet);
+            __syncthreads();
+            if constexpr (DIR == 1) {
+                Real nr, Sd, N;
+                totals<1>(lds_ldr<Real>(kRegPart + kSet + read_at), &nr, &Sd);
+                pow2_scale(nr, &N, &inv);
+                c = eps * Sd * inv;
+                if (tid == 0) {
+                    scalN[T] = N;
+                    scalS[T] = Sd;
+                }
+                if (T > 0) {
+                    const float e = *reinterpret_cast<const float*>(
+                        reinterpret_cast<const char*>(erows + (size_t)(T - 1) * P) + ysrc);
+                    const Real u = (Real)e * (inv * v + c);
+                    if (owns) lds_st(row_at, u);
+                    put(r0 * u, r1 * u, 0u);
+                }
+                __syncthreads();
+            }
+        }
+        const ptrdiff_t tstep = DIR == 0 ? (ptrdiff_t)rows : -(ptrdiff_t)rows;
+        constexpr int kS = DIR == 0 ? 1 : -1;
+        trow = trel + (size_t)(DIR == 0 ? 1 : T - 1) * rows + row;
+        sN = scalN + (DIR == 0 ? 0 : T - 1);
+        sS = scalS + (DIR == 0 ? 0 : T - 1);
+        keep_n = keep_s[0] = keep_s[sizeof(Real) / 4 - 1] = 0;
+        if (owns) {
+            for (int k0 = 1; k0 <= T; k0 += kBlock) {
+                const int left = T - k0;  // steps of the block after its first
+                fetch_block(k0 + kBlock);
+#define LFMMI_SHORT_STEP(Q) \
+    if (left >= Q) step<Q, DIR>(eps, row_at, e_at, read_at, write_at, tstep);
+                LFMMI_SHORT_STEP(0)
+                LFMMI_SHORT_STEP(1)
+                LFMMI_SHORT_STEP(2)
+                LFMMI_SHORT_STEP(3)
+                LFMMI_SHORT_STEP(4)
+                LFMMI_SHORT_STEP(5)
+                LFMMI_SHORT_STEP(6)
+                LFMMI_SHORT_STEP(7)
+#undef LFMMI_SHORT_STEP
+                if (wave == 0 && lane < kBlock && lane <= left) {
+                    Real N, s;
+                    if constexpr (sizeof(Real) == 8) {
+                        N = __longlong_as_double((long long)keep_n << 32);
+                        s = __longlong_as_double(((long long)keep_s[1] << 32) | (uint32_t)keep_s[0]);
+                    } else {
+                        N = __int_as_float(keep_n);
+                        s = __int_as_float(keep_s[0]);
+                    }
+                    sN[kS * lane] = N;
+                    sS[kS * lane] = s;
+                }
+                sN += kS * kBlock;
+                sS += kS * kBlock;
+                store_block();
+            }
+        } else {
+            for (int k = 1; k <= T; ++k) __syncthreads();
+        }
+
+        // ---- last scalars (alpha) and the closing dot product (beta's last rows: from the
+        // trellis, each by the thread that stored it)
+        if constexpr (DIR == 0) {
+            Real nr, Sd, N;
+            totals<0>(lds_ldr<Real>(kRegPart + ((T & 1) ? kSet : 0u) + read_at), &nr, &Sd);
+            pow2_scale(nr, &N, &inv);
+            c = eps * Sd * inv;
+            if (tid == 0) {
+                scalN[T] = N;
+                scalS[T] = Sd;
+            }
+        }
+        Real z = 0;
+        if (owns) {
+            const Real raw = DIR == 0 ? lds_ldr<Real>(((T & 1) ? kRegX1 : 0u) + row_at) : trel[row];
+            z = (Real)p.g.vfin[vec] * (raw * inv + c * (Real)p.g.vb[vec]);
+        }
+        z = wave_sum_uniform(z);
+        __syncthreads();
+        if (lane == 0) lds_st(kRegPart + (uint32_t)wave * kRB, z);
+        __syncthreads();
+        if (tid == 0) {
+            Real Z = 0;
+            for (int w = 0; w < nwaves; ++w) Z += lds_ldr<Real>(kRegPart + (uint32_t)w * kRB);
+            static_cast<Real*>(p.zfin)[(size_t)DIR * p.B + b] = Z;
         }
     }
 };
@@ -1635,7 +1932,7 @@ __device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scr
 }
 
 template <typename Real, int NSLOT, bool YREP, bool HAS_WB, int NT, bool HYBRID = false,
-          bool BIG = false, bool HUBS = false, bool GROUPED = false>
+          bool BIG = false, bool HUBS = false, int BY_STATE = 0>
 __global__ void __launch_bounds__(NT) k_rec(FbParams p)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1646,10 +1943,15 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
 #endif
     const SeqDesc sd = p.seqs[b];
     const OrdDesc od = p.g.ords[sd.graph * 3 + dir];
-    if constexpr (GROUPED) {
+    if constexpr (BY_STATE == 1) {
         static_assert(NSLOT > 0 && !YREP && !HYBRID && !BIG && !HUBS, "grouped: resident arcs only");
         RecGrouped<Real, HAS_WB, NSLOT, NT> r;
-        r.run(p, sd, od, b, dir);
+        if (dir == 0) r.template run<0>(p, sd, od, b);
+        else r.template run<1>(p, sd, od, b);
+    } else if constexpr (BY_STATE == 2) {
+        RecShort<Real, NSLOT, NT> r;
+        if (dir == 0) r.template run<0>(p, sd, od, b);
+        else r.template run<1>(p, sd, od, b);
     } else if constexpr (NSLOT > 0) {
         RecRegs<Real, YREP, HAS_WB, NSLOT, NT, HYBRID, BIG, HUBS> r;
         r.run(p, sd, od, b, dir, lds_raw);
@@ -2352,11 +2654,13 @@ struct RecVariant {
     RecKernel fn;
     int hybrid = 0;  // 1: hybrid, 2: hybrid with the large LDS map
     int hubs = 0;    // handles hub slices
-    int grouped = 0; // emission by entered state: no emission gather (RecGrouped)
+    int grouped = 0; // emission by entered state: 1 RecGrouped, 2 RecShort
 };
-#define LFMMI_REC_GROUPED(REAL, WIDE, NSLOT, WB, NT)                                             \
-    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, (WB != 0), NT, false, false, false, true>, \
+#define LFMMI_REC_GROUPED(REAL, WIDE, NSLOT, WB, NT)                                          \
+    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, (WB != 0), NT, false, false, false, 1>, \
      0, 0, 1}
+#define LFMMI_REC_SHORT(REAL, WIDE, NS, NT) \
+    {WIDE, NS, 0, 0, NT, k_rec<REAL, NS, false, false, NT, false, false, false, 2>, 0, 0, 2}
 
 #define LFMMI_REC(REAL, WIDE, NSLOT, WB, NT)                                                    \
     {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, (WB != 0), NT>},                         \
@@ -2398,20 +2702,28 @@ const RecVariant kRecVariants[] = {
     {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, false, 1024, true, true, true>, 2, 1},
     // emission by entered state (two registers per slot: more slots fit)
     LFMMI_REC_GROUPED(float, 0, 16, 0, 1024), LFMMI_REC_GROUPED(float, 0, 24, 0, 1024),
-    LFMMI_REC_GROUPED(float, 0, 32, 0, 1024), LFMMI_REC_GROUPED(float, 0, 48, 0, 512),
+    LFMMI_REC_GROUPED(float, 0, 32, 0, 1024), LFMMI_REC_GROUPED(float, 0, 36, 0, 1024),
     LFMMI_REC_GROUPED(float, 0, 16, 1, 1024), LFMMI_REC_GROUPED(float, 0, 24, 1, 1024),
-    LFMMI_REC_GROUPED(double, 1, 8, 1, 1024), LFMMI_REC_GROUPED(double, 1, 16, 1, 512),
+    LFMMI_REC_GROUPED(float, 0, 32, 1, 1024), LFMMI_REC_GROUPED(float, 0, 36, 1, 1024),
+    LFMMI_REC_GROUPED(double, 1, 8, 1, 1024), LFMMI_REC_GROUPED(double, 1, 16, 1, 1024),
     LFMMI_REC_GROUPED(double, 1, 16, 0, 1024),
+    // ... one short slice per wave
+    LFMMI_REC_SHORT(float, 0, 4, 512), LFMMI_REC_SHORT(float, 0, 8, 512),
+    LFMMI_REC_SHORT(double, 1, 4, 512), LFMMI_REC_SHORT(double, 1, 8, 512),
+    LFMMI_REC_SHORT(float, 0, 4, 1024), LFMMI_REC_SHORT(float, 0, 8, 1024),
+    LFMMI_REC_SHORT(double, 1, 4, 1024), LFMMI_REC_SHORT(double, 1, 8, 1024),
 };
 #undef LFMMI_REC
 #undef LFMMI_REC_GROUPED
+#undef LFMMI_REC_SHORT
 
 const RecVariant* find_rec(bool wide, int nslot, bool yrep, bool has_wb, int hybrid, bool hubs,
-                           bool grouped)
+                           int grouped, int threads)
 {
     for (const RecVariant& v : kRecVariants)
-        if (v.wide == (wide ? 1 : 0) && v.nslot == nslot && v.has_wb == (has_wb ? 1 : 0) &&
-            v.grouped == (grouped ? 1 : 0) &&
+        if (v.wide == (wide ? 1 : 0) && v.nslot == nslot && v.grouped == grouped &&
+            (grouped != 2 || threads <= v.max_threads) &&
+            (grouped == 2 || v.has_wb == (has_wb ? 1 : 0)) &&
             (grouped || (v.yrep == (yrep ? 1 : 0) && v.hybrid == hybrid && v.hubs == (hubs ? 1 : 0))))
             return &v;
     return nullptr;
@@ -2435,13 +2747,26 @@ int rec_grouped_slots(bool wide, bool has_wb, int max_wave_slots, int threads)
 {
     int best = 0;
     for (const RecVariant& v : kRecVariants)
-        if (v.grouped && v.wide == (wide ? 1 : 0) && v.has_wb == (has_wb ? 1 : 0) &&
+        if (v.grouped == 1 && v.wide == (wide ? 1 : 0) && v.has_wb == (has_wb ? 1 : 0) &&
             v.nslot >= max_wave_slots && threads <= v.max_threads && (best == 0 || v.nslot < best))
             best = v.nslot;
     return best;
 }
 
-int rec_grouped_max_rows(int threads) { return kGroupedPasses * threads; }
+int rec_grouped_max_rows(bool wide, int threads)
+{
+    return std::min(kGroupedPasses * threads, grouped_rows(wide));
+}
+
+int rec_short_slots(bool wide, int max_wave_slots, int threads)
+{
+    int best = 0;
+    for (const RecVariant& v : kRecVariants)
+        if (v.grouped == 2 && v.wide == (wide ? 1 : 0) && v.nslot >= max_wave_slots &&
+            threads <= v.max_threads && (best == 0 || v.nslot < best))
+            best = v.nslot;
+    return best;
+}
 
 int rec_hybrid_slots(bool wide, bool has_wb, bool yrep, bool hubs, int map)
 {
@@ -2556,12 +2881,13 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
     const bool wide = sizeof(Real) == 8;
     const RecVariant* rv =
         find_rec(wide, shape.rec_nslot, shape.rec_yrep != 0, shape.rec_has_wb != 0,
-                 shape.rec_hybrid, shape.rec_hubs != 0, shape.rec_grouped != 0);
+                 shape.rec_hybrid, shape.rec_hubs != 0, shape.rec_short ? 2 : shape.rec_grouped,
+                 shape.rec_threads);
     if (!rv || shape.rec_threads > rv->max_threads) return hipErrorInvalidConfiguration;
     if (bk.n > 1 && (e = hipEventRecord(bk.fork, stream)) != hipSuccess) return e;
 
     int rec_threads = shape.rec_threads;
-    if (shape.rec_nslot > 0 && !shape.rec_grouped) {
+    if (shape.rec_nslot > 0 && !shape.rec_grouped && !shape.rec_short) {
         // enough threads to stage one emission row in the variant's passes; waves
         // beyond the graph's own hold no arcs
         const int units = shape.rec_yrep ? p.P * 8 : p.P;

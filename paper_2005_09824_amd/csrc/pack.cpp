@@ -1015,6 +1015,12 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
             const Arrangement& ar = d == 0 ? af : ab;
             out->row_pdf[d].assign((size_t)ar.num_slices * kLanes, 0);
             for (int32_t s = 0; s < S; ++s) out->row_pdf[d][ar.pos[s]] = std::max(pdf_of[s], 0);
+            out->in_w[d].assign((size_t)ar.num_slices * kLanes, 0.0);
+            out->in_wpi[d].assign((size_t)ar.num_slices * kLanes, 0.0);
+            for (int64_t a = 0; a < A; ++a) {
+                out->in_w[d][ar.pos[g.dst[a]]] += (double)w[a];
+                out->in_wpi[d][ar.pos[g.dst[a]]] += (double)w[a] * (double)g.init_prob[g.src[a]];
+            }
         }
         out->row_occ.clear();
         out->pdf_states.clear();

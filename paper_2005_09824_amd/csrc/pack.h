@@ -70,7 +70,10 @@ struct PackedGraph {
     // states nothing enters); filled only when the flag is set.
     bool pdf_by_dst = false;
     std::vector<int32_t> row_pdf[2];
-    // ... and, filled with it, what the occupancy pass by entered state reads:
+    // Filled with it, in the same numberings: sums over the arcs into the row's state of the
+    // arc weight, and of the weight times the initial probability of the state it leaves.
+    std::vector<double> in_w[2], in_wpi[2];
+    // ... and what the occupancy pass by entered state reads:
     // row_occ[FWD row] = the BWD row of the row's state | place << 16, the places being
     // the states sorted by pdf (pdf d's: pdf_states[d] .. pdf_states[d + 1] - 1);
     // padding rows and states nothing enters have the place after the last.

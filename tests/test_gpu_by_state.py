@@ -59,3 +59,43 @@ def test_occupancies_by_state(S, k, P, some_final):
     if P == 9:
         g["pdf"] = np.where(g["dst"] % 8 == 0, g["pdf"], 3).astype(np.int32)
     parity(g, [9, 1, 8, 0, 5], 11)
+
+
+# the recursion without an emission gather: one barrier per step, scalars of a step known
+# before its rows. Waves with one short slice (4, 8 slots), resident arcs up to the most
+# slots that are built, uniform and other initial probabilities, fp32 and fp64; lengths
+# around the two steps that are fetched ahead
+@pytest.mark.parametrize("S,k,P,init,some_final,leak", [
+    (1, 0, 1, "uniform", False, 1e-5), (20, 1, 7, "uniform", False, 0.3), (130, 1, 7, "varied", False, 1e-5),
+    (1024, 1, 40, "uniform", False, 1e-5), (1024, 3, 40, "varied", True, 1e-3), (200, 1, 9, "varied", True, 0.0),
+    (1500, 6, 40, "varied", False, 1e-3), (1900, 12, 60, "varied", False, 1e-5),
+    (2000, 15, 60, "uniform", False, 1e-3), (4096, 6, 84, "uniform", False, 0.0),
+    (700, 3, 84, "varied", True, 1e-3),
+])
+def test_recursion_by_state(S, k, P, init, some_final, leak):
+    rng = np.random.default_rng(S + k)
+    g = by_state_graph(rng, S, k, P, init, some_final)
+    parity(g, [6, 1, 0, 2, 3, 4, 5, 23], 23, leak)
+
+
+def test_recursion_by_state_flags_what_it_flagged_before():
+    # a chain that cannot be left in so few frames: zero probability; a NaN logit
+    K, P = 40, 6
+    src = np.arange(K - 1, dtype=np.int32)
+    g = {"num_states": K, "num_pdfs": P, "src": src, "dst": src + 1,
+         "pdf": ((src + 1) % P).astype(np.int32), "logw": np.zeros(K - 1, np.float32),
+         "init_prob": np.eye(K, dtype=np.float32)[0], "final_prob": np.eye(K, dtype=np.float32)[K - 1]}
+    torch = pytest.importorskip("torch")
+    x = torch.zeros((3, 60, P))
+    x[1, 7, 2] = float("nan")
+    h = binding.lfmmi_graph_create(g)
+    lengths = np.array([39, 39, 20], np.int32)
+    objf, grad, status = binding.lfmmi_forward_backward(h, x.cuda(), lengths, 0.0)
+    torch.cuda.synchronize()
+    h.close()
+    assert status.tolist() == [0, 3, 1]
+    assert objf[0].item() == 0.0 and np.isnan(objf[1].item()) and objf[2].item() == -np.inf
+    assert torch.all(grad[1:] == 0)
+    want = torch.zeros((39, P))
+    want[torch.arange(39), (torch.arange(39) + 1) % P] = 1.0
+    assert torch.equal(grad[0, :39].cpu(), want)
