@@ -1859,21 +1859,23 @@ struct RecShort {
 //   turns ahat_{t-1} * w * e_t * bhat_t into an occupancy,
 //   c_t = exp(A_{t-1} + B_t - log Z'),  A, B = prefix / suffix sums of log n,
 // in fp64. Called by every thread of a workgroup (at most 256 of them work);
-// scratch: 8 KB of LDS nobody else uses.
+// scratch: 96 bytes of LDS nobody else uses.
 // ---------------------------------------------------------------------------
 // Largest difference (nats) between the alpha-side and the beta-side log Z of a
 // sequence that counts as rounding: fp32 state vectors on the longest workloads
 // here differ by a few 1e-5.
 constexpr double kTotalsAgree = 1e-3;
 
+// The prefix sums run over lanes first (shuffles), then over the waves' totals: one thread
+// adding up 256 partial sums one after the other took 12 to 15 us at the end of every
+// sequence. A thread keeps the logarithms of its first kKeep frames.
 template <typename Real>
 __device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scratch_raw)
 {
-    double* sa = reinterpret_cast<double*>(scratch_raw);
-    double* sb = sa + 256;
-    double* sm = sb + 256;
-    double* tot = sm + 256;
+    constexpr int kKeep = 4;  // all of them up to 1,023 frames
+    double* tot = reinterpret_cast<double*>(scratch_raw);  // [wave][3]
     const int tid = threadIdx.x;
+    const int lane = tid & 63;
     const int workers = min((int)blockDim.x, 256);
     const SeqDesc sd = p.seqs[b];
     const int T = sd.T;
@@ -1885,26 +1887,52 @@ __device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scr
     const bool work = tid < workers;
     const int i0 = work ? min(tid * chunk, n) : n, i1 = min(i0 + chunk, n);
     double la = 0.0, lb = 0.0, lm = 0.0;
-    for (int i = i0; i < i1; ++i) {
+    double ka[kKeep], kb[kKeep];
+    if (work)
+        for (int t = tid; t < T; t += workers) lm += (double)p.rowmax[(size_t)b * p.T + t];
+#pragma unroll
+    for (int q = 0; q < kKeep; ++q) {
+        const bool on = i0 + q < i1;
+        ka[q] = on ? log((double)na[i0 + q]) : 0.0;
+        kb[q] = on ? log((double)nb[i0 + q]) : 0.0;
+        la += ka[q];
+        lb += kb[q];
+    }
+    for (int i = i0 + kKeep; i < i1; ++i) {
         la += log((double)na[i]);
         lb += log((double)nb[i]);
     }
-    if (work)
-        for (int t = tid; t < T; t += workers) lm += (double)p.rowmax[(size_t)b * p.T + t];
-    if (work) { sa[tid] = la; sb[tid] = lb; sm[tid] = lm; }
-    __syncthreads();
-    if (tid == 0) {
-        double ra = 0.0, rb = 0.0, rm = 0.0;
-        for (int i = 0; i < workers; ++i) {
-            const double xa = sa[i], xb = sb[i];
-            sa[i] = ra; sb[i] = rb;  // exclusive prefixes
-            ra += xa; rb += xb; rm += sm[i];
+    double ra = la, rb = lb;  // inclusive sums over the wave's lanes
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double xa = __shfl_up(ra, o, 64), xb = __shfl_up(rb, o, 64);
+        lm += __shfl_xor(lm, o, 64);
+        if (lane >= o) {
+            ra += xa;
+            rb += xb;
         }
-        tot[0] = ra; tot[1] = rb; tot[2] = rm;
+    }
+    if (work && lane == 63) {
+        double* w = tot + 3 * (tid >> 6);
+        w[0] = ra;
+        w[1] = rb;
+        w[2] = lm;
     }
     __syncthreads();
-    const double totB = tot[1], msum = tot[2];
-    const double lz = log((double)static_cast<const Real*>(p.zfin)[b]) + tot[0];
+    double totA = 0.0, totB = 0.0, msum = 0.0;
+    ra = __shfl_up(ra, 1, 64);  // exclusive
+    rb = __shfl_up(rb, 1, 64);
+    if (lane == 0) ra = rb = 0.0;
+    for (int w = 0; w < workers >> 6; ++w) {
+        if (w == tid >> 6) {
+            ra += totA;
+            rb += totB;
+        }
+        totA += tot[3 * w];
+        totB += tot[3 * w + 1];
+        msum += tot[3 * w + 2];
+    }
+    const double lz = log((double)static_cast<const Real*>(p.zfin)[b]) + totA;
     // the same total from the beta side: pi . beta'_0. The two agree up to rounding
     // unless a pass lost mass to underflow (a state whose alpha is below the range
     // of Real next to the frame's total while its beta is that much above, or the
@@ -1913,9 +1941,18 @@ __device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scr
     const bool nonfinite_in = !(msum == msum);
     const bool dead = !(lz > -INFINITY && lz < INFINITY) || nonfinite_in;
     const bool lossy = !dead && !(fabs(lz - lz_beta) <= kTotalsAgree);
-    double ra = work ? sa[tid] : 0.0, rb = work ? sb[tid] : 0.0;
-    for (int i = i0; i < i1; ++i) {
+    auto scale = [&](const int i) {
         if (i >= 1) cfac[i] = dead ? (Real)0 : (Real)exp(ra + (totB - rb) - lz);
+    };
+#pragma unroll
+    for (int q = 0; q < kKeep; ++q)
+        if (i0 + q < i1) {
+            scale(i0 + q);
+            ra += ka[q];
+            rb += kb[q];
+        }
+    for (int i = i0 + kKeep; i < i1; ++i) {
+        scale(i);
         ra += log((double)na[i]);
         rb += log((double)nb[i]);
     }
@@ -2901,7 +2938,7 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
         std::max<size_t>(shape.rec_nslot > 0
                              ? reg_lds_bytes()
                              : rec_lds_bytes(p.lds_rows, p.P, wide, shape.rec_yrep != 0),
-                         8192 + 64);
+                         64 + 96);
     // bucket 0 (the longest sequences) first, on the caller's stream
     for (int q = 0; q < bk.n; ++q) {
         if (bk.count[q] <= 0) continue;
