@@ -67,7 +67,9 @@ struct lfmmi_graph {
     bool rec_hubs = false;  // some FWD / BWD ordering has hub slices
     int rec_hybrid = 0;  // 1, 2: rec_nslot slots of a wave in registers, its others streamed
                          // (2: LDS map for up to 12288 states)
-    bool has_wb = false;  // arcs carry a per-arc leak factor (some init_prob is not uniform)
+    bool has_wb = false;  // packed with leak factors (some init_prob is not uniform)
+    bool over_pi = false;  // ... which the device copy folds into the arcs: state values are
+                           // kept divided by the initial probabilities
     bool rec_grouped = false;  // every arc takes the pdf of the state it enters and the
                                // recursion runs the variant without an emission gather
     bool rec_short = false;    // ... and its variant for waves that own one short slice
@@ -111,6 +113,25 @@ struct lfmmi_graph {
 };
 
 namespace {
+
+// Whether the weights of a graph stay ordinary fp32 numbers when state values are kept
+// divided by the initial probabilities: w * pi[from] / pi[to] (alpha) and w * pi[from]
+// (occupancies).
+bool leak_by_rows(const ArcList& g)
+{
+    std::vector<double> lp(g.num_states);
+    for (int32_t s = 0; s < g.num_states; ++s) {
+        if (!(g.init_prob[s] > 0.f)) return false;
+        lp[s] = std::log((double)g.init_prob[s]);
+    }
+    constexpr double kLow = -87.0, kHigh = 88.0;  // inside the normal range of fp32
+    auto normal = [&](const double l) { return l > kLow && l < kHigh; };
+    for (int64_t a = 0; a < g.num_arcs; ++a) {
+        const double l = (double)g.logw[a] + lp[g.src[a]];
+        if (!normal(l) || !normal(l - lp[g.dst[a]])) return false;
+    }
+    return true;
+}
 
 lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
                       const int64_t* arc_off, const int32_t* src, const int32_t* dst,
@@ -309,19 +330,26 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
             h->rec_short = gslots > 0;
             if (st == LFMMI_OK && gslots == 0) gslots = grouped_slots();
             h->rec_grouped = gslots > 0 && !h->rec_short;
+            // Initial probabilities that differ: state values divided by them need no leak
+            // factor per arc and take every variant that a uniform one takes, but have to leave
+            // every weight an ordinary fp32 number (see leak_by_rows).
+            auto leak = [&]() { return !h->has_wb ? 0 : (h->over_pi ? 2 : 1); };
+            h->over_pi = st == LFMMI_OK && gslots == 0 && h->has_wb && !h->wide && !h->rec_hubs &&
+                         env_int("LFMMI_OVER_PI", 1) != 0;
+            for (int32_t g = 0; g < n && h->over_pi; ++g) h->over_pi = leak_by_rows(arcs_of(g));
             auto resident = [&](int slots, int wv) {
-                return rec_register_slots(h->wide, h->has_wb, h->rec_yrep, h->rec_hubs, slots,
+                return rec_register_slots(h->wide, leak(), h->rec_yrep, h->rec_hubs, slots,
                                           wv * kLanes);
             };
             // too many arcs for the registers: keep the first slots of every wave there
             // and stream the others, where the fixed LDS map of that kernel holds the graph
             auto hybrid_possible = [&]() {  // 0: no; 1: 32 KB state vectors; 2: 48 KB
-                if (h->wide || h->has_wb || env_int("LFMMI_HYBRID", 1) == 0) return 0;
+                if (h->wide || leak() == 1 || env_int("LFMMI_HYBRID", 1) == 0) return 0;
                 if (h->rec_yrep ? num_pdfs > 255 : num_pdfs > 3072) return 0;
                 // padded rows, not states: see registers_possible
                 const int most = std::max(h->max_rows_f, h->max_rows_b);
                 const int map = most <= 8192 ? 1 : (most <= 12288 && !h->rec_yrep ? 2 : 0);
-                return map != 0 && rec_hybrid_slots(h->wide, h->has_wb, h->rec_yrep, h->rec_hubs,
+                return map != 0 && rec_hybrid_slots(h->wide, leak(), h->rec_yrep, h->rec_hubs,
                                                     map) > 0
                            ? map
                            : 0;
@@ -341,12 +369,13 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
                 }
                 if (st == LFMMI_OK && h->rec_nslot == 0 && hybrid_possible() != 0) {
                     h->rec_hybrid = hybrid_possible();
-                    h->rec_nslot = rec_hybrid_slots(h->wide, h->has_wb, h->rec_yrep, h->rec_hubs,
+                    h->rec_nslot = rec_hybrid_slots(h->wide, leak(), h->rec_yrep, h->rec_hubs,
                                                     h->rec_hybrid);
                 }
                 if (h->rec_nslot != 0 || !h->rec_yrep) break;
                 h->rec_yrep = false;
             }
+            if (h->rec_nslot == 0) h->over_pi = false;  // the streamed recursion: factors per arc
             if (st != LFMMI_OK) {
                 delete h;
                 return st;
@@ -410,8 +439,8 @@ lfmmi_status upload(lfmmi_graph* h)
             d.max_wave_slots = od.max_wave_slots;
             d.total_slots = od.total_slots;
             d.mask_at = (int32_t)n_mask;
-            d.has_wb = od.has_wb;
-            d.b_const = od.b_const;
+            d.has_wb = h->over_pi ? 0 : od.has_wb;
+            d.b_const = h->over_pi ? 1.f : od.b_const;
             d.closing = od.closing_slots;
             d.a_const = od.a_const;
             n_mask += od.wave_mask.size();
@@ -472,11 +501,29 @@ lfmmi_status upload(lfmmi_graph* h)
             // starts at an even slot.
             uint2* recs = reinterpret_cast<uint2*>(host.data() + at_recs) + (size_t)d.rec_at * kLanes;
             float* wbs = reinterpret_cast<float*>(host.data() + at_wb) + (size_t)d.rec_at * kLanes;
+            // over_pi: what an arc's weight is multiplied with, by the FWD row it leaves
+            // (alpha: divided by that of the row it is stored in), and the weight of closing
+            // slots, whose emission is the word that stays 0
+            const std::vector<float>& pi_f = h->packed[g].vb[0];
+            const std::vector<float>& pi_row = o == 0 ? h->packed[g].vb[0] : h->packed[g].va[1];
+            const uint32_t closing_key = rec_zero_word(h->rec_hybrid) << 16;
+            int32_t slice = 0;
             for (size_t i = 0; i < od.key.size(); ++i) {
                 const size_t slot = i / kLanes, lane = i % kLanes;
                 const size_t to = ((slot >> 1) * kLanes + lane) * 2 + (slot & 1);
+                while (slot >= (size_t)od.slice_off[slice + 1]) ++slice;
+                float w = od.w[i];
+                if (h->over_pi && o < 2 && slot + 1 == (size_t)od.slice_off[slice + 1]) {
+                    w = pi_row[(size_t)slice * kLanes + lane];
+                    std::memcpy(&recs[to].y, &w, 4);
+                    recs[to].x = closing_key;
+                    continue;
+                }
+                if (h->over_pi && o != 1 && w != 0.f)
+                    w = (float)((double)w * (double)pi_f[(od.key[i] & 0xffffu) / 4] /
+                                (o == 0 ? (double)pi_row[(size_t)slice * kLanes + lane] : 1.0));
                 uint32_t wbits;
-                std::memcpy(&wbits, &od.w[i], 4);
+                std::memcpy(&wbits, &w, 4);
                 uint32_t key = od.key[i];
                 // replicated emission rows: the upper half becomes the byte offset of
                 // this lane's copy of the value, 128 * pdf + 4 * (lane % 32)
@@ -505,6 +552,18 @@ lfmmi_status upload(lfmmi_graph* h)
                 std::memcpy(host.data() + at_va + (size_t)d.vec_at * 4, pg.va[o].data(), nrow * 4);
                 std::memcpy(host.data() + at_vb + (size_t)d.vec_at * 4, pg.vb[o].data(), nrow * 4);
                 std::memcpy(host.data() + at_vfin + (size_t)d.vec_at * 4, pg.vfin[o].data(), nrow * 4);
+                if (h->over_pi && o == 0) {  // alpha over pi: start 1, dot pi, target 1, final f pi
+                    float* v0 = reinterpret_cast<float*>(host.data() + at_vinit) + d.vec_at;
+                    float* va = reinterpret_cast<float*>(host.data() + at_va) + d.vec_at;
+                    float* vb = reinterpret_cast<float*>(host.data() + at_vb) + d.vec_at;
+                    float* vf = reinterpret_cast<float*>(host.data() + at_vfin) + d.vec_at;
+                    for (size_t r = 0; r < nrow; ++r) {
+                        const float pi = pg.vb[0][r];
+                        v0[r] = vb[r] = od.row_id[r] >= 0 ? 1.f : 0.f;
+                        va[r] = pi;
+                        vf[r] = (float)((double)pg.vfin[0][r] * (double)pi);
+                    }
+                }
                 if (pg.row_pdf[o].size() == nrow)
                     std::memcpy(host.data() + at_rowpdfs + (size_t)d.vec_at * 4, pg.row_pdf[o].data(),
                                 nrow * 4);
@@ -692,6 +751,7 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
     p.lds_rows_occ_b = h->max_rows_b;
     p.lds_rows_occ = h->max_rows_occ;
     p.accumulate = accumulate ? 1 : 0;
+    p.alpha_over_pi = h->over_pi ? 1 : 0;
     p.leak = leak;
     p.grad_scale = grad_scale;
 
@@ -704,7 +764,7 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
     shape.rec_grouped = h->rec_grouped ? 1 : 0;
     shape.rec_short = h->rec_short ? 1 : 0;
     shape.profile_rec_only = h->profile == 2 ? 1 : 0;
-    shape.rec_has_wb = h->has_wb ? 1 : 0;
+    shape.rec_leak = !h->has_wb ? 0 : (h->over_pi ? 2 : 1);
     shape.occ_states =
         h->occ_states ? occ_states_frames(h->max_rows_f, h->max_rows_b, h->wide) : 0;
     shape.occ_threads = h->occ_waves * kLanes;
@@ -1103,7 +1163,7 @@ lfmmi_status lfmmi_graph_ordering_info(const lfmmi_graph* h, int32_t g, int32_t 
     info[2] = o.num_waves;
     info[3] = o.total_slots;
     info[4] = o.max_wave_slots;
-    info[5] = ord < 2 ? h->rec_nslot : 0;
+    info[5] = ord < 2 && !(h->over_pi && h->rec_hybrid) ? h->rec_nslot : 0;
     info[6] = ord < 2 && h->rec_yrep ? 1 : 0;
     info[7] = o.has_wb;
     info[8] = o.gather_cycles;

@@ -92,6 +92,7 @@ struct FbParams {
     int32_t wide;           // 1: state vectors, trellis and scales in fp64
     int32_t emis_ready;     // 1: emis / rowmax already hold this batch's values (the other
                             // pass of a full-loss call computed them): k_emit skips them
+    int32_t alpha_over_pi;  // 1: alpha is kept divided by the initial probabilities
     float leak, grad_scale;
 };
 
@@ -99,7 +100,8 @@ struct LaunchShape {
     int rec_threads;   // workgroup size of the recursion kernel
     int rec_nslot;     // arc slots held in registers per lane (0: streamed)
     int rec_yrep;      // emission row replicated across LDS banks
-    int rec_has_wb;    // arcs carry a per-arc leak factor
+    int rec_leak;      // 0: one initial probability, 1: arcs carry a leak factor, 2: state
+                       // values are kept divided by the initial probabilities (RecRegs)
     int rec_hubs;      // some graph of the handle has hub slices
     int profile_rec_only;  // of the four events per bucket record only those around k_rec
     int rec_hybrid;    // 1: only the first slots of a wave are register-resident;
@@ -151,11 +153,11 @@ hipError_t launch_describe(const FbParams& p, const int32_t* lengths, int num_gr
 // Dynamic LDS the recursion / occupancy kernels need.
 size_t rec_lds_bytes(int lds_rows, int P, bool wide, bool yrep);
 // Register-resident slot count the recursion kernel offers for this shape (0: none).
-int rec_register_slots(bool wide, bool has_wb, bool yrep, bool hubs, int max_wave_slots,
+int rec_register_slots(bool wide, int leak, bool yrep, bool hubs, int max_wave_slots,
                        int threads);
 // Slots of the hybrid variant (a wave's leading slices in registers, the others
 // streamed) for this kind of graph, 0 if there is none.
-int rec_hybrid_slots(bool wide, bool has_wb, bool yrep, bool hubs, int map /* 1: 32 KB, 2: 48 KB */);
+int rec_hybrid_slots(bool wide, int leak, bool yrep, bool hubs, int map /* 1: 32 KB, 2: 48 KB */);
 // Slots of the variant for graphs whose arcs take the pdf of the entered state
 // (0: none for this shape), and the rows it stages emissions for with this many threads.
 int rec_grouped_slots(bool wide, bool has_wb, int max_wave_slots, int threads);
@@ -163,6 +165,8 @@ int rec_grouped_max_rows(bool wide, int threads);
 // Arc slots per wave of the variant for graphs as above whose waves own one slice each
 // (0: none for this shape).
 int rec_short_slots(bool wide, int max_wave_slots, int threads);
+// Byte offset in an emission buffer of the word that stays 0 (32 KB or 48 KB map).
+uint32_t rec_zero_word(int hybrid);
 size_t occ_lds_bytes(int rows_a, int rows_b, int occ_rows, bool wide);
 int occ_plane_frames(int rows, int occ_rows, int most);
 size_t occ_plane_lds_bytes(int rows, int occ_rows, int frames);

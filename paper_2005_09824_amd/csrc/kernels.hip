@@ -554,16 +554,28 @@ __host__ __device__ constexpr int stage_passes(bool yrep, int nt)
 // states) instead of 32 KB each.
 // HUBS: the graph has hub slices (64 lanes that share one row's arcs, added up where
 // the slice ends); variants without it carry none of that code.
-template <typename Real, bool YREP, bool HAS_WB, int NSLOT, int NT, bool HYBRID = false,
+// LEAK 0: every state has the same initial probability. 1: arcs carry w * b[from] beside w.
+// 2: initial probabilities differ, state values are kept divided by them. With v = pi u
+// the leak target is 1 on every state in both directions, so that arcs need no factor of
+// their own: an arc of alpha carries w * pi[from] / pi[to] (folded in at upload), the total
+// s = sum pi u takes a row's pi from its closing slot, and s is also what a step is scaled by.
+// Two registers and a multiply-add less per slot than 1, so the hybrid has room for it: 5,000
+// states, 50,000 arcs, B = 32, 5.88 -> 1.82 ms a call (1 had to stream every arc); 1,237
+// states in registers, B = 17: 289 -> 238 us. 1 stays for fp64, for hub slices and for graphs
+// whose scaled weights would leave the normal range of fp32.
+template <typename Real, bool YREP, int LEAK, int NSLOT, int NT, bool HYBRID = false,
           bool BIG = false, bool HUBS = false>
 struct RecRegs {
-    static_assert(!HYBRID || (!HAS_WB && sizeof(Real) == 4), "hybrid: fp32, constant leak weights");
+    static constexpr bool HAS_WB = LEAK == 1;
+    static constexpr bool ROWS = LEAK == 2;
+    static_assert(!ROWS || !HUBS, "row weights: no hub slices");
+    static_assert(!HYBRID || (!HAS_WB && sizeof(Real) == 4), "hybrid: fp32, no factors per arc");
     static_assert(!BIG || (HYBRID && !YREP), "the large map: hybrid, plain emission rows");
     // this variant's LDS map (the names hide the 32 KB map's constants)
     static constexpr uint32_t kRegX1 = BIG ? 49152u : lfmmi::kRegX1;
     static constexpr uint32_t kRegY0 = BIG ? 98304u : lfmmi::kRegY0;
     static constexpr uint32_t kRegY1 = BIG ? 114688u : lfmmi::kRegY1;
-    static constexpr uint32_t kRegYZero = BIG ? 16380u : lfmmi::kRegYZero;
+    static constexpr uint32_t kRegYZero = BIG ? 16380u : lfmmi::kRegYZero;  // see rec_zero_word()
     static_assert(lfmmi::kRegPart == 131072u, "both maps end where the partial sums begin");
     static constexpr uint32_t kRB = sizeof(Real);  // bytes of a state value
     // Emission staging. Replicated rows (YREP): a thread writes four of the 32
@@ -698,7 +710,7 @@ struct RecRegs {
         // Without per-row leak-dot weights s is a_const * n.
         pv = row16_allsum(pv);
         const Real N = lane_value(pv, 0);
-        const Real Sd = HAS_WB ? lane_value(pv, 16) : aconst * N;
+        const Real Sd = HAS_WB ? lane_value(pv, 16) : (ROWS ? N : aconst * N);
         Real inv = 0;
         if (N > 0) {
             if constexpr (sizeof(Real) == 4) {
@@ -714,7 +726,7 @@ struct RecRegs {
             }
         }
         const Real c = eps * Sd * inv;
-        const Real cb = HAS_WB ? c : c * bconst;
+        const Real cb = HAS_WB || ROWS ? c : c * bconst;
         LFMMI_REC_MARK(0)  // head: last step's partial sums into this step's scalars
 
         // (the leak's accumulator stays fp32 also beside fp64 state values: a few products
@@ -799,8 +811,8 @@ struct RecRegs {
                 if (hub_slice && lane != 0) v = 0;
                 lds_st(xn + row4, v);
                 *reinterpret_cast<Real*>(tr + row4) = v;
-                n += v;
-                if (HAS_WB) s += (Real)wr[i + 1] * v;  // the closing slot's w is a[row]
+                n += ROWS ? (Real)wr[i + 1] * v : v;   // the closing slot's w is a[row]
+                if (HAS_WB) s += (Real)wr[i + 1] * v;
                 acc1 = 0;
                 acc2 = 0;
                 row4 += 64 * kRB;
@@ -840,7 +852,7 @@ struct RecRegs {
                                                : so[at + 1];
                 };
                 int o1 = slice_end(sl);
-                auto close = [&]() {
+                auto close = [&](const uint32_t closing_w) {  // w of the slice's last slot
                     const bool hub_slice =
                         HUBS && (sl - sl_stream < 64 ? ((hub_bits >> (sl - sl_stream)) & 1) != 0
                                                      : hub[sl] != 0);
@@ -853,7 +865,7 @@ struct RecRegs {
                     const uint32_t at = (uint32_t)(sl * 64 + lane) * kRB;
                     lds_st(xn + at, v);
                     *reinterpret_cast<Real*>(tr + at) = v;
-                    n += v;
+                    n += ROWS ? (Real)__uint_as_float(closing_w) * v : v;
                     a1 = 0;
                     a2 = 0;
                     ++sl;
@@ -884,7 +896,7 @@ struct RecRegs {
                     a1 = fmaf(t1, x1, a1);
                     a2 += t1;
                     i += 2;
-                    if (i == o1) close();
+                    if (i == o1) close(qa.w);
                     if (b_valid) {
                         const float t2 = __uint_as_float(qb.y) * e2, t3 = __uint_as_float(qb.w) * e3;
                         a1 = fmaf(t2, x2, a1);
@@ -892,7 +904,7 @@ struct RecRegs {
                         a1 = fmaf(t3, x3, a1);
                         a2 += t3;
                         i += 2;
-                        if (i == o1) close();
+                        if (i == o1) close(qb.w);
                     }
                 };
                 uint4 q0 = pair_at(0);
@@ -957,7 +969,7 @@ struct RecRegs {
         asm volatile("" ::: "memory");  // nothing else moves ahead of these reads
         pv = row16_allsum(pv);
         const Real N = lane_value(pv, 0);
-        const Real Sd = HAS_WB ? lane_value(pv, 16) : aconst * N;
+        const Real Sd = HAS_WB ? lane_value(pv, 16) : (ROWS ? N : aconst * N);
         Real inv = 0;
         if (N > 0) {
             if constexpr (sizeof(Real) == 4) {
@@ -970,7 +982,7 @@ struct RecRegs {
             }
         }
         const Real c = eps * Sd * inv;
-        const Real cb = HAS_WB ? c : c * bconst;
+        const Real cb = HAS_WB || ROWS ? c : c * bconst;
         LFMMI_REC_MARK(0)
         store_y(yn);
         load_y();
@@ -992,7 +1004,7 @@ struct RecRegs {
             const Real v = inv * acc1 + cb * (Real)acc2;
             lds_st(xn + row4_first, v);
             *reinterpret_cast<Real*>(reinterpret_cast<char*>(trow) + row4_first) = v;
-            n = v;
+            n = ROWS ? (Real)a_row * v : v;
             if (HAS_WB) s = (Real)a_row * v;
         }
         LFMMI_REC_MARK(1)
@@ -1125,6 +1137,7 @@ struct RecRegs {
                 n += v;
                 s += (Real)p.g.va[od.vec_at + row] * v;
             }
+            if (ROWS) n = s;
             n = wave_sum_uniform(n);
             s = wave_sum_uniform(s);
             if (lane == 0) {
@@ -1162,7 +1175,7 @@ struct RecRegs {
             if (s1 - s0 <= 1 && nsl <= kLeanSlots) {  // wave-uniform
                 const bool owns = s1 > s0;
                 float a_row = 0.f;  // the closing slot is the slice's last
-                if (HAS_WB && owns) a_row = nsl == 2 ? wr[1] : wr[kLeanSlots - 1];
+                if ((HAS_WB || ROWS) && owns) a_row = nsl == 2 ? wr[1] : wr[kLeanSlots - 1];
                 for (; k + 1 <= T; k += 2) {
                     step_lean<1>(k, T, tid, lane, eps, aconst, bconst, owns, a_row, row4_first, part_at);
                     step_lean<0>(k + 1, T, tid, lane, eps, aconst, bconst, owns, a_row, row4_first, part_at);
@@ -1189,7 +1202,7 @@ struct RecRegs {
             Real pv = lds_ldr<Real>(pc + (lane & (HAS_WB ? 31 : 15)) * kRB);
             pv = row16_allsum(pv);
             const Real N = lane_value(pv, 0);
-            const Real Sd = HAS_WB ? lane_value(pv, 16) : aconst * N;
+            const Real Sd = HAS_WB ? lane_value(pv, 16) : (ROWS ? N : aconst * N);
             const Real inv = N > 0 ? (Real)1 / N : (Real)0;
             const Real c = eps * Sd * inv;
             if (tid == 0) {
@@ -1968,7 +1981,7 @@ __device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scr
     }
 }
 
-template <typename Real, int NSLOT, bool YREP, bool HAS_WB, int NT, bool HYBRID = false,
+template <typename Real, int NSLOT, bool YREP, int LEAK, int NT, bool HYBRID = false,
           bool BIG = false, bool HUBS = false, int BY_STATE = 0>
 __global__ void __launch_bounds__(NT) k_rec(FbParams p)
 {
@@ -1982,7 +1995,7 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
     const OrdDesc od = p.g.ords[sd.graph * 3 + dir];
     if constexpr (BY_STATE == 1) {
         static_assert(NSLOT > 0 && !YREP && !HYBRID && !BIG && !HUBS, "grouped: resident arcs only");
-        RecGrouped<Real, HAS_WB, NSLOT, NT> r;
+        RecGrouped<Real, LEAK == 1, NSLOT, NT> r;
         if (dir == 0) r.template run<0>(p, sd, od, b);
         else r.template run<1>(p, sd, od, b);
     } else if constexpr (BY_STATE == 2) {
@@ -1990,10 +2003,10 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
         if (dir == 0) r.template run<0>(p, sd, od, b);
         else r.template run<1>(p, sd, od, b);
     } else if constexpr (NSLOT > 0) {
-        RecRegs<Real, YREP, HAS_WB, NSLOT, NT, HYBRID, BIG, HUBS> r;
+        RecRegs<Real, YREP, LEAK, NSLOT, NT, HYBRID, BIG, HUBS> r;
         r.run(p, sd, od, b, dir, lds_raw);
     } else {
-        rec_run<Real, YREP, HAS_WB, NT, HUBS>(p, sd, od, b, dir, lds_raw);
+        rec_run<Real, YREP, LEAK == 1, NT, HUBS>(p, sd, od, b, dir, lds_raw);
     }
     // The workgroup that finishes a sequence second (alpha or beta) computes its
     // scales: no launch of their own, and no wait for the other sequences.
@@ -2639,9 +2652,10 @@ __global__ void __launch_bounds__(kOccStatesThreads) k_occ_states(FbParams p)
         for (int u = 0; u < kRows; ++u) {
             const int r = r0 + u * kOccStatesThreads + tid;
             at[u] = r < rows_f ? row_occ[r] : 0u;
+            const Real pi = p.alpha_over_pi && r < rows_f ? (Real)p.g.va[ords[0].vec_at + r] : (Real)1;
 #pragma unroll
             for (int f = 0; f < F; ++f)
-                v[u][f] = r < rows_f && live(f) ? ar[(size_t)f * rows_f + r] : (Real)0;
+                v[u][f] = r < rows_f && live(f) ? pi * ar[(size_t)f * rows_f + r] : (Real)0;
         }
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
@@ -2687,23 +2701,27 @@ using RecKernel = void (*)(FbParams);
 constexpr int kHybridSlots = 36;
 
 struct RecVariant {
-    int wide, nslot, yrep, has_wb, max_threads;
+    int wide, nslot, yrep, leak, max_threads;
     RecKernel fn;
     int hybrid = 0;  // 1: hybrid, 2: hybrid with the large LDS map
     int hubs = 0;    // handles hub slices
     int grouped = 0; // emission by entered state: 1 RecGrouped, 2 RecShort
 };
 #define LFMMI_REC_GROUPED(REAL, WIDE, NSLOT, WB, NT)                                          \
-    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, (WB != 0), NT, false, false, false, 1>, \
+    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, WB, NT, false, false, false, 1>, \
      0, 0, 1}
 #define LFMMI_REC_SHORT(REAL, WIDE, NS, NT) \
-    {WIDE, NS, 0, 0, NT, k_rec<REAL, NS, false, false, NT, false, false, false, 2>, 0, 0, 2}
+    {WIDE, NS, 0, 0, NT, k_rec<REAL, NS, false, 0, NT, false, false, false, 2>, 0, 0, 2}
 
 #define LFMMI_REC(REAL, WIDE, NSLOT, WB, NT)                                                    \
-    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, (WB != 0), NT>},                         \
-    {WIDE, NSLOT, 1, WB, NT, k_rec<REAL, NSLOT, true, (WB != 0), NT>},                          \
-    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, (WB != 0), NT, false, false, true>, 0, 1}, \
-    {WIDE, NSLOT, 1, WB, NT, k_rec<REAL, NSLOT, true, (WB != 0), NT, false, false, true>, 0, 1}
+    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, WB, NT>},                         \
+    {WIDE, NSLOT, 1, WB, NT, k_rec<REAL, NSLOT, true, WB, NT>},                          \
+    {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, WB, NT, false, false, true>, 0, 1}, \
+    {WIDE, NSLOT, 1, WB, NT, k_rec<REAL, NSLOT, true, WB, NT, false, false, true>, 0, 1}
+// initial probabilities that differ, in row weights (no hub slices)
+#define LFMMI_REC_ROWS(NSLOT, NT)                                \
+    {0, NSLOT, 0, 2, NT, k_rec<float, NSLOT, false, 2, NT>},     \
+    {0, NSLOT, 1, 2, NT, k_rec<float, NSLOT, true, 2, NT>}
 const RecVariant kRecVariants[] = {
     // streamed arcs
     LFMMI_REC(float, 0, 0, 0, 1024), LFMMI_REC(float, 0, 0, 1, 1024),
@@ -2712,9 +2730,9 @@ const RecVariant kRecVariants[] = {
     LFMMI_REC(float, 0, 16, 0, 1024), LFMMI_REC(float, 0, 20, 0, 1024),
     LFMMI_REC(float, 0, 24, 0, 1024), LFMMI_REC(float, 0, 26, 0, 1024),
     // (28 slots with hub code and a replicated emission row would spill a register)
-    {0, 28, 0, 0, 1024, k_rec<float, 28, false, false, 1024>},
-    {0, 28, 1, 0, 1024, k_rec<float, 28, true, false, 1024>},
-    {0, 28, 0, 0, 1024, k_rec<float, 28, false, false, 1024, false, false, true>, 0, 1},
+    {0, 28, 0, 0, 1024, k_rec<float, 28, false, 0, 1024>},
+    {0, 28, 1, 0, 1024, k_rec<float, 28, true, 0, 1024>},
+    {0, 28, 0, 0, 1024, k_rec<float, 28, false, 0, 1024, false, false, true>, 0, 1},
     LFMMI_REC(float, 0, 16, 1, 1024),
     // register-resident arcs, 12 waves (168 VGPRs per lane)
     LFMMI_REC(float, 0, 32, 0, 768), LFMMI_REC(float, 0, 36, 0, 768),
@@ -2722,21 +2740,26 @@ const RecVariant kRecVariants[] = {
     LFMMI_REC(float, 0, 32, 0, 512), LFMMI_REC(float, 0, 48, 0, 512),
     LFMMI_REC(float, 0, 32, 1, 512),
     // (48 slots with per-arc leak factors: plain emission rows only, no spill)
-    {0, 48, 0, 1, 512, k_rec<float, 48, false, true, 512>},
-    {0, 48, 0, 1, 512, k_rec<float, 48, false, true, 512, false, false, true>, 0, 1},
+    {0, 48, 0, 1, 512, k_rec<float, 48, false, 1, 512>},
+    {0, 48, 0, 1, 512, k_rec<float, 48, false, 1, 512, false, false, true>, 0, 1},
     // fp64 state vectors (graphs with non-final states: numerators are small)
     LFMMI_REC(double, 1, 8, 1, 1024), LFMMI_REC(double, 1, 16, 1, 1024),
     LFMMI_REC(double, 1, 32, 1, 512),
     LFMMI_REC(double, 1, 16, 0, 1024), LFMMI_REC(double, 1, 32, 0, 512),
+    LFMMI_REC_ROWS(16, 1024), LFMMI_REC_ROWS(20, 1024), LFMMI_REC_ROWS(24, 1024),
+    LFMMI_REC_ROWS(26, 1024), LFMMI_REC_ROWS(36, 768), LFMMI_REC_ROWS(48, 512),
+    {0, kHybridSlots, 0, 2, 1024, k_rec<float, kHybridSlots, false, 2, 1024, true>, 1},
+    {0, kHybridSlots, 1, 2, 1024, k_rec<float, kHybridSlots, true, 2, 1024, true>, 1},
+    {0, kHybridSlots, 0, 2, 1024, k_rec<float, kHybridSlots, false, 2, 1024, true, true>, 2},
     // hybrid: kHybridSlots slots of a wave in registers, its other slices streamed
-    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, false, 1024, true>, 1},
-    {0, kHybridSlots, 1, 0, 1024, k_rec<float, kHybridSlots, true, false, 1024, true>, 1},
+    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true>, 1},
+    {0, kHybridSlots, 1, 0, 1024, k_rec<float, kHybridSlots, true, 0, 1024, true>, 1},
     // ... with the LDS map for up to 12288 states
-    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, false, 1024, true, true>, 2},
+    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true, true>, 2},
     // ... and the three for graphs with hub slices
     // (with a replicated emission row the hub code would spill a register: plain rows)
-    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, false, 1024, true, false, true>, 1, 1},
-    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, false, 1024, true, true, true>, 2, 1},
+    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true, false, true>, 1, 1},
+    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true, true, true>, 2, 1},
     // emission by entered state (two registers per slot: more slots fit)
     LFMMI_REC_GROUPED(float, 0, 16, 0, 1024), LFMMI_REC_GROUPED(float, 0, 24, 0, 1024),
     LFMMI_REC_GROUPED(float, 0, 32, 0, 1024), LFMMI_REC_GROUPED(float, 0, 36, 0, 1024),
@@ -2751,16 +2774,17 @@ const RecVariant kRecVariants[] = {
     LFMMI_REC_SHORT(double, 1, 4, 1024), LFMMI_REC_SHORT(double, 1, 8, 1024),
 };
 #undef LFMMI_REC
+#undef LFMMI_REC_ROWS
 #undef LFMMI_REC_GROUPED
 #undef LFMMI_REC_SHORT
 
-const RecVariant* find_rec(bool wide, int nslot, bool yrep, bool has_wb, int hybrid, bool hubs,
+const RecVariant* find_rec(bool wide, int nslot, bool yrep, int leak, int hybrid, bool hubs,
                            int grouped, int threads)
 {
     for (const RecVariant& v : kRecVariants)
         if (v.wide == (wide ? 1 : 0) && v.nslot == nslot && v.grouped == grouped &&
             (grouped != 2 || threads <= v.max_threads) &&
-            (grouped == 2 || v.has_wb == (has_wb ? 1 : 0)) &&
+            (grouped == 2 || v.leak == leak) &&
             (grouped || (v.yrep == (yrep ? 1 : 0) && v.hybrid == hybrid && v.hubs == (hubs ? 1 : 0))))
             return &v;
     return nullptr;
@@ -2768,12 +2792,12 @@ const RecVariant* find_rec(bool wide, int nslot, bool yrep, bool has_wb, int hyb
 
 }  // namespace
 
-int rec_register_slots(bool wide, bool has_wb, bool yrep, bool hubs, int max_wave_slots,
+int rec_register_slots(bool wide, int leak, bool yrep, bool hubs, int max_wave_slots,
                        int threads)
 {
     int best = 0;
     for (const RecVariant& v : kRecVariants)
-        if (v.wide == (wide ? 1 : 0) && v.has_wb == (has_wb ? 1 : 0) && v.nslot > 0 && !v.hybrid &&
+        if (v.wide == (wide ? 1 : 0) && v.leak == leak && v.nslot > 0 && !v.hybrid &&
             !v.grouped && v.yrep == (yrep ? 1 : 0) && v.hubs == (hubs ? 1 : 0) &&
             v.nslot >= max_wave_slots && threads <= v.max_threads && (best == 0 || v.nslot < best))
             best = v.nslot;
@@ -2784,7 +2808,7 @@ int rec_grouped_slots(bool wide, bool has_wb, int max_wave_slots, int threads)
 {
     int best = 0;
     for (const RecVariant& v : kRecVariants)
-        if (v.grouped == 1 && v.wide == (wide ? 1 : 0) && v.has_wb == (has_wb ? 1 : 0) &&
+        if (v.grouped == 1 && v.wide == (wide ? 1 : 0) && v.leak == (has_wb ? 1 : 0) &&
             v.nslot >= max_wave_slots && threads <= v.max_threads && (best == 0 || v.nslot < best))
             best = v.nslot;
     return best;
@@ -2805,10 +2829,12 @@ int rec_short_slots(bool wide, int max_wave_slots, int threads)
     return best;
 }
 
-int rec_hybrid_slots(bool wide, bool has_wb, bool yrep, bool hubs, int map)
+uint32_t rec_zero_word(int hybrid) { return hybrid == 2 ? 16380u : kRegYZero; }
+
+int rec_hybrid_slots(bool wide, int leak, bool yrep, bool hubs, int map)
 {
     for (const RecVariant& v : kRecVariants)
-        if (v.hybrid == map && v.wide == (wide ? 1 : 0) && v.has_wb == (has_wb ? 1 : 0) &&
+        if (v.hybrid == map && v.wide == (wide ? 1 : 0) && v.leak == leak &&
             v.yrep == (yrep ? 1 : 0) && v.hubs == (hubs ? 1 : 0))
             return v.nslot;
     return 0;
@@ -2917,7 +2943,7 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
     hipError_t e;
     const bool wide = sizeof(Real) == 8;
     const RecVariant* rv =
-        find_rec(wide, shape.rec_nslot, shape.rec_yrep != 0, shape.rec_has_wb != 0,
+        find_rec(wide, shape.rec_nslot, shape.rec_yrep != 0, shape.rec_leak,
                  shape.rec_hybrid, shape.rec_hubs != 0, shape.rec_short ? 2 : shape.rec_grouped,
                  shape.rec_threads);
     if (!rv || shape.rec_threads > rv->max_threads) return hipErrorInvalidConfiguration;

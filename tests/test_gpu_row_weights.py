@@ -1,0 +1,66 @@
+"""GPU parity for graphs whose initial probabilities differ from state to state, against the
+fp64 CPU oracle: state values kept divided by them, in every register-resident recursion.
+
+Tolerances as in test_gpu_parity.py: objf 1e-4 relative, gradient 1e-4 absolute."""
+import numpy as np
+import pytest
+
+from oracle import lfmmi_oracle as oracle
+from paper_2005_09824_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+# slots per wave: 16 .. 28 at 16 waves, the half as many waves with more, part of a wave's
+# arcs streamed with either LDS map, plain and replicated emission rows; one slice; a pdf per
+# entered state in a graph too large for the recursion by state (its occupancies are by state)
+@pytest.mark.parametrize("S,k,P,by_state,leak", [
+    (1, 0, 3, False, 1e-5), (20, 2, 10, False, 0.3), (64, 5, 300, False, 1e-5),
+    (1000, 5, 84, False, 1e-3), (1237, 6, 51, False, 1e-5), (1900, 8, 84, False, 1e-5),
+    (2048, 9, 84, False, 0.0), (2000, 10, 700, False, 1e-5), (600, 30, 60, False, 1e-5),
+    (5000, 9, 84, False, 1e-5), (5000, 9, 900, False, 1e-3), (9000, 5, 300, False, 1e-5),
+    (4500, 9, 84, True, 1e-3),
+])
+def test_row_weights(S, k, P, by_state, leak):
+    rng = np.random.default_rng(S + P)
+    g = workloads.random_den_graph(rng, S, k, P, 0.5)
+    if by_state:
+        g["pdf"] = rng.integers(0, P, S).astype(np.int32)[g["dst"]]
+    p = rng.uniform(0.01, 1.0, S) ** 2
+    g["init_prob"] = (p / p.sum()).astype(np.float32)
+    g["final_prob"] = rng.uniform(0.2, 1.0, S).astype(np.float32)
+    run(g, leak)
+
+
+@pytest.mark.parametrize("kind", ["wide_range", "tiny_weights"])
+def test_weights_that_leave_the_range_keep_their_factors_per_arc(kind):
+    # pi[from] / pi[to] or w * pi[from] outside the normal range of fp32
+    rng = np.random.default_rng(3)
+    g = workloads.random_den_graph(rng, 300, 5, 20, 0.5)
+    p = rng.uniform(0.5, 1.0, 300)
+    if kind == "wide_range":
+        p[::3] *= 1e-30
+    else:
+        g["logw"] = np.minimum(g["logw"], 0).astype(np.float32)
+        g["logw"][::7] = -84.0
+    g["init_prob"] = (p / p.sum()).astype(np.float32)
+    run(g, 1e-5)
+
+
+def run(g, leak):
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(9)
+    P, T = g["num_pdfs"], 14
+    lengths = np.array([14, 1, 0, 7, 2], np.int32)
+    x = rng.normal(0, 2, (5, T, P)).astype(np.float32)
+    for b in range(5):
+        x[b, lengths[b]:] = np.nan
+    h = binding.lfmmi_graph_create(g)
+    assert binding.lfmmi_graph_info(h)["fp64"] == 0
+    objf, grad, status = binding.lfmmi_forward_backward(h, torch.from_numpy(x).cuda(), lengths, leak)
+    torch.cuda.synchronize()
+    h.close()
+    lz, gamma = oracle.forward_backward(g, x, lengths, leak)
+    assert np.all(status.cpu().numpy() == 0)
+    assert np.all(np.abs(objf.cpu().numpy() - lz) <= 1e-4 * np.maximum(np.abs(lz), 1.0))
+    assert np.abs(grad.cpu().numpy().astype(np.float64) - gamma).max() <= 1e-4
