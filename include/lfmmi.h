@@ -183,17 +183,20 @@ lfmmi_status lfmmi_forward_backward_static(const lfmmi_graph *graph, const float
  *   status[b]   = the two passes' flags or-ed together (may be NULL)
  * exactly what lfmmi_forward_backward(num, ..., +1, 0, ...) followed by
  * lfmmi_forward_backward(den, ..., -1, 1, ...) leaves in the three arrays (bit for
- * bit), and enqueued the same way: the numerators' pass, then the denominator's,
- * on hip_stream. The emission values exp(logit - row maximum) are computed once,
+ * bit). Where the recursion workgroups of both passes fit the chip together (4 B
+ * at most its compute units: B <= 64), no sequence is empty and the batch has 8
+ * sequences or one of 256 frames, the passes run at the same time, the numerators'
+ * on a stream of the library's that hip_stream waits for (LFMMI_BESIDE=0: never).
+ * Otherwise the numerators' pass is enqueued first, then the denominator's, both on
+ * hip_stream, and the emission values exp(logit - row maximum) are computed once,
  * by the numerators' pass; the denominator's reads them from that handle's
  * workspace. If the denominator's pass is refused (an error code comes back) the
  * numerators' pass is already enqueued and the three arrays are left holding its
  * results alone: treat them as undefined.
- * (Running the two passes beside each other on streams of their own
- * was built and measured 13 to 24 % slower on the 128-sequence workload: the
- * numerators' workgroups then take compute units from the denominator's longest
- * sequences, whose recursion decides when the call ends, and HIP streams of one
- * priority give no say in that.) num: a batch handle with B graphs (or one graph
+ * (With more sequences, side by side was measured 13 to 24 % slower on the
+ * 128-sequence workload: the numerators' workgroups then take compute units from
+ * the denominator's longest sequences, whose recursion decides when the call ends,
+ * and HIP streams of one priority give no say in that.) num: a batch handle with B graphs (or one graph
  * for all); den: usually one shared graph; the two must be different handles.
  * Arguments and errors otherwise as lfmmi_forward_backward.
  */

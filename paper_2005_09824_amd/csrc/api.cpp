@@ -104,6 +104,9 @@ struct lfmmi_graph {
     // streams and events of the concurrent buckets of a call, made on first use
     hipEvent_t fork = nullptr;
     hipEvent_t join[Buckets::kMax] = {nullptr, nullptr, nullptr, nullptr};  // [0] unused
+    // a denominator whose numerators run beside it (see lfmmi_loss)
+    hipEvent_t side_fork = nullptr, side_done = nullptr;
+    int compute_units = 0;  // of the device of the upload
 
     // profiling: per call made while enabled 4 * (its bucket count) events
     int profile = 0;  // 0 off, 1 events around every kernel, 2 around the recursion only
@@ -617,6 +620,9 @@ lfmmi_status upload(lfmmi_graph* h)
     h->dg.row_slot = reinterpret_cast<const int32_t*>(base + at_rowpdf);
     h->dg.pdf_first = reinterpret_cast<const int32_t*>(base + at_pfirst);
     h->dg.ords = reinterpret_cast<const OrdDesc*>(base + at_ords);
+    if (hipDeviceGetAttribute(&h->compute_units, hipDeviceAttributeMultiprocessorCount, h->device) !=
+        hipSuccess)
+        h->compute_units = 0;
     h->uploaded = true;
     return LFMMI_OK;
 }
@@ -787,6 +793,226 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
                    shape.occ_multi == 1 ? 4 : (shape.occ_multi == 2 && large_planes ? 2 : 1)));
 }
 
+// One pass over a batch. `beside` (or null): an event of another pass that runs at the same
+// time and writes the same outputs, already recorded; this pass adds to them once it is past.
+lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32_t* lengths,
+                      int32_t B, int32_t T, int32_t P, float leak, float grad_scale,
+                      int accumulate, float* objf, float* grad, int32_t* status,
+                      void* hip_stream, int buckets_most, hipEvent_t beside)
+{
+    lfmmi_graph* h = const_cast<lfmmi_graph*>(graph);  // the workspace is mutable state
+    lfmmi_status st = check_call(h, logits, lengths, B, T, P, leak, grad_scale, objf, grad);
+    if (st != LFMMI_OK || B == 0) return st;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    hipError_t e;
+
+    // ---- per-sequence descriptors and the launch order (longest first)
+    std::vector<SeqDesc> seqs(B);
+    int64_t a_at = 0, b_at = 0, s_at = 0;
+    for (int32_t b = 0; b < B; ++b) {
+        const int32_t g = h->num_graphs == 1 ? 0 : b;
+        const int64_t rf = h->packed[g].ord[0].num_slices * kLanes;
+        const int64_t rb = h->packed[g].ord[1].num_slices * kLanes;
+        seqs[b].alpha_at = a_at;
+        seqs[b].beta_at = b_at;
+        seqs[b].T = lengths[b];
+        seqs[b].graph = g;
+        seqs[b].scal_at = (int32_t)s_at;
+        seqs[b].pad = 0;
+        a_at += rf * (lengths[b] + 1);
+        b_at += rb * (lengths[b] + 1);
+        s_at += lengths[b] + 1;
+    }
+    if (s_at > (int64_t)1 << 30) return fail(LFMMI_ERR_UNSUPPORTED, "too many frames in one call");
+    std::vector<int32_t> by_len(B);
+    std::iota(by_len.begin(), by_len.end(), 0);
+    std::stable_sort(by_len.begin(), by_len.end(), [&](int32_t x, int32_t y) {
+        const int64_t wx = (int64_t)lengths[x] * h->packed[seqs[x].graph].num_arcs;
+        const int64_t wy = (int64_t)lengths[y] * h->packed[seqs[y].graph].num_arcs;
+        return wx != wy ? wx > wy : lengths[x] > lengths[y];
+    });
+    std::vector<int32_t> order((size_t)2 * B);
+    for (int32_t i = 0; i < B; ++i) {
+        order[(size_t)2 * i] = by_len[i] << 1;
+        order[(size_t)2 * i + 1] = (by_len[i] << 1) | 1;
+    }
+
+    const CallLayout lay = layout_call(h, B, T, P, a_at, b_at, s_at);
+    const size_t late_bytes = beside ? (size_t)B * 2 * sizeof(float) : 0;
+    const size_t total = lay.total + late_bytes, stage_need = lay.stage_need;
+    if (total > h->ws_bytes) {
+        h->desc_lengths.clear();
+        h->desc_T = -1;
+        if (h->ws) {
+            (void)hipDeviceSynchronize();
+            (void)hipFree(h->ws);
+            h->ws = nullptr;
+            h->ws_bytes = 0;
+        }
+        // an eighth more than asked for: batches whose lengths vary a little from call to
+        // call (the usual training loop) then settle after a few calls instead of
+        // synchronising and reallocating at every new maximum
+        size_t want = total + total / 8;
+        if ((e = hipMalloc(&h->ws, want)) != hipSuccess) {
+            want = total;
+            e = hipMalloc(&h->ws, want);
+        }
+        if (e != hipSuccess) {
+            h->ws = nullptr;
+            return fail(LFMMI_ERR_OOM, "workspace of " + std::to_string(total) +
+                                           " bytes: " + hipGetErrorString(e));
+        }
+        h->ws_bytes = want;
+    }
+    // descriptors depend on the lengths and T only: a call with the same ones as
+    // the last finds them on the device already
+    const bool same_desc = h->desc_T == T && (int32_t)h->desc_lengths.size() == B &&
+                           std::equal(h->desc_lengths.begin(), h->desc_lengths.end(), lengths);
+    unsigned char* ws = static_cast<unsigned char*>(h->ws);
+    if (!same_desc) {
+        if (stage_need > h->stage_bytes) {
+            if (h->stage) {
+                if (h->stage_pending) (void)hipEventSynchronize(h->stage_done);
+                (void)hipHostFree(h->stage);
+                h->stage = nullptr;
+                h->stage_bytes = 0;
+            }
+            if ((e = hipHostMalloc(&h->stage, stage_need, hipHostMallocDefault)) != hipSuccess) {
+                h->stage = nullptr;
+                return fail(LFMMI_ERR_OOM, std::string("hipHostMalloc: ") + hipGetErrorString(e));
+            }
+            h->stage_bytes = stage_need;
+        }
+        if (!h->stage_done &&
+            (e = hipEventCreateWithFlags(&h->stage_done, hipEventDisableTiming)) != hipSuccess)
+            return fail_hip(e, "hipEventCreate");
+        if (h->stage_pending) {
+            // the previous call's descriptor copy must have left the staging buffer
+            if ((e = hipEventSynchronize(h->stage_done)) != hipSuccess)
+                return fail_hip(e, "hipEventSynchronize");
+            h->stage_pending = false;
+        }
+        unsigned char* stg = static_cast<unsigned char*>(h->stage);
+        std::memcpy(stg + lay.at_seqs, seqs.data(), sizeof(SeqDesc) * B);
+        std::memcpy(stg + lay.at_order, order.data(), sizeof(int32_t) * 2 * B);
+        h->desc_lengths.clear();
+        h->desc_T = -1;
+        if ((e = hipMemcpyAsync(ws, stg, stage_need, hipMemcpyHostToDevice, stream)) != hipSuccess)
+            return fail_hip(e, "hipMemcpyAsync");
+        if ((e = hipEventRecord(h->stage_done, stream)) != hipSuccess)
+            return fail_hip(e, "hipEventRecord");
+        h->stage_pending = true;
+        h->desc_lengths.assign(lengths, lengths + B);
+        h->desc_T = T;
+    }
+
+    FbParams p{};
+    LaunchShape shape;
+    fill_params(h, lay, ws, logits, B, T, P, leak, grad_scale, accumulate, objf, grad, status, &p,
+                &shape);
+    if (beside) {
+        p.objf_late = reinterpret_cast<float*>(ws + lay.total);
+        p.status_late = reinterpret_cast<int32_t*>(p.objf_late + B);
+    }
+
+    // ---- buckets of sequences that run concurrently (longest sequences first):
+    // an eighth, a quarter, a quarter and the rest, so that the bucket that ends
+    // last has little occupancy work left to do on its own
+    Buckets bk;
+    bk.before_occ = beside;
+    {
+        int want = std::min(env_int("LFMMI_BUCKETS", Buckets::kMax), buckets_most);
+        want = std::max(1, std::min(want, B / 2));
+        if (T == 0) want = 1;
+        static const double upto[Buckets::kMax][Buckets::kMax] = {
+            {1.0, 1.0, 1.0, 1.0}, {0.25, 1.0, 1.0, 1.0}, {0.15, 0.5, 1.0, 1.0}, {0.125, 0.375, 0.625, 1.0}};
+        double fr[Buckets::kMax];
+        for (int q = 0; q < Buckets::kMax; ++q) fr[q] = upto[want - 1][q];
+        if (const char* txt = std::getenv("LFMMI_BUCKET_FRACS")) {  // "f0,f1,f2": tuning
+            const char* c = txt;
+            for (int q = 0; q + 1 < want && *c; ++q) {
+                char* stop = nullptr;
+                const double v = std::strtod(c, &stop);
+                if (stop == c) break;
+                if (v > 0.0 && v <= 1.0) fr[q] = v;
+                c = *stop == ',' ? stop + 1 : stop;
+            }
+        }
+        bk.n = want;
+        int at = 0;
+        for (int q = 0; q < want; ++q) {
+            int end = q == want - 1 ? B : (int)std::lround(fr[q] * B);
+            end = std::max(at + 1, std::min(end, B - (want - 1 - q)));
+            bk.first[q] = at;
+            bk.count[q] = end - at;
+            for (int i = at; i < end; ++i) bk.tmax[q] = std::max(bk.tmax[q], lengths[by_len[i]]);
+            at = end;
+        }
+        if (want > 1) {
+            if (!h->fork &&
+                (e = hipEventCreateWithFlags(&h->fork, hipEventDisableTiming)) != hipSuccess)
+                return fail_hip(e, "hipEventCreate");
+            for (int q = 1; q < want; ++q) {
+                // plain streams (default priority) that do not synchronise with stream 0
+                hipStream_t aux = nullptr;
+                if ((e = bucket_stream(h->device, q, &aux)) != hipSuccess)
+                    return fail_hip(e, "hipStreamCreate");
+                if (!h->join[q] &&
+                    (e = hipEventCreateWithFlags(&h->join[q], hipEventDisableTiming)) != hipSuccess)
+                    return fail_hip(e, "hipEventCreate");
+                bk.streams[q] = aux;
+                bk.join[q] = h->join[q];
+            }
+            bk.fork = h->fork;
+        }
+    }
+
+    hipEvent_t* ev = nullptr;
+    if (h->profile) {
+        const size_t first = h->ev.size(), count = 4 * (size_t)bk.n;
+        h->ev.resize(first + count, nullptr);
+        for (size_t i = first; i < first + count; ++i)
+            if (!h->ev_free.empty()) {
+                h->ev[i] = h->ev_free.back();
+                h->ev_free.pop_back();
+            } else if ((e = hipEventCreate(&h->ev[i])) != hipSuccess) {
+                for (size_t j = first; j < i; ++j) (void)hipEventDestroy(h->ev[j]);
+                h->ev.resize(first);
+                return fail_hip(e, "hipEventCreate");
+            }
+        h->ev_buckets.push_back(bk.n);
+        ev = h->ev.data() + first;
+    }
+    if ((e = launch_forward_backward(p, shape, stream, ev, bk)) != hipSuccess)
+        return fail_hip(e, "kernel launch");
+    return LFMMI_OK;
+}
+
+// Whether the two passes of a full-loss call run at the same time (see lfmmi_loss): both
+// passes' recursion workgroups fit the chip, every sequence has frames (its occupancy kernel
+// does the adding), no events are being collected, which would overlap, and the call is long
+// or its batch large enough. With 8 sequences each pass in turn cuts its batch into four
+// buckets, so that one after the other costs more launches and events already (50 frames: 190
+// to 270 us a call, 106 to 170 beside each other); smaller batches of short sequences are bound
+// by the host, which pays 30 to 70 us more for the events of the second stream (training step,
+// B = 2, 45 frames: 153 us in turn, 226 beside) and need longer passes to win that back (B = 2:
+// 81 / 64 us of GPU time at 48 frames, 290 / 201 and 446 / 353 us at 280).
+bool beside_each_other(const lfmmi_graph* num, const lfmmi_graph* den, const int32_t* lengths,
+                       int32_t B, int32_t T)
+{
+    if (env_int("LFMMI_BESIDE", 1) == 0 || env_int("LFMMI_BUCKETS", Buckets::kMax) < Buckets::kMax)
+        return false;
+    if (!lengths || B < 1 || T < 1 || num->profile || den->profile) return false;
+    if (!num->uploaded || !den->uploaded || num->device != den->device) return false;
+    if (4 * (int64_t)B > den->compute_units) return false;
+    int32_t longest = 0;
+    for (int32_t b = 0; b < B; ++b) {
+        if (lengths[b] < 1) return false;
+        longest = std::max(longest, lengths[b]);
+    }
+    return B >= 2 * Buckets::kMax || longest >= 256;
+}
+
 }  // namespace
 
 extern "C" {
@@ -861,6 +1087,8 @@ void lfmmi_graph_destroy(lfmmi_graph* h)
             if (h->join[q]) (void)hipEventDestroy(h->join[q]);
         }
         if (h->fork) (void)hipEventDestroy(h->fork);
+        if (h->side_fork) (void)hipEventDestroy(h->side_fork);
+        if (h->side_done) (void)hipEventDestroy(h->side_done);
     }
     delete h;
 }
@@ -870,186 +1098,8 @@ lfmmi_status lfmmi_forward_backward(const lfmmi_graph* graph, const float* logit
                                     float leak, float grad_scale, int accumulate, float* objf,
                                     float* grad, int32_t* status, void* hip_stream)
 {
-    lfmmi_graph* h = const_cast<lfmmi_graph*>(graph);  // the workspace is mutable state
-    lfmmi_status st = check_call(h, logits, lengths, B, T, P, leak, grad_scale, objf, grad);
-    if (st != LFMMI_OK || B == 0) return st;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    hipError_t e;
-
-    // ---- per-sequence descriptors and the launch order (longest first)
-    std::vector<SeqDesc> seqs(B);
-    int64_t a_at = 0, b_at = 0, s_at = 0;
-    for (int32_t b = 0; b < B; ++b) {
-        const int32_t g = h->num_graphs == 1 ? 0 : b;
-        const int64_t rf = h->packed[g].ord[0].num_slices * kLanes;
-        const int64_t rb = h->packed[g].ord[1].num_slices * kLanes;
-        seqs[b].alpha_at = a_at;
-        seqs[b].beta_at = b_at;
-        seqs[b].T = lengths[b];
-        seqs[b].graph = g;
-        seqs[b].scal_at = (int32_t)s_at;
-        seqs[b].pad = 0;
-        a_at += rf * (lengths[b] + 1);
-        b_at += rb * (lengths[b] + 1);
-        s_at += lengths[b] + 1;
-    }
-    if (s_at > (int64_t)1 << 30) return fail(LFMMI_ERR_UNSUPPORTED, "too many frames in one call");
-    std::vector<int32_t> by_len(B);
-    std::iota(by_len.begin(), by_len.end(), 0);
-    std::stable_sort(by_len.begin(), by_len.end(), [&](int32_t x, int32_t y) {
-        const int64_t wx = (int64_t)lengths[x] * h->packed[seqs[x].graph].num_arcs;
-        const int64_t wy = (int64_t)lengths[y] * h->packed[seqs[y].graph].num_arcs;
-        return wx != wy ? wx > wy : lengths[x] > lengths[y];
-    });
-    std::vector<int32_t> order((size_t)2 * B);
-    for (int32_t i = 0; i < B; ++i) {
-        order[(size_t)2 * i] = by_len[i] << 1;
-        order[(size_t)2 * i + 1] = (by_len[i] << 1) | 1;
-    }
-
-    const CallLayout lay = layout_call(h, B, T, P, a_at, b_at, s_at);
-    const size_t total = lay.total, stage_need = lay.stage_need;
-    if (total > h->ws_bytes) {
-        h->desc_lengths.clear();
-        h->desc_T = -1;
-        if (h->ws) {
-            (void)hipDeviceSynchronize();
-            (void)hipFree(h->ws);
-            h->ws = nullptr;
-            h->ws_bytes = 0;
-        }
-        // an eighth more than asked for: batches whose lengths vary a little from call to
-        // call (the usual training loop) then settle after a few calls instead of
-        // synchronising and reallocating at every new maximum
-        size_t want = total + total / 8;
-        if ((e = hipMalloc(&h->ws, want)) != hipSuccess) {
-            want = total;
-            e = hipMalloc(&h->ws, want);
-        }
-        if (e != hipSuccess) {
-            h->ws = nullptr;
-            return fail(LFMMI_ERR_OOM, "workspace of " + std::to_string(total) +
-                                           " bytes: " + hipGetErrorString(e));
-        }
-        h->ws_bytes = want;
-    }
-    // descriptors depend on the lengths and T only: a call with the same ones as
-    // the last finds them on the device already
-    const bool same_desc = h->desc_T == T && (int32_t)h->desc_lengths.size() == B &&
-                           std::equal(h->desc_lengths.begin(), h->desc_lengths.end(), lengths);
-    unsigned char* ws = static_cast<unsigned char*>(h->ws);
-    if (!same_desc) {
-        if (stage_need > h->stage_bytes) {
-            if (h->stage) {
-                if (h->stage_pending) (void)hipEventSynchronize(h->stage_done);
-                (void)hipHostFree(h->stage);
-                h->stage = nullptr;
-                h->stage_bytes = 0;
-            }
-            if ((e = hipHostMalloc(&h->stage, stage_need, hipHostMallocDefault)) != hipSuccess) {
-                h->stage = nullptr;
-                return fail(LFMMI_ERR_OOM, std::string("hipHostMalloc: ") + hipGetErrorString(e));
-            }
-            h->stage_bytes = stage_need;
-        }
-        if (!h->stage_done &&
-            (e = hipEventCreateWithFlags(&h->stage_done, hipEventDisableTiming)) != hipSuccess)
-            return fail_hip(e, "hipEventCreate");
-        if (h->stage_pending) {
-            // the previous call's descriptor copy must have left the staging buffer
-            if ((e = hipEventSynchronize(h->stage_done)) != hipSuccess)
-                return fail_hip(e, "hipEventSynchronize");
-            h->stage_pending = false;
-        }
-        unsigned char* stg = static_cast<unsigned char*>(h->stage);
-        std::memcpy(stg + lay.at_seqs, seqs.data(), sizeof(SeqDesc) * B);
-        std::memcpy(stg + lay.at_order, order.data(), sizeof(int32_t) * 2 * B);
-        h->desc_lengths.clear();
-        h->desc_T = -1;
-        if ((e = hipMemcpyAsync(ws, stg, stage_need, hipMemcpyHostToDevice, stream)) != hipSuccess)
-            return fail_hip(e, "hipMemcpyAsync");
-        if ((e = hipEventRecord(h->stage_done, stream)) != hipSuccess)
-            return fail_hip(e, "hipEventRecord");
-        h->stage_pending = true;
-        h->desc_lengths.assign(lengths, lengths + B);
-        h->desc_T = T;
-    }
-
-    FbParams p{};
-    LaunchShape shape;
-    fill_params(h, lay, ws, logits, B, T, P, leak, grad_scale, accumulate, objf, grad, status, &p,
-                &shape);
-
-    // ---- buckets of sequences that run concurrently (longest sequences first):
-    // an eighth, a quarter, a quarter and the rest, so that the bucket that ends
-    // last has little occupancy work left to do on its own
-    Buckets bk;
-    {
-        int want = std::min(env_int("LFMMI_BUCKETS", Buckets::kMax), (int)Buckets::kMax);
-        want = std::max(1, std::min(want, B / 2));
-        if (T == 0) want = 1;
-        static const double upto[Buckets::kMax][Buckets::kMax] = {
-            {1.0, 1.0, 1.0, 1.0}, {0.25, 1.0, 1.0, 1.0}, {0.15, 0.5, 1.0, 1.0}, {0.125, 0.375, 0.625, 1.0}};
-        double fr[Buckets::kMax];
-        for (int q = 0; q < Buckets::kMax; ++q) fr[q] = upto[want - 1][q];
-        if (const char* txt = std::getenv("LFMMI_BUCKET_FRACS")) {  // "f0,f1,f2": tuning
-            const char* c = txt;
-            for (int q = 0; q + 1 < want && *c; ++q) {
-                char* stop = nullptr;
-                const double v = std::strtod(c, &stop);
-                if (stop == c) break;
-                if (v > 0.0 && v <= 1.0) fr[q] = v;
-                c = *stop == ',' ? stop + 1 : stop;
-            }
-        }
-        bk.n = want;
-        int at = 0;
-        for (int q = 0; q < want; ++q) {
-            int end = q == want - 1 ? B : (int)std::lround(fr[q] * B);
-            end = std::max(at + 1, std::min(end, B - (want - 1 - q)));
-            bk.first[q] = at;
-            bk.count[q] = end - at;
-            for (int i = at; i < end; ++i) bk.tmax[q] = std::max(bk.tmax[q], lengths[by_len[i]]);
-            at = end;
-        }
-        if (want > 1) {
-            if (!h->fork &&
-                (e = hipEventCreateWithFlags(&h->fork, hipEventDisableTiming)) != hipSuccess)
-                return fail_hip(e, "hipEventCreate");
-            for (int q = 1; q < want; ++q) {
-                // plain streams (default priority) that do not synchronise with stream 0
-                hipStream_t aux = nullptr;
-                if ((e = bucket_stream(h->device, q, &aux)) != hipSuccess)
-                    return fail_hip(e, "hipStreamCreate");
-                if (!h->join[q] &&
-                    (e = hipEventCreateWithFlags(&h->join[q], hipEventDisableTiming)) != hipSuccess)
-                    return fail_hip(e, "hipEventCreate");
-                bk.streams[q] = aux;
-                bk.join[q] = h->join[q];
-            }
-            bk.fork = h->fork;
-        }
-    }
-
-    hipEvent_t* ev = nullptr;
-    if (h->profile) {
-        const size_t first = h->ev.size(), count = 4 * (size_t)bk.n;
-        h->ev.resize(first + count, nullptr);
-        for (size_t i = first; i < first + count; ++i)
-            if (!h->ev_free.empty()) {
-                h->ev[i] = h->ev_free.back();
-                h->ev_free.pop_back();
-            } else if ((e = hipEventCreate(&h->ev[i])) != hipSuccess) {
-                for (size_t j = first; j < i; ++j) (void)hipEventDestroy(h->ev[j]);
-                h->ev.resize(first);
-                return fail_hip(e, "hipEventCreate");
-            }
-        h->ev_buckets.push_back(bk.n);
-        ev = h->ev.data() + first;
-    }
-    if ((e = launch_forward_backward(p, shape, stream, ev, bk)) != hipSuccess)
-        return fail_hip(e, "kernel launch");
-    return LFMMI_OK;
+    return run_pass(graph, logits, lengths, B, T, P, leak, grad_scale, accumulate, objf, grad,
+                    status, hip_stream, Buckets::kMax, nullptr);
 }
 
 lfmmi_status lfmmi_forward_backward_static(const lfmmi_graph* graph, const float* logits,
@@ -1111,15 +1161,47 @@ lfmmi_status lfmmi_loss(const lfmmi_graph* num, const lfmmi_graph* den, const fl
 {
     if (!num || !den) return fail(LFMMI_ERR_INVALID_ARG, "graph is null");
     if (num == den) return fail(LFMMI_ERR_INVALID_ARG, "numerator and denominator share a handle");
-    // Numerators (+1, overwrite), then the denominator (-1, accumulate), one after the
-    // other on the caller's stream. Running the two passes on streams of their own
-    // was measured slower (see the header): without stream priorities the numerators'
-    // workgroups take compute units from the denominator's longest sequences, whose
-    // recursion is the critical path of the call.
     lfmmi_graph* hn = const_cast<lfmmi_graph*>(num);
     lfmmi_graph* hd = const_cast<lfmmi_graph*>(den);
+    lfmmi_status st = LFMMI_OK;
+    // Numerators (+1, overwrite) and the denominator (-1, accumulate). Where every recursion
+    // workgroup of both passes finds a compute unit of its own (a denominator's fills one) the
+    // passes run beside each other, the numerators on the last bucket's stream: the
+    // denominator's occupancy kernels wait for them and add to what they wrote.
+    // Numerators of 20 to 120 phones beside an HMM-expanded denominator of 2,016 states, B = 64:
+    // training step 1,059 -> 776 us; up to 225 frames, 2,000 states: 574 -> 432 us at B = 64,
+    // 467 -> 336 at B = 32, 445 -> 316 at B = 8.
+    if (beside_each_other(hn, hd, lengths, B, T)) {
+        st = check_call(hn, logits, lengths, B, T, P, leak, 1.f, objf, grad);
+        if (st == LFMMI_OK) st = check_call(hd, logits, lengths, B, T, P, leak, -1.f, objf, grad);
+        if (st != LFMMI_OK) return st;
+        hipStream_t stream = static_cast<hipStream_t>(hip_stream), side = nullptr;
+        constexpr int kSide = Buckets::kMax - 1;
+        hipError_t e;
+        if ((e = bucket_stream(hd->device, kSide, &side)) != hipSuccess)
+            return fail_hip(e, "hipStreamCreate");
+        for (hipEvent_t* ev : {&hd->side_fork, &hd->side_done})
+            if (!*ev && (e = hipEventCreateWithFlags(ev, hipEventDisableTiming)) != hipSuccess)
+                return fail_hip(e, "hipEventCreate");
+        if ((e = hipEventRecord(hd->side_fork, stream)) != hipSuccess ||
+            (e = hipStreamWaitEvent(side, hd->side_fork, 0)) != hipSuccess)
+            return fail_hip(e, "fork");
+        st = run_pass(num, logits, lengths, B, T, P, leak, 1.f, 0, objf, grad, status, side, 1,
+                      nullptr);
+        // (also where a pass failed: what it did enqueue is joined to the caller's stream)
+        if ((e = hipEventRecord(hd->side_done, side)) != hipSuccess) return fail_hip(e, "join");
+        if (st == LFMMI_OK)
+            st = run_pass(den, logits, lengths, B, T, P, leak, -1.f, 1, objf, grad, status,
+                          hip_stream, kSide, hd->side_done);
+        if (st != LFMMI_OK) (void)hipStreamWaitEvent(stream, hd->side_done, 0);
+        return st;
+    }
+    // Otherwise one after the other on the caller's stream: beside each other the numerators'
+    // workgroups take compute units from the denominator's longest sequences, whose recursion
+    // is the critical path of the call (B = 128, 2,000 states: 1.40 ms in sequence, 1.46 to
+    // 1.80 ms on streams of their own).
     hn->last_emis = nullptr;
-    lfmmi_status st = lfmmi_forward_backward(num, logits, lengths, B, T, P, leak, 1.f, 0, objf,
+    st = lfmmi_forward_backward(num, logits, lengths, B, T, P, leak, 1.f, 0, objf,
                                              grad, status, hip_stream);
     if (st != LFMMI_OK) return st;
     // exp(logit - row maximum) and the row maxima are the same for both passes: the

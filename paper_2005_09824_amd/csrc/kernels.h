@@ -83,6 +83,8 @@ struct FbParams {
     int32_t* status_out;    // [B] or null
     float* objf;            // [B]
     float* grad;            // [B, T, P]
+    float* objf_late;       // [B], status_late [B]: where the recursion leaves what the
+    int32_t* status_late;   // occupancy kernel then adds to objf and status_out; or null
     int64_t scal_total;
     int32_t B, T, P;
     int32_t lds_rows;       // largest padded row count over the handle's graphs
@@ -128,6 +130,7 @@ struct Buckets {
     int tmax[kMax] = {0, 0, 0, 0};   // longest sequence of the bucket
     hipStream_t streams[kMax] = {nullptr, nullptr, nullptr, nullptr};  // [0] unused
     hipEvent_t fork = nullptr;                                        // n > 1 only
+    hipEvent_t before_occ = nullptr;  // every bucket's occupancy kernel waits for it, or null
     hipEvent_t join[kMax] = {nullptr, nullptr, nullptr, nullptr};      // [0] unused
 };
 

@@ -1976,6 +1976,11 @@ __device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scr
         if (lossy) st |= 4;
         const float val = nonfinite_in ? __builtin_nanf("") : (float)(lz + msum);
         const float out = p.grad_scale * val;
+        if (p.objf_late) {  // k_occ adds them, see add_late_objective
+            p.objf_late[b] = out;
+            p.status_late[b] = st;
+            return;
+        }
         p.objf[b] = p.accumulate ? p.objf[b] + out : out;
         if (p.status_out) p.status_out[b] = p.accumulate ? (p.status_out[b] | st) : st;
     }
@@ -2032,6 +2037,18 @@ template <typename Real>
 __device__ __forceinline__ Real occ_term(const uint2 r, const Real* XA, const Real* XB)
 {
     return (Real)__uint_as_float(r.y) * lds_at(XB, r.x >> 16) * lds_at(XA, r.x & 0xffffu);
+}
+
+
+// A pass that runs beside the one it adds to: its recursion leaves a sequence's objective and
+// status aside, and its occupancy kernel, which waits for the other pass, adds them. At the end
+// of that kernel: a store ahead of the descriptor loads would take them off the scalar path
+// (2,000-state denominator, B = 64: 652 -> 710 us a call).
+__device__ __forceinline__ void add_late_objective(const FbParams& p, const int b)
+{
+    if (!p.objf_late || blockIdx.x != 0 || threadIdx.x != 0) return;
+    p.objf[b] += p.objf_late[b];
+    if (p.status_out) p.status_out[b] |= p.status_late[b];
 }
 
 template <typename Real>
@@ -2140,6 +2157,7 @@ __global__ void __launch_bounds__(1024) k_occ(FbParams p, int frames_per_wg)
         // the next frame's row sums are stored after its staging barrier, which
         // every thread reaches only once it is done here
     }
+    add_late_objective(p, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -2575,6 +2593,7 @@ __global__ void __launch_bounds__(1024) k_occ_planes(FbParams p, int groups_per_
         }
         LFMMI_MARK(8)  // sums of the pdfs with many rows
     }
+    add_late_objective(p, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -2694,6 +2713,7 @@ __global__ void __launch_bounds__(kOccStatesThreads) k_occ_states(FbParams p)
             *g = p.accumulate ? *g + out : out;
         }
     }
+    add_late_objective(p, b);
 }
 
 // ---- kernel variants ---------------------------------------------------------
@@ -2990,6 +3010,7 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
         if ((e = hipGetLastError()) != hipSuccess) return e;
         LFMMI_EVQ(2)
         const int tq = std::min(bk.tmax[q], p.T);
+        if (bk.before_occ && (e = hipStreamWaitEvent(on, bk.before_occ, 0)) != hipSuccess) return e;
         if (tq > 0) {
             if (shape.occ_states > 0) {
                 const int F = shape.occ_states;

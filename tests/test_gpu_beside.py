@@ -1,0 +1,87 @@
+"""The full-loss call whose two passes run at the same time (small batches) against the two
+calls one after the other: the same bits, also with empty sequences in the batch, from another
+stream than the default one and replayed from a HIP graph."""
+import numpy as np
+import pytest
+
+from paper_2005_09824_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _setup(B, pdf_by_state, seed, empty=False):
+    import torch
+    rng = np.random.default_rng(seed)
+    if pdf_by_state:
+        den = workloads.hmm_den_graph(rng, 14, 6, 0.5)
+    else:
+        den = workloads.random_den_graph(rng, 700, 5, 28, 0.5)
+    P = den["num_pdfs"]
+    num = [workloads.phone_string_num_graph(rng.integers(1, P // 2, size=int(n)), P)
+           for n in rng.integers(4, 14, size=B)]
+    lens = rng.integers(30, 90, size=B).astype(np.int32)
+    if B < 8:
+        lens[0] = 256  # fewer sequences run at the same time from 256 frames on
+    if empty:
+        lens[B // 2] = 0
+    x = torch.from_numpy(rng.normal(0, 2, size=(B, lens.max() + 5, P)).astype(np.float32)).cuda()
+    return binding.lfmmi_graph_create_batch(num), binding.lfmmi_graph_create(den), x, lens
+
+
+def _in_turn(num, den, x, lens):
+    objf, grad, st = binding.lfmmi_forward_backward(num, x, lens, 1e-5, 1.0, False)
+    binding.lfmmi_forward_backward(den, x, lens, 1e-5, -1.0, True, objf, grad, st)
+    return objf, grad, st
+
+
+# 64 sequences: the largest batch whose 4 B workgroups fit 256 compute units; 65: one more
+@pytest.mark.parametrize("B,pdf_by_state,empty", [(1, False, False), (1, True, False), (9, True, True),
+                                                  (7, False, False), (8, True, False), (64, True, False),
+                                                  (64, False, False), (65, True, False)])
+def test_same_bits_as_the_two_passes_in_turn(B, pdf_by_state, empty):
+    import torch
+    num, den, x, lens = _setup(B, pdf_by_state, 100 + B, empty)
+    want = _in_turn(num, den, x, lens)
+    torch.cuda.synchronize()
+    out = (torch.full_like(want[0], 7.0), torch.full_like(want[1], -3.0), torch.full_like(want[2], 5))
+    for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        for t in out:
+            t.fill_(9)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            for _ in range(3):
+                binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)
+            got = [t.clone() for t in out]
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+    num.close()
+    den.close()
+
+
+def test_replays_from_a_hip_graph():
+    import torch
+    num, den, x, lens = _setup(6, True, 5)
+    want = _in_turn(num, den, x, lens)
+    out = tuple(torch.empty_like(t) for t in want)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)
+    for _ in range(3):
+        for t in out:
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, want):
+            assert torch.equal(a, b)
+        binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)  # eager work between the replays
+        torch.cuda.synchronize()
+    del graph
+    num.close()
+    den.close()
