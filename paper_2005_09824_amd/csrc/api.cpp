@@ -921,7 +921,17 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
     Buckets bk;
     bk.before_occ = beside;
     {
-        int want = std::min(env_int("LFMMI_BUCKETS", Buckets::kMax), buckets_most);
+        // One bucket where the longest recursion is too short for other sequences' occupancy
+        // pass to hide behind it: every further bucket costs 10 to 20 us in launches and events.
+        // The estimate of a step follows the kernels' times from 20 to 5,000 states. 1 / 4
+        // buckets, B = 32: 20 states, 200 frames 158 / 168 us; 600 states, 120 frames 130 / 154;
+        // 2,000 states, 120 frames 184 / 201, 400 frames 535 / 507; 5,000 states, 60 frames
+        // 266 / 273, 120 frames 472 / 445. LFMMI_BUCKETS set: as many as it says.
+        double longest_us = 0.0;
+        for (int32_t b = 0; b < B; ++b)
+            longest_us = std::max(longest_us, lengths[b] * (0.6 + 3e-5 * h->packed[seqs[b].graph].num_arcs));
+        int want = std::min(env_int("LFMMI_BUCKETS", longest_us < 200.0 ? 1 : (int)Buckets::kMax),
+                            buckets_most);
         want = std::max(1, std::min(want, B / 2));
         if (T == 0) want = 1;
         static const double upto[Buckets::kMax][Buckets::kMax] = {

@@ -1,4 +1,6 @@
-"""The full-loss call whose two passes run at the same time (small batches) against the two
+"""Which parts of a call run at the same time must not show in its results.
+
+The full-loss call whose two passes run at the same time (small batches) against the two
 calls one after the other: the same bits, also with empty sequences in the batch, from another
 stream than the default one and replayed from a HIP graph."""
 import numpy as np
@@ -84,4 +86,39 @@ def test_replays_from_a_hip_graph():
         torch.cuda.synchronize()
     del graph
     num.close()
+    den.close()
+
+
+# 90 frames: one bucket by default; 330: four (500 states, 3,000 arcs); both against every count
+@pytest.mark.parametrize("T", [90, 330])
+def test_bucket_counts_give_the_same_bits_eager_and_replayed(T, monkeypatch):
+    import torch
+    rng = np.random.default_rng(T)
+    den = binding.lfmmi_graph_create(workloads.random_den_graph(rng, 500, 5, 40, 0.5))
+    lens = rng.integers(1, T + 1, size=12).astype(np.int32)
+    lens[3] = T
+    x = torch.from_numpy(rng.normal(0, 2, size=(12, T, 40)).astype(np.float32)).cuda()
+    want = binding.lfmmi_forward_backward(den, x, lens, 1e-5, 1.0, False)
+    out = tuple(torch.empty_like(t) for t in want)
+    side = torch.cuda.Stream()
+    for count in "1234":
+        monkeypatch.setenv("LFMMI_BUCKETS", count)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            binding.lfmmi_forward_backward(den, x, lens, 1e-5, 1.0, False, *out)
+            torch.cuda.synchronize()
+            for a, b in zip(out, want):
+                assert torch.equal(a, b)
+            with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+                binding.lfmmi_forward_backward(den, x, lens, 1e-5, 1.0, False, *out)
+        for _ in range(3):
+            for t in out:
+                t.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(out, want):
+                assert torch.equal(a, b)
+        del graph
     den.close()
