@@ -1001,12 +1001,11 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
 // Whether the two passes of a full-loss call run at the same time (see lfmmi_loss): both
 // passes' recursion workgroups fit the chip, every sequence has frames (its occupancy kernel
 // does the adding), no events are being collected, which would overlap, and the call is long
-// or its batch large enough. With 8 sequences each pass in turn cuts its batch into four
-// buckets, so that one after the other costs more launches and events already (50 frames: 190
-// to 270 us a call, 106 to 170 beside each other); smaller batches of short sequences are bound
-// by the host, which pays 30 to 70 us more for the events of the second stream (training step,
-// B = 2, 45 frames: 153 us in turn, 226 beside) and need longer passes to win that back (B = 2:
-// 81 / 64 us of GPU time at 48 frames, 290 / 201 and 446 / 353 us at 280).
+// or its batch large enough. 8 sequences of 50 frames: 84 to 119 us a call in turn, 65 to 100
+// beside each other; 64 of 150 frames: 223 to 395 and 175 to 323. Smaller batches of short
+// sequences are bound by the host, which pays 30 to 70 us more for the events of the second
+// stream (training step, B = 2, 45 frames: 153 us in turn, 226 beside), and need longer passes
+// to win that back (B = 2, 280 frames: 290 to 446 us in turn, 201 to 353 beside).
 bool beside_each_other(const lfmmi_graph* num, const lfmmi_graph* den, const int32_t* lengths,
                        int32_t B, int32_t T)
 {
@@ -1179,7 +1178,7 @@ lfmmi_status lfmmi_loss(const lfmmi_graph* num, const lfmmi_graph* den, const fl
     // passes run beside each other, the numerators on the last bucket's stream: the
     // denominator's occupancy kernels wait for them and add to what they wrote.
     // Numerators of 20 to 120 phones beside an HMM-expanded denominator of 2,016 states, B = 64:
-    // training step 1,059 -> 776 us; up to 225 frames, 2,000 states: 574 -> 432 us at B = 64,
+    // training step 1,059 -> 798 us; up to 225 frames, 2,000 states: 574 -> 432 us at B = 64,
     // 467 -> 336 at B = 32, 445 -> 316 at B = 8.
     if (beside_each_other(hn, hd, lengths, B, T)) {
         st = check_call(hn, logits, lengths, B, T, P, leak, 1.f, objf, grad);
