@@ -2032,13 +2032,16 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
 // on timing. (An LDS float atomic add takes about 190 clocks per wave
 // instruction on this chip whatever its addresses, against 2 to 4 for a store.)
 //   gamma_t[d] = c_t * e_t[d] * sum_{a: pdf_a = d} w_a * ahat_{t-1}[src_a] * bhat_t[dst_a]
+// The weight meets alpha first. Where alpha is kept divided by the initial probabilities the
+// weight holds pi[src_a], and only their product is an ordinary number: a small pi times a
+// small beta would be lost (alpha's own share cannot bring it back). In the other graphs
+// neither order loses what the other keeps: both vectors add up to about one.
 // ---------------------------------------------------------------------------
 template <typename Real>
 __device__ __forceinline__ Real occ_term(const uint2 r, const Real* XA, const Real* XB)
 {
-    return (Real)__uint_as_float(r.y) * lds_at(XB, r.x >> 16) * lds_at(XA, r.x & 0xffffu);
+    return (Real)__uint_as_float(r.y) * lds_at(XA, r.x & 0xffffu) * lds_at(XB, r.x >> 16);
 }
-
 
 // A pass that runs beside the one it adds to: its recursion leaves a sequence's objective and
 // status aside, and its occupancy kernel, which waits for the other pass, adds them. At the end
@@ -2470,7 +2473,7 @@ __global__ void __launch_bounds__(1024) k_occ_planes(FbParams p, int groups_per_
                         const int at = i + v0 + v;  // this slot
                         if (v > 0 && at >= w1) break;
 #pragma unroll
-                        for (int f = 0; f < F; ++f) acc[f] = fmaf(w[v] * vb[v][f], va[v][f], acc[f]);
+                        for (int f = 0; f < F; ++f) acc[f] = fmaf(w[v] * va[v][f], vb[v][f], acc[f]);  // (see k_occ)
                         if (((v0 + v) & 1) && at + 1 == o_end) {  // the slice ends with this pair
                             const int k = sl - s0;
                             uint32_t slot;

@@ -48,13 +48,18 @@ def test_weights_that_leave_the_range_keep_their_factors_per_arc(kind):
 
 
 def run(g, leak):
-    torch = pytest.importorskip("torch")
     rng = np.random.default_rng(9)
     P, T = g["num_pdfs"], 14
     lengths = np.array([14, 1, 0, 7, 2], np.int32)
     x = rng.normal(0, 2, (5, T, P)).astype(np.float32)
     for b in range(5):
         x[b, lengths[b]:] = np.nan
+    compare(g, x, lengths, leak)
+
+
+def compare(g, x, lengths, leak):
+    torch = pytest.importorskip("torch")
+    lengths = np.asarray(lengths, np.int32)
     h = binding.lfmmi_graph_create(g)
     assert binding.lfmmi_graph_info(h)["fp64"] == 0
     objf, grad, status = binding.lfmmi_forward_backward(h, torch.from_numpy(x).cuda(), lengths, leak)
@@ -64,3 +69,37 @@ def run(g, leak):
     assert np.all(status.cpu().numpy() == 0)
     assert np.all(np.abs(objf.cpu().numpy() - lz) <= 1e-4 * np.maximum(np.abs(lz), 1.0))
     assert np.abs(grad.cpu().numpy().astype(np.float64) - gamma).max() <= 1e-4
+
+
+def _graph(S, P, arcs, init_prob, final_prob=None):
+    src, dst, pdf, logw = zip(*arcs)
+    return {"num_states": S, "num_pdfs": P, "src": np.array(src, np.int32), "dst": np.array(dst, np.int32),
+            "pdf": np.array(pdf, np.int32), "logw": np.array(logw, np.float32),
+            "init_prob": np.array(init_prob, np.float32),
+            "final_prob": np.ones(S, np.float32) if final_prob is None else np.array(final_prob, np.float32)}
+
+
+def _rare_state(rare, extra_arcs=(), final=1.0):
+    """State 0 starts with probability `rare` and has pdfs 0 and 1 to itself; states 1 to 8,
+    which it is left for by `extra_arcs` only, take pdfs 2 to 5."""
+    arcs = [(0, 0, 0, 0.0), (0, 0, 1, -1.0)] + list(extra_arcs)
+    arcs += [(s, 1 + (s - 1 + k) % 8, 2 + (s + k) % 4, -1.1) for s in range(1, 9) for k in (1, 2, 3)]
+    return _graph(9, 7, arcs, [rare] + [1 / 8] * 8, [final] + [1.0] * 8)
+
+
+def _noise(shape, seed=0):
+    return np.random.default_rng(seed).normal(0, 1, shape).astype(np.float32)
+
+
+# The rare state wins the first frames and is penalised in the following ones, so that its
+# beta is small where its alpha is not: w pi beta leaves the range of fp32, w alpha beta does
+# not. Both kernels that add up occupancies by arc.
+@pytest.mark.parametrize("planes", ["4", "0"])
+@pytest.mark.parametrize("leak", [0.0, 1e-5])
+@pytest.mark.parametrize("rare", [1e-8, 1e-12, 1e-17, 1e-30])
+def test_occupancies_of_a_rare_initial_state(rare, leak, planes, monkeypatch):
+    monkeypatch.setenv("LFMMI_OCC_MULTI", planes)
+    x = _noise((1, 10, 7))
+    x[:, :5, :2] += (75 - np.log(rare)) / 5
+    x[:, 5:, 2:] += 15
+    compare(_rare_state(rare), x, [10], leak)
