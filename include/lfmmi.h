@@ -223,10 +223,10 @@ lfmmi_status lfmmi_graph_info(const lfmmi_graph *graph, int64_t info[8]);
 
 /* Packed ordering `ord` of graph `g`: info[0] rows, [1] slices (64 rows each),
  * [2] waves, [3] total slots (sum of slice widths), [4] max slots of one wave,
- * [5] arc slots the recursion kernel keeps in registers (0: streamed; also 0 where init_prob
- *     is not uniform and only the leading slots of a wave fit),
- * [6] 1 if the emission row is replicated per LDS bank, [7] 1 if the arcs carry
- * a per-arc leak factor (non-uniform init_prob), [8] modelled LDS cycles of the
+ * [5] arc slots of a wave the recursion kernel keeps in registers (0: all streamed),
+ * [6] 1 if the emission row is replicated per LDS bank, [7] how the leak meets an init_prob
+ * that is not uniform: 1 the arcs carry a factor each, 2 state values are kept divided by
+ * init_prob and the arcs need none (0: init_prob is uniform), [8] modelled LDS cycles of the
  * gathers of one frame (per slot and half-wave, the largest number of distinct
  * addresses in one of the 32 banks), [9] 1 if every FWD / BWD slice ends in a
  * closing slot (packed so when init_prob is not uniform), [10] number of hub

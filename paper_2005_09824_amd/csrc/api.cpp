@@ -1254,9 +1254,9 @@ lfmmi_status lfmmi_graph_ordering_info(const lfmmi_graph* h, int32_t g, int32_t 
     info[2] = o.num_waves;
     info[3] = o.total_slots;
     info[4] = o.max_wave_slots;
-    info[5] = ord < 2 && !(h->over_pi && h->rec_hybrid) ? h->rec_nslot : 0;
+    info[5] = ord < 2 ? h->rec_nslot : 0;
     info[6] = ord < 2 && h->rec_yrep ? 1 : 0;
-    info[7] = o.has_wb;
+    info[7] = o.has_wb && h->over_pi ? 2 : o.has_wb;
     info[8] = o.gather_cycles;
     info[9] = ord < 2 ? o.closing_slots : 0;
     info[10] = 0;

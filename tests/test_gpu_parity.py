@@ -82,7 +82,7 @@ def test_scaled_configs_every_element(config, scale):
 
 
 def test_nonuniform_start_distribution_on_the_register_path():
-    # a start distribution that is not uniform: every arc carries its leak factor
+    # a start distribution that is not uniform: state values are kept divided by it
     # and slices end in closing slots; all final weights positive keeps it in fp32
     wl = workloads.make_workload(2, scale={"S": 1500, "B": 4, "Tlo": 20, "Thi": 45}, pad_value=np.nan)
     g = wl["den"]
@@ -92,7 +92,7 @@ def test_nonuniform_start_distribution_on_the_register_path():
     g["final_prob"] = rng.uniform(0.2, 1.0, g["num_states"]).astype(np.float32)
     h = binding.lfmmi_graph_create(g)
     info = binding.lfmmi_graph_ordering_info(h, 0, 0)
-    assert info["per_arc_leak"] == 1 and info["closing_slots"] == 1 and info["register_slots"] > 0
+    assert info["per_arc_leak"] == 2 and info["closing_slots"] == 1 and info["register_slots"] > 0
     assert binding.lfmmi_graph_info(h)["fp64"] == 0
     lz, gamma = oracle.forward_backward(g, wl["logits"], wl["lengths"], wl["leak"])
     check(*run_gpu(h, wl["logits"], wl["lengths"], wl["leak"]), lz, gamma, "non-uniform pi")
@@ -228,7 +228,12 @@ def test_pdf_with_many_occupancy_rows_fp32_and_fp64():
     (3000, 14, 200, "uniform", 0, 0, 3, 10, 30, "hybrid"),     # 32 KB state vectors, replicated emission row
     (3000, 14, 1200, "zipf", 0, 0, 3, 10, 30, "hybrid"),       # plain emission row, pdfs with many rows
     (9000, 6, 3500, "uniform", 0, 0, 2, 8, 20, "streamed"),    # more pdfs than the staging of the register paths takes
-    (3000, 14, 100, "uniform", 1, 0, 3, 10, 30, "streamed"),   # per-arc leak factors, too many arcs for registers
+    (3000, 14, 100, "uniform", 1, 0, 3, 10, 30, "hybrid"),     # values over a start distribution that is not uniform
+    # nonuniform_pi 2: leak factors per arc instead (what a graph whose weights leave the range gets)
+    (3000, 14, 100, "uniform", 2, 0, 3, 10, 30, "streamed"),   # ... too many arcs for registers
+    (1500, 8, 60, "uniform", 2, 0, 3, 10, 30, "registers"),    # ... 16 waves
+    (400, 12, 60, "uniform", 2, 0, 3, 10, 30, "registers"),    # ... up to 8 waves
+    (400, 12, 300, "uniform", 2, 0, 3, 10, 30, "registers"),   # ... plain emission row
     (1500, 10, 60, "uniform", 1, 1, 3, 10, 30, "fp64"),        # fp64 with per-arc leak factors
     (2500, 12, 90, "zipf", 0, 1, 3, 10, 30, "fp64"),           # fp64, larger
     (5000, 3, 84, "uniform", 0, 0, 3, 10, 30, "registers"),    # sparse rows
@@ -237,7 +242,9 @@ def test_pdf_with_many_occupancy_rows_fp32_and_fp64():
     (64, 5, 7, "uniform", 0, 0, 5, 1, 9, "registers"),         # one slice, lengths from 1
 ])
 def test_odd_shapes_through_every_recursion_variant(S, k, P, dist, nonuniform_pi, zero_finals,
-                                                    B, Tlo, Thi, expect):
+                                                    B, Tlo, Thi, expect, monkeypatch):
+    if nonuniform_pi == 2:
+        monkeypatch.setenv("LFMMI_OVER_PI", "0")
     rng = np.random.default_rng(1000 + S + P)
     g = workloads.random_den_graph(rng, S, k, P, 0.5, dist)
     if nonuniform_pi:
@@ -268,6 +275,7 @@ def test_odd_shapes_through_every_recursion_variant(S, k, P, dist, nonuniform_pi
             assert info["register_slots"] > 0
         else:
             assert info["register_slots"] == 0
+        assert info["per_arc_leak"] == (0, 2, 1)[nonuniform_pi]
     lz, gamma = oracle.forward_backward(g, x, lengths, 1e-5)
     check(*run_gpu(h, x, lengths, 1e-5), lz, gamma, "S %d P %d %s" % (S, P, expect))
     h.close()

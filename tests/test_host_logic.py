@@ -392,6 +392,25 @@ def test_packer_finds_graphs_whose_pdf_is_a_function_of_the_entered_state(monkey
     h.close()
 
 
+@pytest.mark.parametrize("over_pi,S,slots,leak", [
+    ("1", 3000, 36, 2),   # values over init_prob: the first slots of a wave in registers
+    ("0", 3000, 0, 1),    # a factor per arc: no room for any
+    ("1", 1000, 16, 2), ("0", 1000, 16, 1),
+])
+def test_ordering_info_tells_what_runs_where_initial_probabilities_differ(over_pi, S, slots, leak, monkeypatch):
+    monkeypatch.setenv("LFMMI_OVER_PI", over_pi)
+    rng = np.random.default_rng(8)
+    g = workloads.random_den_graph(rng, S, 14 if S == 3000 else 6, 100, 0.5)
+    pi = rng.uniform(0.05, 1.0, S)
+    g["init_prob"] = (pi / pi.sum()).astype(np.float32)
+    h = binding.lfmmi_graph_pack(g)
+    for o in (0, 1):
+        info = binding.lfmmi_graph_ordering_info(h, 0, o)
+        assert info["register_slots"] == slots and info["per_arc_leak"] == leak
+        assert (slots == 16) == (info["max_wave_slots"] <= 16)
+    h.close()
+
+
 def test_bench_refuses_more_than_one_gpu():
     # one GPU is the whole target: the command says so and exits before it touches a device
     import subprocess
