@@ -578,6 +578,22 @@ struct RecRegs {
     static constexpr uint32_t kRegYZero = BIG ? 16380u : lfmmi::kRegYZero;  // see rec_zero_word()
     static_assert(lfmmi::kRegPart == 131072u, "both maps end where the partial sums begin");
     static constexpr uint32_t kRB = sizeof(Real);  // bytes of a state value
+    // One arc of an fp32 row without a factor of its own. ROWS: emission times value first.
+    // The weight may hold a ratio of initial probabilities far below one, which that value
+    // makes up for and the emission does not (w * e of a state with pi = 1e-17 whose only arc
+    // takes a pdf 70 below the frame's best is 0). As many instructions either way.
+    static __device__ __forceinline__ void add_arc(const float w, const float e, const float x,
+                                                   float& acc1, float& acc2)
+    {
+        if constexpr (ROWS) {
+            acc1 = fmaf(w, e * x, acc1);
+            acc2 = fmaf(w, e, acc2);
+        } else {
+            const float t = w * e;
+            acc1 = fmaf(t, x, acc1);
+            acc2 += t;
+        }
+    }
     // Emission staging. Replicated rows (YREP): a thread writes four of the 32
     // copies of one value with one 16-byte store, kYPass passes of NT threads
     // cover 8 * P <= kYPass * NT quads. Plain rows: one value per thread and pass.
@@ -790,7 +806,10 @@ struct RecRegs {
             // arc slots; closing and padding slots see e == 0 or w == 0 and add nothing
             const float t0 = wr[i] * e0;
             const float t1 = wr[i + 1] * e1;
-            if constexpr (sizeof(Real) == 4) {
+            if constexpr (ROWS) {
+                add_arc(wr[i], e0, x0, acc1, acc2);
+                add_arc(wr[i + 1], e1, x1, acc1, acc2);
+            } else if constexpr (sizeof(Real) == 4) {
                 acc1 = fmaf(t0, x0, acc1);
                 acc2 = HAS_WB ? fmaf(wbr[HAS_WB ? i : 0], e0, acc2) : acc2 + t0;
                 acc1 = fmaf(t1, x1, acc1);
@@ -890,19 +909,13 @@ struct RecRegs {
                     // one wait for the eight: the first use names the value loaded last
                     asm volatile("" : "+v"(x0), "+v"(e0), "+v"(x1), "+v"(e1), "+v"(x2), "+v"(e2)
                                  : "v"(x3), "v"(e3));
-                    const float t0 = __uint_as_float(qa.y) * e0, t1 = __uint_as_float(qa.w) * e1;
-                    a1 = fmaf(t0, x0, a1);
-                    a2 += t0;
-                    a1 = fmaf(t1, x1, a1);
-                    a2 += t1;
+                    add_arc(__uint_as_float(qa.y), e0, x0, a1, a2);
+                    add_arc(__uint_as_float(qa.w), e1, x1, a1, a2);
                     i += 2;
                     if (i == o1) close(qa.w);
                     if (b_valid) {
-                        const float t2 = __uint_as_float(qb.y) * e2, t3 = __uint_as_float(qb.w) * e3;
-                        a1 = fmaf(t2, x2, a1);
-                        a2 += t2;
-                        a1 = fmaf(t3, x3, a1);
-                        a2 += t3;
+                        add_arc(__uint_as_float(qb.y), e2, x2, a1, a2);
+                        add_arc(__uint_as_float(qb.w), e3, x3, a1, a2);
                         i += 2;
                         if (i == o1) close(qb.w);
                     }
@@ -995,6 +1008,10 @@ struct RecRegs {
 #pragma unroll
         for (int i = 0; i < kLeanSlots; ++i) {
             const float t = wr[i] * ev[i];
+            if constexpr (ROWS) {
+                add_arc(wr[i], ev[i], xv[i], acc1, acc2);
+                continue;
+            }
             if constexpr (sizeof(Real) == 4) acc1 = fmaf(t, xv[i], acc1);
             else acc1 += (Real)t * xv[i];
             acc2 = HAS_WB ? fmaf(wbr[HAS_WB ? i : 0], ev[i], acc2) : acc2 + t;

@@ -79,11 +79,13 @@ def _graph(S, P, arcs, init_prob, final_prob=None):
             "final_prob": np.ones(S, np.float32) if final_prob is None else np.array(final_prob, np.float32)}
 
 
-def _rare_state(rare, extra_arcs=(), final=1.0):
+def _rare_state(rare, extra_arcs=(), final=1.0, arcs_out=3, copies=1):
     """State 0 starts with probability `rare` and has pdfs 0 and 1 to itself; states 1 to 8,
-    which it is left for by `extra_arcs` only, take pdfs 2 to 5."""
+    which it is left for by `extra_arcs` only, take pdfs 2 to 5, `arcs_out` arcs out of each.
+    Every arc stands there `copies` times, each with its share of the weight."""
     arcs = [(0, 0, 0, 0.0), (0, 0, 1, -1.0)] + list(extra_arcs)
-    arcs += [(s, 1 + (s - 1 + k) % 8, 2 + (s + k) % 4, -1.1) for s in range(1, 9) for k in (1, 2, 3)]
+    arcs += [(s, 1 + (s - 1 + k) % 8, 2 + (s + k) % 4, -1.1) for s in range(1, 9) for k in range(1, 1 + arcs_out)]
+    arcs = [(i, j, d, w - np.log(copies)) for i, j, d, w in arcs for _ in range(copies)]
     return _graph(9, 7, arcs, [rare] + [1 / 8] * 8, [final] + [1.0] * 8)
 
 
@@ -103,3 +105,26 @@ def test_occupancies_of_a_rare_initial_state(rare, leak, planes, monkeypatch):
     x[:, :5, :2] += (75 - np.log(rare)) / 5
     x[:, 5:, 2:] += 15
     compare(_rare_state(rare), x, [10], leak)
+
+
+# The rare state is left through one arc that takes a pdf far below the frame's best: the
+# weight w pi[from] / pi[to] times that emission leaves the range of fp32, times the state's
+# value it does not. In a wave of few slots, of more, and of more than the registers hold.
+@pytest.mark.parametrize("arcs_out,copies", [(1, 1), (3, 1), (3, 20)])
+@pytest.mark.parametrize("rare,below", [(1e-4, 70.0), (1e-12, 70.0), (1e-17, 60.0), (1e-17, 70.0)])
+def test_recursion_out_of_a_rare_initial_state(rare, below, arcs_out, copies):
+    x = _noise((1, 8, 7))
+    x[0, :3, 0] += (below + 20 - np.log(rare)) / 3
+    x[0, 3, 6] += below
+    x[0, 3, 0] -= 30
+    x[0, 3, 2:6] -= 10
+    g = _rare_state(rare, [(0, 1, 1, -0.5), (0, 2, 2, -1.0)], 1.0, arcs_out, copies)
+    h = binding.lfmmi_graph_pack(g)
+    info = [binding.lfmmi_graph_ordering_info(h, 0, o) for o in (0, 1)]
+    h.close()
+    assert all(i["per_arc_leak"] == 2 for i in info)
+    if copies > 1:
+        assert all(0 < i["register_slots"] < i["max_wave_slots"] for i in info)
+    else:
+        assert (info[0]["max_wave_slots"] <= 4) == (arcs_out == 1)  # alpha, which holds the ratios
+    compare(g, x, [8], 0.0)
