@@ -117,21 +117,29 @@ struct lfmmi_graph {
 
 namespace {
 
-// Whether the weights of a graph stay ordinary fp32 numbers when state values are kept
-// divided by the initial probabilities: w * pi[from] / pi[to] (alpha) and w * pi[from]
-// (occupancies).
+// Whether a graph stays in the range of fp32 when its state values are kept divided by the
+// initial probabilities. Values reach 1 / pi times what they are otherwise, so the rarest state
+// may start e^40 (2e17) times less often than the most frequent one; with arc weights up to e^20 the
+// sums then stay below e^88. What the device copy holds has to be ordinary numbers:
+// w * pi[from] / pi[to] (alpha), w * pi[from] (occupancies) and final * pi (the closing product).
 bool leak_by_rows(const ArcList& g)
 {
+    constexpr double kLow = -87.0, kHigh = 88.0;  // inside the normal range of fp32
+    constexpr double kMostRatio = 40.0, kMostWeight = 20.0;
+    auto normal = [&](const double l) { return l > kLow && l < kHigh; };
     std::vector<double> lp(g.num_states);
+    double most = -INFINITY, least = INFINITY;
     for (int32_t s = 0; s < g.num_states; ++s) {
         if (!(g.init_prob[s] > 0.f)) return false;
         lp[s] = std::log((double)g.init_prob[s]);
+        most = std::max(most, lp[s]);
+        least = std::min(least, lp[s]);
+        if (g.final_prob[s] > 0.f && !normal(lp[s] + std::log((double)g.final_prob[s]))) return false;
     }
-    constexpr double kLow = -87.0, kHigh = 88.0;  // inside the normal range of fp32
-    auto normal = [&](const double l) { return l > kLow && l < kHigh; };
+    if (most - least > kMostRatio) return false;
     for (int64_t a = 0; a < g.num_arcs; ++a) {
         const double l = (double)g.logw[a] + lp[g.src[a]];
-        if (!normal(l) || !normal(l - lp[g.dst[a]])) return false;
+        if (g.logw[a] > kMostWeight || !normal(l) || !normal(l - lp[g.dst[a]])) return false;
     }
     return true;
 }

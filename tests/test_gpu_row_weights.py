@@ -29,7 +29,7 @@ def test_row_weights(S, k, P, by_state, leak):
     p = rng.uniform(0.01, 1.0, S) ** 2
     g["init_prob"] = (p / p.sum()).astype(np.float32)
     g["final_prob"] = rng.uniform(0.2, 1.0, S).astype(np.float32)
-    run(g, leak)
+    run(g, leak, 2 if S > 1 else 0)
 
 
 @pytest.mark.parametrize("kind", ["wide_range", "tiny_weights"])
@@ -44,24 +44,26 @@ def test_weights_that_leave_the_range_keep_their_factors_per_arc(kind):
         g["logw"] = np.minimum(g["logw"], 0).astype(np.float32)
         g["logw"][::7] = -84.0
     g["init_prob"] = (p / p.sum()).astype(np.float32)
-    run(g, 1e-5)
+    run(g, 1e-5, 1)
 
 
-def run(g, leak):
+def run(g, leak, kept):
     rng = np.random.default_rng(9)
     P, T = g["num_pdfs"], 14
     lengths = np.array([14, 1, 0, 7, 2], np.int32)
     x = rng.normal(0, 2, (5, T, P)).astype(np.float32)
     for b in range(5):
         x[b, lengths[b]:] = np.nan
-    compare(g, x, lengths, leak)
+    compare(g, x, lengths, leak, kept)
 
 
-def compare(g, x, lengths, leak):
+def compare(g, x, lengths, leak, kept):
+    # kept: 2 state values divided by the initial probabilities, 1 a leak factor per arc
     torch = pytest.importorskip("torch")
     lengths = np.asarray(lengths, np.int32)
     h = binding.lfmmi_graph_create(g)
     assert binding.lfmmi_graph_info(h)["fp64"] == 0
+    assert binding.lfmmi_graph_ordering_info(h, 0, 0)["per_arc_leak"] == kept
     objf, grad, status = binding.lfmmi_forward_backward(h, torch.from_numpy(x).cuda(), lengths, leak)
     torch.cuda.synchronize()
     h.close()
@@ -104,7 +106,7 @@ def test_occupancies_of_a_rare_initial_state(rare, leak, planes, monkeypatch):
     x = _noise((1, 10, 7))
     x[:, :5, :2] += (75 - np.log(rare)) / 5
     x[:, 5:, 2:] += 15
-    compare(_rare_state(rare), x, [10], leak)
+    compare(_rare_state(rare), x, [10], leak, 2 if rare > 1e-18 else 1)
 
 
 # The rare state is left through one arc that takes a pdf far below the frame's best: the
@@ -122,9 +124,28 @@ def test_recursion_out_of_a_rare_initial_state(rare, below, arcs_out, copies):
     h = binding.lfmmi_graph_pack(g)
     info = [binding.lfmmi_graph_ordering_info(h, 0, o) for o in (0, 1)]
     h.close()
-    assert all(i["per_arc_leak"] == 2 for i in info)
     if copies > 1:
         assert all(0 < i["register_slots"] < i["max_wave_slots"] for i in info)
     else:
         assert (info[0]["max_wave_slots"] <= 4) == (arcs_out == 1)  # alpha, which holds the ratios
-    compare(g, x, [8], 0.0)
+    compare(g, x, [8], 0.0, 2)
+
+
+# What cannot be kept divided by the initial probabilities in fp32: values that would overflow
+# (large weights into a rare state), final weights that vanish beside them, ratios beyond e^40.
+@pytest.mark.parametrize("kind", ["overflow", "final", "ratio"])
+def test_graphs_that_keep_their_factors_per_arc(kind):
+    if kind == "overflow":
+        S = 51
+        arcs = [(0, 1, 2, 0.0), (0, 7, 3, 0.0)]
+        for s in range(1, S):
+            arcs += [(s, 0, s % 5, 6.0), (s, 1 + s % (S - 1), s * 3 % 5, 0.0)]
+        g, x = _graph(S, 5, arcs, [1e-37] + [0.02] * (S - 1)), _noise((1, 8, 5))
+    elif kind == "final":
+        g, x = _rare_state(1e-17, final=1e-28), _noise((1, 10, 7))
+        x[:, :, :2] += 12
+    else:
+        g, x = _rare_state(1e-19), _noise((1, 10, 7))
+        x[:, :, :2] += 8
+    for leak in (0.0, 1e-5):
+        compare(g, x, [x.shape[1]], leak, 1)
