@@ -2803,6 +2803,7 @@ const RecVariant kRecVariants[] = {
     // emission by entered state (two registers per slot: more slots fit)
     LFMMI_REC_GROUPED(float, 0, 16, 0, 1024), LFMMI_REC_GROUPED(float, 0, 24, 0, 1024),
     LFMMI_REC_GROUPED(float, 0, 32, 0, 1024), LFMMI_REC_GROUPED(float, 0, 36, 0, 1024),
+    LFMMI_REC_GROUPED(float, 0, 48, 0, 512),
     LFMMI_REC_GROUPED(float, 0, 16, 1, 1024), LFMMI_REC_GROUPED(float, 0, 24, 1, 1024),
     LFMMI_REC_GROUPED(float, 0, 32, 1, 1024), LFMMI_REC_GROUPED(float, 0, 36, 1, 1024),
     LFMMI_REC_GROUPED(double, 1, 8, 1, 1024), LFMMI_REC_GROUPED(double, 1, 16, 1, 1024),

@@ -99,3 +99,17 @@ def test_recursion_by_state_flags_what_it_flagged_before():
     want = torch.zeros((39, P))
     want[torch.arange(39), (torch.arange(39) + 1) % P] = 1.0
     assert torch.equal(grad[0, :39].cpu(), want)
+
+
+# small graphs with many arcs a state: 38 to 48 slots a wave with at most 8 waves, lengths around
+# the steps fetched ahead; one slice, three, six
+@pytest.mark.parametrize("S,k,waves,slots", [(60, 40, 1, 48), (150, 30, 3, 46), (340, 24, 6, 38)])
+def test_recursion_by_state_of_small_dense_graphs(S, k, waves, slots):
+    g = by_state_graph(np.random.default_rng(S + k), S, k, 40)
+    h = binding.lfmmi_graph_pack(g)
+    info, fwd = binding.lfmmi_graph_info(h), binding.lfmmi_graph_ordering_info(h, 0, 0)
+    bwd = binding.lfmmi_graph_ordering_info(h, 0, 1)
+    h.close()
+    assert info["rec_waves"] == waves and max(fwd["max_wave_slots"], bwd["max_wave_slots"]) == slots
+    assert info["emission_by_state"] == 1 and fwd["register_slots"] == 48
+    parity(g, [6, 1, 0, 2, 3, 4, 5, 23], 23)
