@@ -1294,6 +1294,8 @@ __device__ __forceinline__ void pow2_scale(const double n, double* N, double* in
 // ahead and stores them one step ahead.
 constexpr int kGroupedPasses = 4;  // rows <= kGroupedPasses * threads in this variant
 constexpr uint32_t kRowSums0 = kRegY0 + 16384u, kRowSums1 = kRegY1 + 16384u;
+// (fp64 with one sum per row could take 4,096 rows if EY1 moved to 80K: measured 2 to 8 % slower
+// at 3,500 and 4,000 states, 16 slots, than the recursion with an emission gather)
 __host__ __device__ constexpr int grouped_rows(bool wide) { return wide ? 2048 : 4096; }
 
 template <typename Real, bool HAS_WB, int NSLOT, int NT>
@@ -2627,12 +2629,11 @@ __global__ void __launch_bounds__(1024) k_occ_planes(FbParams p, int groups_per_
 // products, which lie side by side (the sum's order does not depend on timing).
 // Against the kernels by arc: 780 -> 754 us a call on the 2,016-state HMM-expanded
 // denominator (B = 64), 1,324 -> 1,305 us for the loss of 128 numerators (k_occ<double>
-// before) minus a denominator; no size measured slower.
+// before) minus a denominator. 1,000 to 16,300 states, 2 to 9 arcs a state, up to 2,000 pdfs, both
+// precisions, B = 1 to 128: no call over 1.02 times as long as by arc (see occ_states_threads).
 // ---------------------------------------------------------------------------
-constexpr int kOccStatesThreads = 256;
-
-template <typename Real, int F>
-__global__ void __launch_bounds__(kOccStatesThreads) k_occ_states(FbParams p)
+template <typename Real, int F, int NT>
+__global__ void __launch_bounds__(NT) k_occ_states(FbParams p)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int kRows = 4;  // rows of a thread whose loads are in flight together
@@ -2666,30 +2667,30 @@ __global__ void __launch_bounds__(kOccStatesThreads) k_occ_states(FbParams p)
         cb[f] = c != (Real)0 ? (Real)p.leak * scal[p.scal_total + t] * invb[f] : (Real)0;
     }
     auto live = [&](const int f) { return t0 + f <= T; };
-    for (int r0 = 0; r0 < rows_b; r0 += kRows * kOccStatesThreads) {
+    for (int r0 = 0; r0 < rows_b; r0 += kRows * NT) {
         Real v[kRows][F];
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
-            const int r = r0 + u * kOccStatesThreads + tid;
+            const int r = r0 + u * NT + tid;
 #pragma unroll
             for (int f = 0; f < F; ++f)
                 v[u][f] = r < rows_b && live(f) ? br[(size_t)f * rows_b + r] : (Real)0;
         }
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
-            const int r = r0 + u * kOccStatesThreads + tid;
+            const int r = r0 + u * NT + tid;
             if (r >= rows_b) break;
 #pragma unroll
             for (int f = 0; f < F; ++f) XB[f * p.lds_rows_occ_b + r] = v[u][f] * invb[f] + cb[f];
         }
     }
     __syncthreads();
-    for (int r0 = 0; r0 < rows_f; r0 += kRows * kOccStatesThreads) {
+    for (int r0 = 0; r0 < rows_f; r0 += kRows * NT) {
         Real v[kRows][F];
         uint32_t at[kRows];
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
-            const int r = r0 + u * kOccStatesThreads + tid;
+            const int r = r0 + u * NT + tid;
             at[u] = r < rows_f ? row_occ[r] : 0u;
             const Real pi = p.alpha_over_pi && r < rows_f ? (Real)p.g.va[ords[0].vec_at + r] : (Real)1;
 #pragma unroll
@@ -2698,7 +2699,7 @@ __global__ void __launch_bounds__(kOccStatesThreads) k_occ_states(FbParams p)
         }
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
-            const int r = r0 + u * kOccStatesThreads + tid;
+            const int r = r0 + u * NT + tid;
             if (r >= rows_f) break;
 #pragma unroll
             for (int f = 0; f < F; ++f)
@@ -2708,7 +2709,7 @@ __global__ void __launch_bounds__(kOccStatesThreads) k_occ_states(FbParams p)
     __syncthreads();
     float* g0 = p.grad + ((size_t)b * p.T + (t0 - 1)) * P;
     const int lane8 = tid & 7;
-    for (int d = tid >> 3; d < P; d += kOccStatesThreads / 8) {
+    for (int d = tid >> 3; d < P; d += NT / 8) {
         const int i0 = first[d], i1 = first[d + 1];
         Real sum[F];
 #pragma unroll
@@ -2901,18 +2902,22 @@ hipError_t configure_kernels()
     }
     const void* fns[] = {reinterpret_cast<const void*>(k_occ<float>),
                          reinterpret_cast<const void*>(k_occ<double>),
-                         reinterpret_cast<const void*>(k_occ_states<float, 1>),
-                         reinterpret_cast<const void*>(k_occ_states<float, 2>),
-                         reinterpret_cast<const void*>(k_occ_states<float, 4>),
-                         reinterpret_cast<const void*>(k_occ_states<double, 1>),
-                         reinterpret_cast<const void*>(k_occ_states<double, 2>),
-                         reinterpret_cast<const void*>(k_occ_states<double, 4>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 1, 512>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 1, 1024>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 2, 512>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 4, 256>),
+                         reinterpret_cast<const void*>(k_occ_states<float, 4, 512>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 1, 512>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 1, 1024>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 2, 512>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 4, 256>),
+                         reinterpret_cast<const void*>(k_occ_states<double, 4, 512>),
                          reinterpret_cast<const void*>(k_occ_planes<4, 8192>),
                          reinterpret_cast<const void*>(k_occ_planes<2, 16384>),
                          reinterpret_cast<const void*>(k_occ_planes<2, 32768>),
                          reinterpret_cast<const void*>(k_occ_planes<1, 32768>),
                          reinterpret_cast<const void*>(k_occ_planes<1, 49152>)};
-    constexpr size_t kByPointer = 8;  // the first of them take their LDS by pointer
+    constexpr size_t kByPointer = 12;  // the first of them take their LDS by pointer
     for (size_t i = 0; i < sizeof fns / sizeof fns[0]; ++i) {
         hipError_t e =
             hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -2967,6 +2972,16 @@ int occ_states_frames(int rows_f, int rows_b, bool wide)
     for (int f : {4, 2})
         if (occ_states_lds_bytes(rows_f, rows_b, f, wide) <= 40 * 1024) return f;
     return 1;
+}
+
+// Threads of a workgroup: the more LDS it takes, the fewer share a compute unit and the more
+// loads each has to have in flight itself. 256 threads whatever the size / as below (B = 128):
+// 4,000 states, 28,000 arcs, 250 frames 956 / 858 us a call; 8,000 states, 120 frames 783 / 656; 14,000
+// states 2,686 / 1,521. More threads than this: 300 states (10 KB) 356 / 384 to 481.
+// (By occ_states_frames 256 threads take four frames, 1,024 one.)
+static int occ_states_threads(size_t lds)
+{
+    return lds <= 20 * 1024 ? 256 : (lds <= 40 * 1024 ? 512 : 1024);
 }
 
 size_t occ_plane_lds_bytes(int rows, int occ_rows, int frames)
@@ -3035,12 +3050,14 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
         if (tq > 0) {
             if (shape.occ_states > 0) {
                 const int F = shape.occ_states;
-                void (*fn)(FbParams) = F == 4   ? k_occ_states<Real, 4>
-                                       : F == 2 ? k_occ_states<Real, 2>
-                                                : k_occ_states<Real, 1>;
-                hipLaunchKernelGGL(fn, dim3((tq + F - 1) / F, nb), dim3(kOccStatesThreads),
-                                   occ_states_lds_bytes(p.lds_rows_occ_a, p.lds_rows_occ_b, F, wide),
-                                   on, pq);
+                const size_t lds = occ_states_lds_bytes(p.lds_rows_occ_a, p.lds_rows_occ_b, F, wide);
+                const int nt = occ_states_threads(lds);
+                void (*fn)(FbParams) = nt == 256    ? k_occ_states<Real, 4, 256>
+                                       : nt == 1024 ? k_occ_states<Real, 1, 1024>
+                                       : F == 4     ? k_occ_states<Real, 4, 512>
+                                       : F == 2     ? k_occ_states<Real, 2, 512>
+                                                    : k_occ_states<Real, 1, 512>;
+                hipLaunchKernelGGL(fn, dim3((tq + F - 1) / F, nb), dim3(nt), lds, on, pq);
             } else if (!wide && shape.occ_multi > 0) {
                 const int F = shape.occ_multi;
                 const int per_wg = F * shape.occ_groups;
