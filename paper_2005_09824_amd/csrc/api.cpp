@@ -934,11 +934,22 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
         // The estimate of a step follows the kernels' times from 20 to 5,000 states. 1 / 4
         // buckets, B = 32: 20 states, 200 frames 158 / 168 us; 600 states, 120 frames 130 / 154;
         // 2,000 states, 120 frames 184 / 201, 400 frames 535 / 507; 5,000 states, 60 frames
-        // 266 / 273, 120 frames 472 / 445. LFMMI_BUCKETS set: as many as it says.
+        // 266 / 273, 120 frames 472 / 445. Small graphs reach 330 frames within that estimate,
+        // and from about 230 on several buckets win where there is much to hide: occupancies by
+        // arc of many sequences, or of fewer with many pdfs.
+        // 20 states, 84 pdfs, 280 frames: B = 32 217 / 214, 48 230 / 224, 128 308 / 287; 200 frames, B
+        // = 128 240 / 249. 1,000 pdfs, 280 frames: B = 8 262 / 288, 16 306 / 280, 32 382 / 348. By
+        // state one bucket stays the better one: 300 states, 1,000 pdfs, B = 64 288 / 293, 128
+        // 384 / 427. LFMMI_BUCKETS set: as many as it says.
         double longest_us = 0.0;
-        for (int32_t b = 0; b < B; ++b)
+        int32_t longest = 0;
+        for (int32_t b = 0; b < B; ++b) {
+            longest = std::max(longest, lengths[b]);
             longest_us = std::max(longest_us, lengths[b] * (0.6 + 3e-5 * h->packed[seqs[b].graph].num_arcs));
-        int want = std::min(env_int("LFMMI_BUCKETS", longest_us < 200.0 ? 1 : (int)Buckets::kMax),
+        }
+        const bool much_to_hide = !h->occ_states && longest >= 230 && B >= (P > 512 ? 16 : 48);
+        int want = std::min(env_int("LFMMI_BUCKETS",
+                                    longest_us < 200.0 && !much_to_hide ? 1 : (int)Buckets::kMax),
                             buckets_most);
         want = std::max(1, std::min(want, B / 2));
         if (T == 0) want = 1;
