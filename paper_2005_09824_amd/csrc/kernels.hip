@@ -807,8 +807,11 @@ struct RecRegs {
             const float t0 = wr[i] * e0;
             const float t1 = wr[i + 1] * e1;
             if constexpr (ROWS) {
+                // (one arc after the other: mixed, the 36-slot variant spills a register pair)
                 add_arc(wr[i], e0, x0, acc1, acc2);
+                asm volatile("" : "+v"(acc1), "+v"(acc2));
                 add_arc(wr[i + 1], e1, x1, acc1, acc2);
+                asm volatile("" : "+v"(acc1), "+v"(acc2));
             } else if constexpr (sizeof(Real) == 4) {
                 acc1 = fmaf(t0, x0, acc1);
                 acc2 = HAS_WB ? fmaf(wbr[HAS_WB ? i : 0], e0, acc2) : acc2 + t0;
