@@ -935,19 +935,24 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
         // buckets, B = 32: 20 states, 200 frames 158 / 168 us; 600 states, 120 frames 130 / 154;
         // 2,000 states, 120 frames 184 / 201, 400 frames 535 / 507; 5,000 states, 60 frames
         // 266 / 273, 120 frames 472 / 445. Small graphs reach 330 frames within that estimate,
-        // and from about 230 on several buckets win where there is much to hide: occupancies by
-        // arc of many sequences, or of fewer with many pdfs.
-        // 20 states, 84 pdfs, 280 frames: B = 32 217 / 214, 48 230 / 224, 128 308 / 287; 200 frames, B
-        // = 128 240 / 249. 1,000 pdfs, 280 frames: B = 8 262 / 288, 16 306 / 280, 32 382 / 348. By
-        // state one bucket stays the better one: 300 states, 1,000 pdfs, B = 64 288 / 293, 128
-        // 384 / 427. LFMMI_BUCKETS set: as many as it says.
-        double longest_us = 0.0;
+        // and from about 240 on several buckets win where there is much to hide: occupancies by
+        // arc of many sequences, or of fewer with many pdfs, while the longest are well above the
+        // mean (lengths from T / 3 to T: 0.67 T). 20 states, 84 pdfs, T = 280: B = 24 208 / 214,
+        // 64 248 / 230, 128 311 / 297; T = 230, B = 128 267 / 264. 1,000 pdfs, T = 280: B = 8 262 / 288,
+        // 16 306 / 280, 64 517 / 485. Mean length 0.75 T: 84 pdfs 324 / 329 (B = 128, T = 280), 2,000
+        // pdfs 534 / 500 (600 states, B = 48); 0.8 T: 337 / 356 and 551 / 534; all of length T: 372 /
+        // 410 and 616 / 660. By state one bucket stays the better one: 300 states, 1,000 pdfs, B = 64
+        // 288 / 293, 128 384 / 427. LFMMI_BUCKETS set: as many as it says.
+        double longest_us = 0.0, frames = 0.0;
         int32_t longest = 0;
         for (int32_t b = 0; b < B; ++b) {
+            frames += lengths[b];
             longest = std::max(longest, lengths[b]);
             longest_us = std::max(longest_us, lengths[b] * (0.6 + 3e-5 * h->packed[seqs[b].graph].num_arcs));
         }
-        const bool much_to_hide = !h->occ_states && longest >= 230 && B >= (P > 512 ? 16 : 48);
+        const bool many_pdfs = P > 512;
+        const bool much_to_hide = !h->occ_states && longest >= 240 && B >= (many_pdfs ? 16 : 48) &&
+                                  frames <= (many_pdfs ? 0.78 : 0.7) * B * longest;
         int want = std::min(env_int("LFMMI_BUCKETS",
                                     longest_us < 200.0 && !much_to_hide ? 1 : (int)Buckets::kMax),
                             buckets_most);

@@ -124,12 +124,15 @@ def test_bucket_counts_give_the_same_bits_eager_and_replayed(T, monkeypatch):
     den.close()
 
 
-# how many buckets a call takes where its longest recursion is short
-@pytest.mark.parametrize("by_state,B,T,P,buckets", [
-    (False, 47, 240, 20, 1), (False, 48, 229, 20, 1), (False, 48, 240, 20, 4), (True, 48, 240, 20, 1),
-    (False, 15, 240, 600, 1), (False, 16, 240, 600, 4), (True, 128, 240, 600, 1), (True, 12, 400, 20, 4),
+# how many buckets a call takes where its longest recursion is short; `low`: half of the
+# sequences have that share of T frames
+@pytest.mark.parametrize("by_state,B,T,P,low,buckets", [
+    (False, 47, 240, 20, 0.3, 1), (False, 48, 239, 20, 0.3, 1), (False, 48, 240, 20, 0.3, 4),
+    (False, 48, 240, 20, 0.45, 1), (True, 48, 240, 20, 0.3, 1),
+    (False, 15, 240, 600, 0.3, 1), (False, 16, 240, 600, 0.3, 4), (False, 16, 240, 600, 0.55, 4),
+    (False, 16, 240, 600, 0.6, 1), (True, 128, 240, 600, 0.3, 1), (True, 12, 400, 20, 1.0, 4),
 ])
-def test_bucket_count_of_short_calls(by_state, B, T, P, buckets):
+def test_bucket_count_of_short_calls(by_state, B, T, P, low, buckets):
     import torch
     rng = np.random.default_rng(B)
     g = workloads.random_den_graph(rng, 20, 2, P, 0.5)
@@ -137,7 +140,8 @@ def test_bucket_count_of_short_calls(by_state, B, T, P, buckets):
         g["pdf"] = rng.integers(0, P, 20).astype(np.int32)[g["dst"]]
     den = binding.lfmmi_graph_create(g)
     binding.lfmmi_profile_enable(den, True)
-    x = torch.zeros((B, T, P), device="cuda")
-    binding.lfmmi_forward_backward(den, x, np.full(B, T, np.int32), 1e-5)
+    lens = np.full(B, T, np.int32)
+    lens[(B + 1) // 2:] = int(low * T)
+    binding.lfmmi_forward_backward(den, torch.zeros((B, T, P), device="cuda"), lens, 1e-5)
     assert binding.lfmmi_profile_read(den)["launches"] == buckets
     den.close()
