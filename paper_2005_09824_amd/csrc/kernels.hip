@@ -411,12 +411,14 @@ __device__ __forceinline__ double lane_value(double v, int l)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// v with lane L holding `value` (wave-uniform) instead.
+// v with lane L holding `value` (wave-uniform) instead. By the compiler's own intrinsic, not by
+// inline assembly: a lane write that reads a scalar register two instructions or fewer behind
+// the v_readlane that wrote it needs a wait, which the compiler puts in for its own only.
+__device__ int writelane_i32(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 template <int L>
-__device__ __forceinline__ int write_lane(int v, const int value)
+__device__ __forceinline__ int write_lane(const int v, const int value)
 {
-    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(value), "n"(L));
-    return v;
+    return writelane_i32(value, L, v);
 }
 
 // Sum over the 64 lanes, returned as a wave-uniform value.
