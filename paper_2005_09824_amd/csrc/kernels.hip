@@ -2911,18 +2911,16 @@ hipError_t configure_kernels()
                          reinterpret_cast<const void*>(k_occ_states<float, 1, 1024>),
                          reinterpret_cast<const void*>(k_occ_states<float, 2, 512>),
                          reinterpret_cast<const void*>(k_occ_states<float, 4, 256>),
-                         reinterpret_cast<const void*>(k_occ_states<float, 4, 512>),
                          reinterpret_cast<const void*>(k_occ_states<double, 1, 512>),
                          reinterpret_cast<const void*>(k_occ_states<double, 1, 1024>),
                          reinterpret_cast<const void*>(k_occ_states<double, 2, 512>),
                          reinterpret_cast<const void*>(k_occ_states<double, 4, 256>),
-                         reinterpret_cast<const void*>(k_occ_states<double, 4, 512>),
                          reinterpret_cast<const void*>(k_occ_planes<4, 8192>),
                          reinterpret_cast<const void*>(k_occ_planes<2, 16384>),
                          reinterpret_cast<const void*>(k_occ_planes<2, 32768>),
                          reinterpret_cast<const void*>(k_occ_planes<1, 32768>),
                          reinterpret_cast<const void*>(k_occ_planes<1, 49152>)};
-    constexpr size_t kByPointer = 12;  // the first of them take their LDS by pointer
+    constexpr size_t kByPointer = 10;  // the first of them take their LDS by pointer
     for (size_t i = 0; i < sizeof fns / sizeof fns[0]; ++i) {
         hipError_t e =
             hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -2981,12 +2979,13 @@ int occ_states_frames(int rows_f, int rows_b, bool wide)
 
 // Threads of a workgroup: the more LDS it takes, the fewer share a compute unit and the more
 // loads each has to have in flight itself. 256 threads whatever the size / as below (B = 128):
-// 4,000 states, 28,000 arcs, 250 frames 956 / 858 us a call; 8,000 states, 120 frames 783 / 656; 14,000
-// states 2,686 / 1,521. More threads than this: 300 states (10 KB) 356 / 384 to 481.
-// (By occ_states_frames 256 threads take four frames, 1,024 one.)
-static int occ_states_threads(size_t lds)
+// 2,016 states (two frames, 32 KB) 356 / 341 us a call; 4,000 states, 28,000 arcs, 250 frames 956 /
+// 858; 8,000 states, 120 frames 783 / 656; 14,000 states 2,686 / 1,521. More threads where four frames
+// share a workgroup: 300 states (10 KB) 356 / 384 to 481; 128 numerators of 400 states in fp64
+// (29 KB) 1,005 / 1,023.
+static int occ_states_threads(int frames, size_t lds)
 {
-    return lds <= 20 * 1024 ? 256 : (lds <= 40 * 1024 ? 512 : 1024);
+    return frames == 4 ? 256 : (lds <= 40 * 1024 ? 512 : 1024);
 }
 
 size_t occ_plane_lds_bytes(int rows, int occ_rows, int frames)
@@ -3056,11 +3055,10 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
             if (shape.occ_states > 0) {
                 const int F = shape.occ_states;
                 const size_t lds = occ_states_lds_bytes(p.lds_rows_occ_a, p.lds_rows_occ_b, F, wide);
-                const int nt = occ_states_threads(lds);
-                void (*fn)(FbParams) = nt == 256    ? k_occ_states<Real, 4, 256>
-                                       : nt == 1024 ? k_occ_states<Real, 1, 1024>
-                                       : F == 4     ? k_occ_states<Real, 4, 512>
+                const int nt = occ_states_threads(F, lds);
+                void (*fn)(FbParams) = F == 4       ? k_occ_states<Real, 4, 256>
                                        : F == 2     ? k_occ_states<Real, 2, 512>
+                                       : nt == 1024 ? k_occ_states<Real, 1, 1024>
                                                     : k_occ_states<Real, 1, 512>;
                 hipLaunchKernelGGL(fn, dim3((tq + F - 1) / F, nb), dim3(nt), lds, on, pq);
             } else if (!wide && shape.occ_multi > 0) {
