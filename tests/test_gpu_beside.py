@@ -11,13 +11,17 @@ from paper_2005_09824_amd import binding, workloads
 pytestmark = pytest.mark.gpu
 
 
+def _den_graph(pdf_by_state, seed):
+    rng = np.random.default_rng(seed)
+    if pdf_by_state:
+        return workloads.hmm_den_graph(rng, 14, 6, 0.5)
+    return workloads.random_den_graph(rng, 700, 5, 28, 0.5)
+
+
 def _setup(B, pdf_by_state, seed, empty=False):
     import torch
     rng = np.random.default_rng(seed)
-    if pdf_by_state:
-        den = workloads.hmm_den_graph(rng, 14, 6, 0.5)
-    else:
-        den = workloads.random_den_graph(rng, 700, 5, 28, 0.5)
+    den = _den_graph(pdf_by_state, seed)
     P = den["num_pdfs"]
     num = [workloads.phone_string_num_graph(rng.integers(1, P // 2, size=int(n)), P)
            for n in rng.integers(4, 14, size=B)]
@@ -36,11 +40,25 @@ def _in_turn(num, den, x, lens):
     return objf, grad, st
 
 
+# A denominator whose numerators run at the same time takes 8 bytes a sequence more for what its
+# recursion leaves aside: whether they did shows in the workspace of a fresh handle.
+def _den_workspace(num, den_graph, x, lens, out, monkeypatch, beside):
+    import torch
+    monkeypatch.setenv("LFMMI_BESIDE", beside)
+    den = binding.lfmmi_graph_create(den_graph)
+    binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)
+    torch.cuda.synchronize()
+    n = binding.lfmmi_graph_info(den)["workspace_bytes"]
+    den.close()
+    monkeypatch.delenv("LFMMI_BESIDE")
+    return n
+
+
 # 64 sequences: the largest batch whose 4 B workgroups fit 256 compute units; 65: one more
 @pytest.mark.parametrize("B,pdf_by_state,empty", [(1, False, False), (1, True, False), (9, True, True),
                                                   (7, False, False), (8, True, False), (64, True, False),
                                                   (64, False, False), (65, True, False)])
-def test_same_bits_as_the_two_passes_in_turn(B, pdf_by_state, empty):
+def test_same_bits_as_the_two_passes_in_turn(B, pdf_by_state, empty, monkeypatch):
     import torch
     num, den, x, lens = _setup(B, pdf_by_state, 100 + B, empty)
     want = _in_turn(num, den, x, lens)
@@ -57,6 +75,49 @@ def test_same_bits_as_the_two_passes_in_turn(B, pdf_by_state, empty):
         torch.cuda.synchronize()
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+    g = _den_graph(pdf_by_state, 100 + B)
+    more = [_den_workspace(num, g, x, lens, out, monkeypatch, v) for v in "01"]
+    assert (more[1] > more[0]) == (B <= 64 and not empty)
+    num.close()
+    den.close()
+
+
+# A NaN logit, an utterance too short for its numerator, both and neither, with the status asked
+# for and not: what the denominator's pass leaves aside meets what the numerators' pass wrote,
+# in every kernel that adds it: by state, by arc with planes, one frame at a time, fp64
+@pytest.mark.parametrize("kind", ["by_state", "by_arc", "frame_at_a_time", "fp64"])
+def test_flagged_sequences_side_by_side(kind, monkeypatch):
+    import torch
+    if kind == "frame_at_a_time":
+        monkeypatch.setenv("LFMMI_OCC_MULTI", "0")
+    num, den, x, lens = _setup(10, kind == "by_state", 77)
+    if kind == "fp64":
+        g = _den_graph(False, 77)
+        g["final_prob"][::3] = 0
+        den.close()
+        den = binding.lfmmi_graph_create(g)
+        assert binding.lfmmi_graph_info(den)["fp64"] == 1
+    lens[[2, 6]] = 2  # two frames: no path through four phones or more
+    x[3, 5, 4] = float("nan")
+    x[6, 1, 0] = float("nan")
+    want = _in_turn(num, den, x, lens)
+    torch.cuda.synchronize()
+    st = want[2].cpu().numpy()
+    assert st[2] & 1 and st[3] & 2 and st[6] & 2 and np.all(np.delete(st, [2, 3, 6]) == 0)
+    for status in (torch.full_like(want[2], 5), None):
+        out = [torch.full_like(want[0], 9.0), torch.full_like(want[1], 9.0), status]
+        if status is None:  # (the wrapper would make one)
+            import ctypes
+            assert binding.load_library().lfmmi_loss(
+                num.handle, den.handle, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(lens.ctypes.data),
+                *x.shape, 1e-5, ctypes.c_void_p(out[0].data_ptr()), ctypes.c_void_p(out[1].data_ptr()),
+                None, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        else:
+            binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)
+        torch.cuda.synchronize()
+        for a, b in zip(out, want):
+            if a is not None:
+                assert np.array_equal(a.cpu().numpy(), b.cpu().numpy(), equal_nan=a.dtype.is_floating_point)
     num.close()
     den.close()
 

@@ -440,11 +440,12 @@ def test_config5_full_size_all_sequences():
     den.close(); num.close()
 
 
-def test_a_call_with_its_four_buckets_replays_from_a_hip_graph():
+def test_a_call_with_its_four_buckets_replays_from_a_hip_graph(monkeypatch):
     # after one eager call (workspace allocated, descriptors staged) a call enqueues kernels,
     # event records and event waits only: captured on a side stream, with the buckets' streams
     # joining the capture through the fork event, it replays with the same bits, also with
     # eager calls and synchronisations between the replays
+    monkeypatch.setenv("LFMMI_BUCKETS", "4")  # (a call this short takes one by itself)
     torch = _torch()
     wl = workloads.make_workload(2, scale={"S": 600, "B": 12, "Tlo": 20, "Thi": 90})
     h = binding.lfmmi_graph_create(wl["den"])
