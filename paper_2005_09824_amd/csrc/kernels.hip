@@ -2812,7 +2812,7 @@ const RecVariant kRecVariants[] = {
     LFMMI_REC_GROUPED(float, 0, 48, 0, 512),
     LFMMI_REC_GROUPED(float, 0, 16, 1, 1024), LFMMI_REC_GROUPED(float, 0, 24, 1, 1024),
     LFMMI_REC_GROUPED(float, 0, 32, 1, 1024), LFMMI_REC_GROUPED(float, 0, 36, 1, 1024),
-    LFMMI_REC_GROUPED(double, 1, 8, 1, 1024), LFMMI_REC_GROUPED(double, 1, 16, 1, 1024),
+    LFMMI_REC_GROUPED(double, 1, 16, 1, 1024),
     LFMMI_REC_GROUPED(double, 1, 16, 0, 1024),
     // ... one short slice per wave
     LFMMI_REC_SHORT(float, 0, 4, 512), LFMMI_REC_SHORT(float, 0, 8, 512),
