@@ -186,7 +186,9 @@ lfmmi_status lfmmi_forward_backward_static(const lfmmi_graph *graph, const float
  * bit). Where the recursion workgroups of both passes fit the chip together (4 B
  * at most its compute units: B <= 64), no sequence is empty and the batch has 8
  * sequences or one of 256 frames, the passes run at the same time, the numerators'
- * on a stream of the library's that hip_stream waits for (LFMMI_BESIDE=0: never).
+ * on a stream of the library's that hip_stream waits for (LFMMI_BESIDE=0: never; nor
+ * while either handle collects events, see lfmmi_profile_enable: what they time is the
+ * passes in turn).
  * Otherwise the numerators' pass is enqueued first, then the denominator's, both on
  * hip_stream, and the emission values exp(logit - row maximum) are computed once,
  * by the numerators' pass; the denominator's reads them from that handle's
@@ -196,8 +198,9 @@ lfmmi_status lfmmi_forward_backward_static(const lfmmi_graph *graph, const float
  * (With more sequences, side by side was measured 13 to 24 % slower on the
  * 128-sequence workload: the numerators' workgroups then take compute units from
  * the denominator's longest sequences, whose recursion decides when the call ends,
- * and HIP streams of one priority give no say in that.) num: a batch handle with B graphs (or one graph
- * for all); den: usually one shared graph; the two must be different handles.
+ * and HIP streams of one priority give no say in that.)
+ * num: a batch handle with B graphs (or one graph for all); den: usually one shared
+ * graph; the two must be different handles.
  * Arguments and errors otherwise as lfmmi_forward_backward.
  */
 lfmmi_status lfmmi_loss(const lfmmi_graph *num, const lfmmi_graph *den, const float *logits,
@@ -218,7 +221,8 @@ enum { LFMMI_ORD_FWD = 0, LFMMI_ORD_BWD = 1, LFMMI_ORD_OCC = 2 };
  * carries the pdf-id of the state it enters - graphs expanded from HMMs whose
  * states emit, Section 4.2 - and the recursion runs without an emission gather per
  * arc: alpha multiplies a row by its emission once, beta folds the emission into
- * the stored vector), [7] workspace bytes held. */
+ * the stored vector; not set for graphs of one short slice a wave, per-utterance
+ * numerators, whose straight-line variant does the same), [7] workspace bytes held. */
 lfmmi_status lfmmi_graph_info(const lfmmi_graph *graph, int64_t info[8]);
 
 /* Packed ordering `ord` of graph `g`: info[0] rows, [1] slices (64 rows each),
@@ -271,7 +275,8 @@ lfmmi_status lfmmi_graph_ordering_copy(const lfmmi_graph *graph, int32_t g, int3
  * workgroup of a sequence computes); [2] 0; [3] occupancy + gradient (0 at
  * level 2) - with the number of calls in *calls and of launches of each kernel
  * in *launches (either may be NULL), then forgets them. Launches of one call
- * overlap: the means do not add up to the time of a call. */
+ * overlap: the means do not add up to the time of a call. While events are collected
+ * lfmmi_loss runs its two passes in turn (results are the same bits). */
 lfmmi_status lfmmi_profile_enable(lfmmi_graph *graph, int enable);
 lfmmi_status lfmmi_profile_read(lfmmi_graph *graph, float ms[4], int32_t *calls,
                                 int32_t *launches);

@@ -1025,11 +1025,16 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
 // Whether the two passes of a full-loss call run at the same time (see lfmmi_loss): both
 // passes' recursion workgroups fit the chip, every sequence has frames (its occupancy kernel
 // does the adding), no events are being collected, which would overlap, and the call is long
-// or its batch large enough. 8 sequences of 50 frames: 84 to 119 us a call in turn, 65 to 100
-// beside each other; 64 of 150 frames: 223 to 395 and 175 to 323. Smaller batches of short
-// sequences are bound by the host, which pays 30 to 70 us more for the events of the second
-// stream (training step, B = 2, 45 frames: 153 us in turn, 226 beside), and need longer passes
-// to win that back (B = 2, 280 frames: 290 to 446 us in turn, 201 to 353 beside).
+// or its batch large enough. In turn / beside each other, calls that follow one another: 8
+// sequences of up to 60 frames 83 to 128 / 67 to 108 us, 64 of up to 150 frames 182 to 428 / 137
+// to 371 (20 to 2,000 states), only below 40 frames on a few hundred states 60 / 76. What it costs
+// is host time, 25 / 64 us a call, in events and waits of the second stream. A program whose
+// host runs ahead of its device does not see that; one that waits for the host does: training
+// steps with no model around them, 20 states, B = 8, up to 59 frames 123 / 218, 120 frames 163 /
+// 221, 176 frames 214 / 222, 218 frames 251 / 222; 2,016 states, B = 32, up to 57 frames 170 / 165, 98
+// frames 228 / 202. Smaller batches of short sequences have less to gain and need longer passes to
+// win that back (training step, B = 2, 45 frames: 153 / 226; calls, B = 2, 280 frames: 290 to 446 /
+// 201 to 353).
 bool beside_each_other(const lfmmi_graph* num, const lfmmi_graph* den, const int32_t* lengths,
                        int32_t B, int32_t T)
 {
