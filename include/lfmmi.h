@@ -188,7 +188,7 @@ lfmmi_status lfmmi_forward_backward_static(const lfmmi_graph *graph, const float
  * sequences or one of 256 frames, the passes run at the same time, the numerators'
  * on a stream of the library's that hip_stream waits for (LFMMI_BESIDE=0: never; nor
  * while either handle collects events, see lfmmi_profile_enable: what they time is the
- * passes in turn).
+ * passes in turn; nor with fewer than 4 sequences under capture).
  * Otherwise the numerators' pass is enqueued first, then the denominator's, both on
  * hip_stream, and the emission values exp(logit - row maximum) are computed once,
  * by the numerators' pass; the denominator's reads them from that handle's

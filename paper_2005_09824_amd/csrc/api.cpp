@@ -1035,8 +1035,10 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
 // frames 228 / 202. Smaller batches of short sequences have less to gain and need longer passes to
 // win that back (training step, B = 2, 45 frames: 153 / 226; calls, B = 2, 280 frames: 290 to 446 /
 // 201 to 353).
+// A call of fewer than four sequences uses no stream of the library's by itself and stays so
+// under capture: other threads' eager calls use those streams at the same time.
 bool beside_each_other(const lfmmi_graph* num, const lfmmi_graph* den, const int32_t* lengths,
-                       int32_t B, int32_t T)
+                       int32_t B, int32_t T, hipStream_t stream)
 {
     if (env_int("LFMMI_BESIDE", 1) == 0 || env_int("LFMMI_BUCKETS", Buckets::kMax) < Buckets::kMax)
         return false;
@@ -1048,7 +1050,10 @@ bool beside_each_other(const lfmmi_graph* num, const lfmmi_graph* den, const int
         if (lengths[b] < 1) return false;
         longest = std::max(longest, lengths[b]);
     }
-    return B >= 2 * Buckets::kMax || longest >= 256;
+    if (B < 2 * Buckets::kMax && longest < 256) return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (B < 4 && stream && hipStreamIsCapturing(stream, &capture) != hipSuccess) return false;
+    return capture == hipStreamCaptureStatusNone;
 }
 
 }  // namespace
@@ -1209,7 +1214,7 @@ lfmmi_status lfmmi_loss(const lfmmi_graph* num, const lfmmi_graph* den, const fl
     // Numerators of 20 to 120 phones beside an HMM-expanded denominator of 2,016 states, B = 64:
     // training step 1,059 -> 798 us; up to 225 frames, 2,000 states: 574 -> 432 us at B = 64,
     // 467 -> 336 at B = 32, 445 -> 316 at B = 8.
-    if (beside_each_other(hn, hd, lengths, B, T)) {
+    if (beside_each_other(hn, hd, lengths, B, T, static_cast<hipStream_t>(hip_stream))) {
         st = check_call(hn, logits, lengths, B, T, P, leak, 1.f, objf, grad);
         if (st == LFMMI_OK) st = check_call(hd, logits, lengths, B, T, P, leak, -1.f, objf, grad);
         if (st != LFMMI_OK) return st;

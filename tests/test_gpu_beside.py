@@ -150,6 +150,56 @@ def test_replays_from_a_hip_graph():
     den.close()
 
 
+# Fewer than four sequences need no stream of the library's under capture: while one thread
+# captures such a call, another one's eager call runs on those streams
+def test_a_captured_call_of_few_sequences_stays_on_its_stream():
+    import threading
+    import torch
+    num, den, x, lens = _setup(2, True, 6)
+    eager = binding.lfmmi_graph_create(workloads.random_den_graph(np.random.default_rng(3), 500, 5, 40, 0.5))
+    ex = torch.zeros((12, 400, 40), device="cuda")
+    want_e = binding.lfmmi_forward_backward(eager, ex, np.full(12, 400, np.int32), 1e-5)
+    want = _in_turn(num, den, x, lens)
+    out = tuple(torch.empty_like(t) for t in want)
+    out_e = tuple(torch.empty_like(t) for t in want_e)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    errors = []
+
+    def eager_call():
+        try:
+            with torch.cuda.stream(other):
+                binding.lfmmi_forward_backward(eager, ex, np.full(12, 400, np.int32), 1e-5, 1.0, False, *out_e)
+        except Exception as e:  # reported below, on the test's own thread
+            errors.append(e)
+
+    with torch.cuda.stream(side):
+        binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)
+        torch.cuda.synchronize()
+        graph.capture_begin(capture_error_mode="thread_local")
+        try:
+            binding.lfmmi_loss(num, den, x, lens, 1e-5, *out)
+            t = threading.Thread(target=eager_call)
+            t.start()
+            t.join()
+        finally:
+            graph.capture_end()
+    assert not errors
+    for _ in range(3):
+        for t in out:
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out + out_e, want + want_e):
+            assert torch.equal(a, b)
+    del graph
+    for h in (num, den, eager):
+        h.close()
+
+
 # 90 frames: one bucket by default; 330: four (500 states, 3,000 arcs); both against every count
 @pytest.mark.parametrize("T", [90, 330])
 def test_bucket_counts_give_the_same_bits_eager_and_replayed(T, monkeypatch):
