@@ -563,8 +563,8 @@ __host__ __device__ constexpr int stage_passes(bool yrep, int nt)
 // s = sum pi u takes a row's pi from its closing slot, and s is also what a step is scaled by.
 // Two registers and a multiply-add less per slot than 1, so the hybrid has room for it: 5,000
 // states, 50,000 arcs, B = 32, 5.88 -> 1.82 ms a call (1 had to stream every arc); 1,237
-// states in registers, B = 17: 289 -> 238 us. 1 stays for fp64, for hub slices and for graphs
-// whose scaled weights would leave the normal range of fp32.
+// states in registers, B = 17: 289 -> 238 us. 1 stays for fp64, for hub slices, for graphs that
+// leave the range of fp32 that way and where nothing stays in registers.
 template <typename Real, bool YREP, int LEAK, int NSLOT, int NT, bool HYBRID = false,
           bool BIG = false, bool HUBS = false>
 struct RecRegs {
@@ -1270,10 +1270,11 @@ struct RecRegs {
 //     values, and the next step has both scalars by the time its first row is done.
 // n is kept as the power of two below the sum: any positive scale cancels, and its
 // inverse is then one subtraction of exponents.
-// Bound by the gathers and the issue of a step (16 waves, up to 36 slots each). The launch of
-// the eight longest sequences (500 frames) of an HMM-expanded denominator of 2,016 states whose
-// fullest wave has 36 slots: 617 us; 837 us with the hybrid recursion, which such a graph took
-// before (the variant with two barriers in beta held 32 slots).
+// Bound by the gathers and the issue of a step (16 waves, up to 36 slots each; up to 8 waves, 48
+// slots). The launch of the eight longest sequences (500 frames) of an HMM-expanded denominator
+// of 2,016 states whose fullest wave has 36 slots: 617 us; 837 us with the hybrid recursion, which
+// such a graph took before (the variant with two barriers in beta held 32 slots). 60 states of 40
+// arcs (48 slots, one wave), 500 frames, B = 1: 529 us a call with an emission gather, 394 without.
 // ---------------------------------------------------------------------------
 // N: the largest power of two not above n (0 below the normal range, and nothing beyond 2^126,
 // 2^1022 in fp64); inv: its inverse, without a test for totals that are zero or not finite:
