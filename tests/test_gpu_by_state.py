@@ -113,3 +113,20 @@ def test_recursion_by_state_of_small_dense_graphs(S, k, waves, slots):
     assert info["rec_waves"] == waves and max(fwd["max_wave_slots"], bwd["max_wave_slots"]) == slots
     assert info["emission_by_state"] == 1 and fwd["register_slots"] == 48
     parity(g, [6, 1, 0, 2, 3, 4, 5, 23], 23)
+
+
+# occupancies by state where the recursion has hub slices (63 padding rows each)
+@pytest.mark.parametrize("init,some_final", [("uniform", False), ("varied", False), ("varied", True)])
+def test_occupancies_by_state_with_hub_slices(init, some_final):
+    rng = np.random.default_rng(31)
+    S, P = 900, 60
+    g = by_state_graph(rng, S, 6, P, init, some_final)
+    into, out_of = rng.choice(S, 500, replace=False), rng.choice(S, 350, replace=False)
+    g["src"] = np.concatenate([g["src"], into, np.full(350, 3)]).astype(np.int32)
+    g["dst"] = np.concatenate([g["dst"], np.full(500, 5), out_of]).astype(np.int32)
+    g["logw"] = np.concatenate([g["logw"], np.log(rng.uniform(0.01, 0.2, 850))]).astype(np.float32)
+    g["pdf"] = rng.integers(0, P, S).astype(np.int32)[g["dst"]]
+    h = binding.lfmmi_graph_pack(g)
+    assert all(binding.lfmmi_graph_ordering_info(h, 0, o)["hub_slices"] == 1 for o in (0, 1))
+    h.close()
+    parity(g, [9, 1, 8, 0, 23], 23)

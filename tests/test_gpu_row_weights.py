@@ -149,3 +149,28 @@ def test_graphs_that_keep_their_factors_per_arc(kind):
         x[:, :, :2] += 8
     for leak in (0.0, 1e-5):
         compare(g, x, [x.shape[1]], leak, 1)
+
+
+def test_one_handle_of_graphs_with_equal_and_differing_initial_probabilities():
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(12)
+    P, graphs = 30, []
+    for S, k, varied in ((200, 4, True), (64, 3, False), (1, 0, False), (700, 5, True)):
+        g = workloads.random_den_graph(rng, S, k, P, 0.5)
+        if varied:
+            p = rng.uniform(0.01, 1.0, S) ** 2
+            g["init_prob"] = (p / p.sum()).astype(np.float32)
+        graphs.append(g)
+    lengths = np.array([12, 9, 14, 5], np.int32)
+    x = rng.normal(0, 2, (4, 14, P)).astype(np.float32)
+    for b in range(4):
+        x[b, lengths[b]:] = np.nan
+    h = binding.lfmmi_graph_create_batch(graphs)
+    assert all(binding.lfmmi_graph_ordering_info(h, i, 0)["per_arc_leak"] == 2 for i in range(4))
+    objf, grad, status = binding.lfmmi_forward_backward(h, torch.from_numpy(x).cuda(), lengths, 1e-3)
+    torch.cuda.synchronize()
+    h.close()
+    lz, gamma = oracle.forward_backward_per_utt(graphs, x, lengths, 1e-3)
+    assert np.all(status.cpu().numpy() == 0)
+    assert np.all(np.abs(objf.cpu().numpy() - lz) <= 1e-4 * np.maximum(np.abs(lz), 1.0))
+    assert np.abs(grad.cpu().numpy().astype(np.float64) - gamma).max() <= 1e-4
