@@ -580,6 +580,7 @@ struct RecRegs {
     static constexpr uint32_t kRegYZero = BIG ? 16380u : lfmmi::kRegYZero;  // see rec_zero_word()
     static_assert(lfmmi::kRegPart == 131072u, "both maps end where the partial sums begin");
     static constexpr uint32_t kRB = sizeof(Real);  // bytes of a state value
+    static constexpr bool kOneByOne = ROWS && !HYBRID && NSLOT >= 36;
     // One arc of an fp32 row without a factor of its own. ROWS: emission times value first.
     // The weight may hold a ratio of initial probabilities far below one, which that value
     // makes up for and the emission does not (w * e of a state with pi = 1e-17 whose only arc
@@ -809,11 +810,11 @@ struct RecRegs {
             const float t0 = wr[i] * e0;
             const float t1 = wr[i + 1] * e1;
             if constexpr (ROWS) {
-                // (one arc after the other: mixed, the 36-slot variant spills a register pair)
                 add_arc(wr[i], e0, x0, acc1, acc2);
-                asm volatile("" : "+v"(acc1), "+v"(acc2));
+                // (one arc after the other: mixed, the 36-slot variant spills a register pair)
+                if constexpr (kOneByOne) asm volatile("" : "+v"(acc1), "+v"(acc2));
                 add_arc(wr[i + 1], e1, x1, acc1, acc2);
-                asm volatile("" : "+v"(acc1), "+v"(acc2));
+                if constexpr (kOneByOne) asm volatile("" : "+v"(acc1), "+v"(acc2));
             } else if constexpr (sizeof(Real) == 4) {
                 acc1 = fmaf(t0, x0, acc1);
                 acc2 = HAS_WB ? fmaf(wbr[HAS_WB ? i : 0], e0, acc2) : acc2 + t0;
