@@ -942,7 +942,9 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
         // 16 306 / 280, 64 517 / 485. Mean length 0.75 T: 84 pdfs 324 / 329 (B = 128, T = 280), 2,000
         // pdfs 534 / 500 (600 states, B = 48); 0.8 T: 337 / 356 and 551 / 534; all of length T: 372 /
         // 410 and 616 / 660. By state one bucket stays the better one: 300 states, 1,000 pdfs, B = 64
-        // 288 / 293, 128 384 / 427. LFMMI_BUCKETS set: as many as it says.
+        // 288 / 293, 128 384 / 427, and beside another pass, whose end every occupancy kernel waits
+        // for: 449 states, 2,350 pdfs, B = 52, full loss of up to 285 frames 625 / 652. LFMMI_BUCKETS
+        // set: as many as it says.
         double longest_us = 0.0, frames = 0.0;
         int32_t longest = 0;
         for (int32_t b = 0; b < B; ++b) {
@@ -951,7 +953,7 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
             longest_us = std::max(longest_us, lengths[b] * (0.6 + 3e-5 * h->packed[seqs[b].graph].num_arcs));
         }
         const bool many_pdfs = P > 512;
-        const bool much_to_hide = !h->occ_states && longest >= 240 && B >= (many_pdfs ? 16 : 48) &&
+        const bool much_to_hide = !beside && !h->occ_states && longest >= 240 && B >= (many_pdfs ? 16 : 48) &&
                                   frames <= (many_pdfs ? 0.78 : 0.7) * B * longest;
         int want = std::min(env_int("LFMMI_BUCKETS",
                                     longest_us < 200.0 && !much_to_hide ? 1 : (int)Buckets::kMax),
