@@ -72,6 +72,7 @@ struct lfmmi_graph {
                            // kept divided by the initial probabilities
     bool rec_grouped = false;  // every arc takes the pdf of the state it enters and the
                                // recursion runs the variant without an emission gather
+    bool rec_line = false;     // ... and its variant for waves that own one or two slices
     bool rec_short = false;    // ... and its variant for waves that own one short slice
     bool occ_states = false;   // ... and the occupancies are added up over states, not arcs
 
@@ -326,6 +327,28 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
                     if (!h->packed[g].pdf_by_dst) return 0;
                 return rec_grouped_slots(h->wide, h->has_wb, max_slots, waves * kLanes);
             };
+            // Such graphs with one or two slices per wave, the narrower one first: the
+            // straight-line variant (fp32), whatever their size. Time of a step, before / with it:
+            // 144 states, 648 arcs 0.54 / 0.28 us; 600, 3,900 0.62 / 0.36; 840, 5,460 0.68 / 0.43
+            // (all three with an emission gather before); 1,440, 19,440 1.04 / 0.67; 2,016, 21,168
+            // 1.02 / 0.70; 2,016, 27,216 1.04 / 0.76. LFMMI_GROUPED=2: without it.
+            auto line_slots = [&]() {
+                if (env_int("LFMMI_GROUPED", 1) != 1) return 0;
+                if (h->rec_hubs || h->wide || !h->occ_states) return 0;
+                if (std::max(h->max_rows_f, h->max_rows_b) > rec_line_max_rows()) return 0;
+                for (int32_t g = 0; g < n; ++g)
+                    for (int o = 0; o < 2; ++o) {
+                        const Ordering& od = h->packed[g].ord[o];
+                        for (int32_t w = 0; w < od.num_waves; ++w) {
+                            const int32_t s0 = od.wave_first[w], own = od.wave_first[w + 1] - s0;
+                            if (own > 2) return 0;
+                            if (own == 2 && od.slice_off[s0 + 1] - od.slice_off[s0] >
+                                                od.slice_off[s0 + 2] - od.slice_off[s0 + 1])
+                                return 0;
+                        }
+                    }
+                return rec_line_slots(h->has_wb, max_slots, waves * kLanes);
+            };
             // Such graphs with at most one slice of few slots per wave (per-utterance
             // numerators): the straight-line variant.
             auto short_slots = [&]() {
@@ -339,6 +362,10 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
             for (int32_t g = 0; g < n && h->occ_states; ++g) h->occ_states = h->packed[g].pdf_by_dst;
             int gslots = st == LFMMI_OK ? short_slots() : 0;
             h->rec_short = gslots > 0;
+            if (st == LFMMI_OK && gslots == 0) {
+                gslots = line_slots();
+                h->rec_line = gslots > 0;
+            }
             if (st == LFMMI_OK && gslots == 0) gslots = grouped_slots();
             h->rec_grouped = gslots > 0 && !h->rec_short;
             // Initial probabilities that differ: state values divided by them need no leak
@@ -776,6 +803,7 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
     shape.rec_hybrid = h->rec_hybrid;
     shape.rec_hubs = h->rec_hubs ? 1 : 0;
     shape.rec_grouped = h->rec_grouped ? 1 : 0;
+    shape.rec_line = h->rec_line ? 1 : 0;
     shape.rec_short = h->rec_short ? 1 : 0;
     shape.profile_rec_only = h->profile == 2 ? 1 : 0;
     shape.rec_leak = !h->has_wb ? 0 : (h->over_pi ? 2 : 1);
@@ -1299,6 +1327,7 @@ lfmmi_status lfmmi_graph_ordering_info(const lfmmi_graph* h, int32_t g, int32_t 
     for (int32_t f : o.slice_hub) info[10] += f != 0;
     // rows one state vector of the chosen recursion kernel's fixed LDS map holds
     info[11] = ord == 2 || h->rec_nslot == 0 ? 0
+               : h->rec_line                 ? rec_line_max_rows()
                : h->rec_hybrid == 2          ? 12288
                                              : (h->wide ? 4096 : 8192);
     return LFMMI_OK;

@@ -1623,6 +1623,332 @@ struct RecGrouped {
 };
 
 // ---------------------------------------------------------------------------
+// The same recursion as one straight line a step, for workgroups whose waves own one or two
+// slices. What bounds a step of such graphs is the serial stream of instructions of a wave from
+// one barrier to the next (one about every 4.6 clocks, ~20 for a branch, taken or not), not the
+// gathers: 2,016 states (442 slots a step, 920 LDS clocks) took 1.05 us a step with RecGrouped, of
+// which the tests for slice ends and what follows them were 0.19 and the staging of emissions
+// 0.15. Here the code is laid out for the width A of the wave's first slice (the packer puts the
+// narrower one first, so A is at most half the slots): no masks and no tests but two for the end
+// of the wave's slots. The emission of a lane's row goes from memory into a register two steps
+// ahead, with no stop in LDS; the sums of a row stay in registers; the totals of 64 steps collect
+// in the lanes of a register.
+// LDS map: X0 [0, 8K)  X1 [8K, 16K)  partial sums at 16K: n of wave w at value 32 * set + w, s 16
+// further; unused words behind them.
+// A step of that graph now takes 0.76 us (442 gathers of 64 lanes, 140 instructions a wave), a call
+// of 64 sequences of 100 to 500 frames 627 -> 504 us.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kLineX1 = 8192, kLinePart = 16384, kLineDump = kLinePart + 256;
+constexpr int kLineRows = 2048;
+__host__ __device__ constexpr size_t line_lds_bytes() { return kLineDump + 384; }
+
+template <bool HAS_WB, int NSLOT, int NT>
+struct RecLine {
+    static_assert(NSLOT % 4 == 0 && NSLOT >= 16, "slots go in groups of four; two tests near the end");
+    static constexpr int kGroup = 4, kRing = 8;  // two groups of gathers in flight before a step's sums
+    static constexpr int kBlock = 64;            // steps whose totals collect in a register
+
+    uint32_t xa[NSLOT];  // byte address of the gathered state value inside X0
+    float wr[NSLOT];     // arc weight (0 in closing and unused slots)
+    uint32_t row4[2];    // byte offset of the lane's rows in a state vector
+    uint32_t ysrc[2];    // ... of their pdfs in an emission row
+    float r[2], g[2];    // alpha: in_wpi of the rows; beta: in_w, in_wpi
+    float e[2][2];       // [parity of the step][slice]: emissions of the rows
+    typedef const __attribute__((address_space(1))) char* global_bytes_t;
+    typedef const __attribute__((address_space(1))) float* global_in_t;
+    typedef __attribute__((address_space(1))) char* global_out_bytes_t;
+    typedef __attribute__((address_space(1))) float* global_out_t;
+    global_bytes_t e2;        // emission row of the step after the next
+    global_out_bytes_t trow;  // trellis row this step writes
+    float inv, c;             // scale and leak of the vector the last step read
+    int keep_n, keep_s;       // lane q: the totals step q of the block found
+
+    __device__ __forceinline__ float emission(const int slice) const
+    {
+        return *(global_in_t)(e2 + ysrc[slice]);
+    }
+
+    // DIR 0: alpha, 1: beta. PAR = k & 1 as in RecRegs. A: slots of the wave's first slice (0: it
+    // owns one slice). `at`: the step's lane in keep_n, keep_s. `count`: the wave's slots.
+    template <int PAR, int DIR, int A>
+    __device__ __forceinline__ void step(const int at, const float leak_by, const uint32_t read_at,
+                                         const uint32_t write_at, const int count)
+    {
+        constexpr uint32_t xc = PAR ? 0u : kLineX1, xn = PAR ? kLineX1 : 0u;
+        constexpr uint32_t pc = kLinePart + (PAR ? 0u : 128u), pn = PAR ? 128u : 0u;
+        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
+        float pv = lds_ld(pc + read_at);
+        float xv[kRing];
+#pragma unroll
+        for (int i = 0; i < kRing; ++i) xv[i] = lds_ld(xc + xa[i]);
+        asm volatile("" ::: "memory");
+        pv = row16_allsum(pv);  // every row of 16 lanes: n (of two sums, odd rows: s)
+        float nr = pv, Sd = pv;
+        if constexpr (kTwoSums) {
+            nr = lane_value(pv, 0);
+            Sd = lane_value(pv, 16);
+        }
+        const uint32_t e2n = min(__float_as_uint(nr) & 0x7f800000u, 0x7e800000u);  // see pow2_scale
+        inv = __uint_as_float(0x7f000000u - e2n);
+        c = leak_by * Sd * inv;
+        keep_n = writelane_i32(__builtin_amdgcn_readfirstlane(__float_as_int(nr)), at, keep_n);
+        if constexpr (kTwoSums) keep_s = writelane_i32(__float_as_int(Sd), at, keep_s);
+
+        float acc = 0.f, n = 0.f, s = 0.f;
+        auto close = [&](const int slice) {
+            const float em = e[PAR][slice];
+            float x, v;
+            if constexpr (DIR == 0) {
+                v = x = em * fmaf(inv, acc, c * r[slice]);
+                n += x;
+            } else {
+                v = acc;
+                x = em * fmaf(inv, acc, c);
+                n = fmaf(r[slice], x, n);
+                if constexpr (kTwoSums) s = fmaf(g[slice], x, s);
+            }
+            lds_st(xn + row4[slice], x);
+            *(global_out_t)(trow + row4[slice]) = v;
+            acc = 0.f;
+            e[PAR][slice] = emission(slice);
+        };
+#pragma unroll
+        for (int i = 0; i < NSLOT; i += kGroup) {
+            if (i >= NSLOT - 2 * kGroup) {
+                int slots = count;
+                asm volatile("" : "+s"(slots));  // compare here, in a scalar register
+                if (i >= slots) break;
+            }
+            // issue priority falls as the wave advances (see RecRegs)
+            if (i == 0) __builtin_amdgcn_s_setprio(2);
+            else if (i == (NSLOT / 12) * 4) __builtin_amdgcn_s_setprio(1);
+            else if (i == (NSLOT / 6) * 4) __builtin_amdgcn_s_setprio(0);
+            float x[kGroup];
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) x[q] = xv[(i + q) % kRing];
+            if (i + kRing < NSLOT) {
+#pragma unroll
+                for (int q = 0; q < kGroup; ++q)
+                    xv[(i + q) % kRing] = lds_ld(xc + xa[(i + kRing + q) % NSLOT]);
+            }
+            // one wait for the group
+            asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]) : "v"(x[3]));
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) {
+                acc = fmaf(wr[i + q], x[q], acc);
+                if (i + q + 1 == A) close(0);
+            }
+        }
+        close(A > 0 ? 1 : 0);
+        __builtin_amdgcn_s_setprio(3);
+        const float ns = kTwoSums ? half_wave_sums(n, s) : wave_sum_lane63(n);
+        lds_st(pn + write_at, ns);
+        __syncthreads();
+    }
+
+    template <int DIR, int A>
+    __device__ __forceinline__ void steps(const int T, const int P, const int rows, const float leak_by,
+                                          const float aconst, const uint32_t read_at,
+                                          const uint32_t write_at, const int count, float* scalN,
+                                          float* scalS, const int wave, const int lane)
+    {
+        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
+        const ptrdiff_t estep = (DIR == 0 ? 4 : -4) * (ptrdiff_t)P;
+        const ptrdiff_t tstep = (DIR == 0 ? 4 : -4) * (ptrdiff_t)rows;
+        auto advance = [&](const int k) {
+            if (k + 2 + DIR < T) e2 += estep;
+            trow += tstep;
+        };
+        for (int k0 = 1; k0 <= T; k0 += kBlock) {
+            const int end = min(k0 + kBlock - 1, T);
+            int k = k0;
+            for (; k + 1 <= end; k += 2) {
+                step<1, DIR, A>(k - k0, leak_by, read_at, write_at, count);
+                advance(k);
+                step<0, DIR, A>(k + 1 - k0, leak_by, read_at, write_at, count);
+                advance(k + 1);
+            }
+            if (k <= end) step<1, DIR, A>(k - k0, leak_by, read_at, write_at, count);
+            // alpha: of the vector that step k read; beta: the scale of the rows that it stored
+            if (wave == 0 && lane <= end - k0) {
+                const float nr = __int_as_float(keep_n);
+                float N, unused;
+                pow2_scale(nr, &N, &unused);
+                const int to = DIR == 0 ? k0 - 1 + lane : T - k0 - lane;
+                scalN[to] = N;
+                scalS[to] = kTwoSums ? __int_as_float(keep_s) : (DIR == 0 ? nr : aconst * nr);
+            }
+        }
+    }
+
+    template <int DIR>
+    __device__ __forceinline__ void run(const FbParams& p, const SeqDesc& sd, const OrdDesc& od,
+                                        const int b)
+    {
+        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
+        const int tid = threadIdx.x;
+        const int lane = tid & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int nwaves = blockDim.x >> 6;
+        const int T = sd.T;
+        const int P = p.P;
+        const int rows = od.num_slices * 64;
+        float* trel = static_cast<float*>(DIR == 0 ? p.alpha : p.beta) +
+                      (DIR == 0 ? sd.alpha_at : sd.beta_at);
+        float* scalN = static_cast<float*>(p.scal) + (size_t)(DIR * 2) * p.scal_total + sd.scal_at;
+        float* scalS = scalN + p.scal_total;
+        const int32_t* so = p.g.slice_off + od.slice_off_at;
+        const float eps = p.leak;
+        const float* erows = p.emis + (size_t)b * p.T * P;
+
+        int s0 = 0, s1 = 0;  // the wave's slices: none, one or two
+        if (wave < od.num_waves) {
+            s0 = p.g.wave_first[od.wave_first_at + wave];
+            s1 = p.g.wave_first[od.wave_first_at + wave + 1];
+        }
+        const int first = so[s0];
+        const int count = so[s1] - first;
+        const int width0 = s1 - s0 == 2 ? so[s0 + 1] - first : 0;
+        load_records<NSLOT>(p, od, lane, first, count, xa, wr);
+        const int closing0 = HAS_WB ? width0 - 1 : -1, closing1 = HAS_WB ? count - 1 : -1;
+#pragma unroll
+        for (int i = 0; i < NSLOT; ++i) {
+            xa[i] = xa[i] & 0xffffu;
+            if (HAS_WB && (i == closing0 || i == closing1)) wr[i] = 0.f;  // holds no arc
+            asm volatile("" : "+v"(xa[i]), "+v"(wr[i]));
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int row = min(s0 + q, max(s1 - 1, 0)) * 64 + lane;
+            row4[q] = (uint32_t)row * 4u;
+            ysrc[q] = (uint32_t)p.g.row_pdf[od.vec_at + row] * 4u;
+            r[q] = (float)(DIR == 0 ? p.g.in_wpi : p.g.in_w)[od.vec_at + row];
+            g[q] = kTwoSums ? (float)p.g.in_wpi[od.vec_at + row] : 0.f;
+            e[0][q] = e[1][q] = 0.f;
+        }
+        keep_n = keep_s = 0;
+        if (tid < 64) lds_st(kLinePart + tid * 4, 0.f);
+        __syncthreads();
+
+        // Frame whose emissions meet the rows that step k stores, as in RecGrouped
+        auto frame_of = [&](int k) { return max(0, min(DIR == 0 ? k - 1 : T - k - 1, T - 1)); };
+        auto total = [&](float a, float bsum, const uint32_t to) {  // this wave's partial sums
+            a = wave_sum_uniform(a);
+            bsum = wave_sum_uniform(bsum);
+            if (lane == 0) {
+                lds_st(to + wave * 4, a);
+                lds_st(to + (16 + wave) * 4, bsum);
+            }
+        };
+        // ---- step 0: v_0 = init into X0, partial sums into set 0
+        {
+            float n = 0.f, s = 0.f;
+            const int ti = DIR == 0 ? 0 : T;
+            for (int sl = s0; sl < s1; ++sl) {
+                const int row = sl * 64 + lane;
+                const float v = p.g.vinit[od.vec_at + row];
+                lds_st(row * 4, v);
+                trel[(size_t)ti * rows + row] = v;
+                n += v;
+                s += p.g.va[od.vec_at + row] * v;
+            }
+            // beta: into set 1 first, the vector itself needs the totals
+            total(n, s, kLinePart + (DIR == 0 ? 0u : 128u));
+            if (T > 0) {
+#pragma unroll
+                for (int k = 1; k <= 2; ++k) {
+                    e2 = (global_bytes_t)(erows + (size_t)frame_of(k) * P);
+                    e[k & 1][0] = emission(0);
+                    e[k & 1][1] = emission(1);
+                }
+                e2 = (global_bytes_t)(erows + (size_t)frame_of(3) * P);
+            }
+            __syncthreads();
+            if constexpr (DIR == 1) {
+                const float pv = row16_allsum(lds_ld(kLinePart + (32u + (lane & 31)) * 4u));
+                const float nr = lane_value(pv, 0), Sd = lane_value(pv, 16);
+                float N;
+                pow2_scale(nr, &N, &inv);
+                c = eps * Sd * inv;
+                if (tid == 0) {
+                    scalN[T] = N;
+                    scalS[T] = Sd;
+                }
+                n = s = 0.f;
+                const float* em = erows + (size_t)max(T - 1, 0) * P;
+                for (int q = 0; q < s1 - s0 && T > 0; ++q) {
+                    const uint32_t at = (uint32_t)((s0 + q) * 64 + lane) * 4u;
+                    const int vec = od.vec_at + (s0 + q) * 64 + lane;
+                    const float u = em[p.g.row_pdf[vec]] * (inv * lds_ld(at) + c);
+                    lds_st(at, u);
+                    n += (float)p.g.in_w[vec] * u;
+                    if (kTwoSums) s += (float)p.g.in_wpi[vec] * u;
+                }
+                total(n, s, kLinePart);
+                __syncthreads();
+            }
+        }
+        trow = (global_out_bytes_t)(trel + (size_t)(DIR == 0 ? 1 : T - 1) * rows);
+        const float aconst = od.a_const;
+        const float leak_by = DIR == 0 || kTwoSums ? eps : eps * aconst;
+        const uint32_t read_at = (uint32_t)(lane & (kTwoSums ? 31 : 15)) * 4u;
+        // where the end-of-step sums go: n from lane 63; of two sums n from lane 31, s from 63
+        const bool says = kTwoSums ? (lane & 31) == 31 : lane == 63;
+        const uint32_t write_at =
+            says ? kLinePart + ((uint32_t)wave + (kTwoSums && lane == 63 ? 16u : 0u)) * 4u
+                 : kLineDump + (uint32_t)lane * 4u;
+        if (s1 > s0) {
+#define LFMMI_LINE_STEPS(A)                                                                      \
+    case A:                                                                                      \
+        if constexpr (A <= NSLOT / 2)                                                            \
+            steps<DIR, A>(T, P, rows, leak_by, aconst, read_at, write_at, count, scalN, scalS,   \
+                          wave, lane);                                                           \
+        break;
+            switch (width0) {
+                LFMMI_LINE_STEPS(0) LFMMI_LINE_STEPS(2) LFMMI_LINE_STEPS(4) LFMMI_LINE_STEPS(6)
+                LFMMI_LINE_STEPS(8) LFMMI_LINE_STEPS(10) LFMMI_LINE_STEPS(12) LFMMI_LINE_STEPS(14)
+                LFMMI_LINE_STEPS(16) LFMMI_LINE_STEPS(18)
+            }
+#undef LFMMI_LINE_STEPS
+        } else {
+            for (int k = 1; k <= T; ++k) __syncthreads();
+        }
+
+        // ---- last scalars (alpha) and the closing dot product; beta's last rows are read
+        // back from the trellis, each by the thread that stored it
+        {
+            if constexpr (DIR == 0) {
+                const uint32_t pc = kLinePart + ((T & 1) ? 128u : 0u);
+                const float nr = lane_value(row16_allsum(lds_ld(pc + (lane & 15) * 4u)), 0);
+                float N;
+                pow2_scale(nr, &N, &inv);
+                c = eps * nr * inv;
+                if (tid == 0) {
+                    scalN[T] = N;
+                    scalS[T] = nr;
+                }
+            }
+            float z = 0.f;
+            for (int sl = s0; sl < s1; ++sl) {
+                const int row = sl * 64 + lane;
+                const float raw = DIR == 0 ? lds_ld(((T & 1) ? kLineX1 : 0u) + row * 4) : trel[row];
+                const float v = raw * inv + c * p.g.vb[od.vec_at + row];
+                z += p.g.vfin[od.vec_at + row] * v;
+            }
+            z = wave_sum_uniform(z);
+            __syncthreads();
+            if (lane == 0) lds_st(kLinePart + wave * 4, z);
+            __syncthreads();
+            if (tid == 0) {
+                float Z = 0.f;
+                for (int w = 0; w < nwaves; ++w) Z += lds_ld(kLinePart + w * 4);
+                static_cast<float*>(p.zfin)[(size_t)DIR * p.B + b] = Z;
+            }
+        }
+    }
+};
+
+// ---------------------------------------------------------------------------
 // The same recursion for workgroups whose waves own at most one slice of at most NS slots
 // (per-utterance numerator graphs: a few hundred states, two or three arcs into each).
 // Such a step is bound by the instructions of one wave from a barrier to the next (a wave
@@ -2027,6 +2353,10 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
     if constexpr (BY_STATE == 1) {
         static_assert(NSLOT > 0 && !YREP && !HYBRID && !BIG && !HUBS, "grouped: resident arcs only");
         RecGrouped<Real, LEAK == 1, NSLOT, NT> r;
+        if (dir == 0) r.template run<0>(p, sd, od, b);
+        else r.template run<1>(p, sd, od, b);
+    } else if constexpr (BY_STATE == 3) {
+        RecLine<LEAK == 1, NSLOT, NT> r;
         if (dir == 0) r.template run<0>(p, sd, od, b);
         else r.template run<1>(p, sd, od, b);
     } else if constexpr (BY_STATE == 2) {
@@ -2753,11 +3083,13 @@ struct RecVariant {
     RecKernel fn;
     int hybrid = 0;  // 1: hybrid, 2: hybrid with the large LDS map
     int hubs = 0;    // handles hub slices
-    int grouped = 0; // emission by entered state: 1 RecGrouped, 2 RecShort
+    int grouped = 0; // emission by entered state: 1 RecGrouped, 2 RecShort, 3 RecLine
 };
 #define LFMMI_REC_GROUPED(REAL, WIDE, NSLOT, WB, NT)                                          \
     {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, WB, NT, false, false, false, 1>, \
      0, 0, 1}
+#define LFMMI_REC_LINE(NSLOT, WB, NT) \
+    {0, NSLOT, 0, WB, NT, k_rec<float, NSLOT, false, WB, NT, false, false, false, 3>, 0, 0, 3}
 #define LFMMI_REC_SHORT(REAL, WIDE, NS, NT) \
     {WIDE, NS, 0, 0, NT, k_rec<REAL, NS, false, 0, NT, false, false, false, 2>, 0, 0, 2}
 
@@ -2816,6 +3148,11 @@ const RecVariant kRecVariants[] = {
     LFMMI_REC_GROUPED(float, 0, 32, 1, 1024), LFMMI_REC_GROUPED(float, 0, 36, 1, 1024),
     LFMMI_REC_GROUPED(double, 1, 16, 1, 1024),
     LFMMI_REC_GROUPED(double, 1, 16, 0, 1024),
+    // ... one or two slices per wave
+    LFMMI_REC_LINE(16, 0, 1024), LFMMI_REC_LINE(24, 0, 1024), LFMMI_REC_LINE(32, 0, 1024),
+    LFMMI_REC_LINE(36, 0, 1024), LFMMI_REC_LINE(48, 0, 512),
+    LFMMI_REC_LINE(16, 1, 1024), LFMMI_REC_LINE(24, 1, 1024), LFMMI_REC_LINE(32, 1, 1024),
+    LFMMI_REC_LINE(36, 1, 1024), LFMMI_REC_LINE(48, 1, 512),
     // ... one short slice per wave
     LFMMI_REC_SHORT(float, 0, 4, 512), LFMMI_REC_SHORT(float, 0, 8, 512),
     LFMMI_REC_SHORT(double, 1, 4, 512), LFMMI_REC_SHORT(double, 1, 8, 512),
@@ -2826,6 +3163,7 @@ const RecVariant kRecVariants[] = {
 #undef LFMMI_REC_ROWS
 #undef LFMMI_REC_GROUPED
 #undef LFMMI_REC_SHORT
+#undef LFMMI_REC_LINE
 
 const RecVariant* find_rec(bool wide, int nslot, bool yrep, int leak, int hybrid, bool hubs,
                            int grouped, int threads)
@@ -2862,6 +3200,18 @@ int rec_grouped_slots(bool wide, bool has_wb, int max_wave_slots, int threads)
             best = v.nslot;
     return best;
 }
+
+int rec_line_slots(bool has_wb, int max_wave_slots, int threads)
+{
+    int best = 0;
+    for (const RecVariant& v : kRecVariants)
+        if (v.grouped == 3 && v.leak == (has_wb ? 1 : 0) && v.nslot >= max_wave_slots &&
+            threads <= v.max_threads && (best == 0 || v.nslot < best))
+            best = v.nslot;
+    return best;
+}
+
+int rec_line_max_rows() { return kLineRows; }
 
 int rec_grouped_max_rows(bool wide, int threads)
 {
@@ -3006,8 +3356,8 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
     const bool wide = sizeof(Real) == 8;
     const RecVariant* rv =
         find_rec(wide, shape.rec_nslot, shape.rec_yrep != 0, shape.rec_leak,
-                 shape.rec_hybrid, shape.rec_hubs != 0, shape.rec_short ? 2 : shape.rec_grouped,
-                 shape.rec_threads);
+                 shape.rec_hybrid, shape.rec_hubs != 0,
+                 shape.rec_short ? 2 : (shape.rec_line ? 3 : shape.rec_grouped), shape.rec_threads);
     if (!rv || shape.rec_threads > rv->max_threads) return hipErrorInvalidConfiguration;
     if (bk.n > 1 && (e = hipEventRecord(bk.fork, stream)) != hipSuccess) return e;
 
@@ -3023,7 +3373,8 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
     }
     // at least the scan's scratch
     const size_t rec_lds =
-        std::max<size_t>(shape.rec_nslot > 0
+        std::max<size_t>(shape.rec_line ? line_lds_bytes()
+                         : shape.rec_nslot > 0
                              ? reg_lds_bytes()
                              : rec_lds_bytes(p.lds_rows, p.P, wide, shape.rec_yrep != 0),
                          64 + 96);

@@ -24,8 +24,9 @@ struct Arrangement {
 // hub[r] != 0: row r gets a slice of its own and its len[r] arcs are spread over
 // the 64 lanes (a row with far more arcs than the others would otherwise make
 // its slice, and so its wave, that many slots long).
+// most_each: slices a wave may own (the caller sees to it that they all find a wave).
 Arrangement arrange(const std::vector<int32_t>& len, int waves, int extra_slots,
-                    const std::vector<uint8_t>* hub = nullptr)
+                    const std::vector<uint8_t>* hub = nullptr, size_t most_each = SIZE_MAX)
 {
     Arrangement ar;
     const int32_t R = (int32_t)len.size();
@@ -51,9 +52,10 @@ Arrangement arrange(const std::vector<int32_t>& len, int waves, int extra_slots,
     std::vector<std::vector<int32_t>> owned(ar.num_waves);
     std::vector<int64_t> load(ar.num_waves, 0);
     for (int32_t s = 0; s < ar.num_slices; ++s) {
-        int best = 0;
-        for (int w = 1; w < ar.num_waves; ++w) {
-            if (load[w] < load[best] ||
+        int best = -1;
+        for (int w = 0; w < ar.num_waves; ++w) {
+            if (owned[w].size() >= most_each) continue;
+            if (best < 0 || load[w] < load[best] ||
                 (load[w] == load[best] && owned[w].size() < owned[best].size()))
                 best = w;
         }
@@ -70,7 +72,7 @@ Arrangement arrange(const std::vector<int32_t>& len, int waves, int extra_slots,
             const int64_t wa = sorted_width[owned[top][a]];
             for (int w = 0; w < ar.num_waves && !improved; ++w) {
                 if (w == top) continue;
-                if (load[w] + wa < load[top]) {  // move
+                if (owned[w].size() < most_each && load[w] + wa < load[top]) {  // move
                     owned[w].push_back(owned[top][a]);
                     owned[top].erase(owned[top].begin() + a);
                     load[w] += wa;
@@ -92,7 +94,11 @@ Arrangement arrange(const std::vector<int32_t>& len, int waves, int extra_slots,
         }
         if (!improved) break;
     }
-    for (int w = 0; w < ar.num_waves; ++w) std::sort(owned[w].begin(), owned[w].end());
+    // (of two slices the narrower one first: see RecLine)
+    for (int w = 0; w < ar.num_waves; ++w) {
+        std::sort(owned[w].begin(), owned[w].end());
+        if (most_each == 2) std::reverse(owned[w].begin(), owned[w].end());
+    }
     ar.pos.assign(R, 0);
     ar.slice_width.clear();
     ar.slice_hub.clear();
@@ -853,6 +859,19 @@ bool uniform_init(const ArcList& g)
     return true;
 }
 
+// Whether the pdf-id of an arc is a function of the state it enters; per state that pdf-id, -1
+// where nothing enters.
+static bool pdf_of_entered_state(const ArcList& g, std::vector<int32_t>* pdf_of)
+{
+    pdf_of->assign(g.num_states, -1);
+    for (int64_t a = 0; a < g.num_arcs; ++a) {
+        int32_t& q = (*pdf_of)[g.dst[a]];
+        if (q < 0) q = g.pdf[a];
+        else if (q != g.pdf[a]) return false;
+    }
+    return true;
+}
+
 std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int occ_waves,
                        bool per_arc_leak, const PackTuning& tune, PackedGraph* out,
                        bool* bad_graph)
@@ -904,16 +923,28 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
         return hub;
     };
     std::vector<uint8_t> hub_f = hubs_of(indeg), hub_b = hubs_of(outdeg);
-    Arrangement af = arrange(indeg, rec_waves, closing, &hub_f);
-    Arrangement ab = arrange(outdeg, rec_waves, closing, &hub_b);
+    // Where the emission of an arc is that of the state it enters, waves own at most two slices
+    // where that leaves their slots in registers: the straight-line recursion asks for it.
+    std::vector<int32_t> entered_pdf;
+    const bool by_state = pdf_of_entered_state(g, &entered_pdf);
+    auto arranged = [&](const std::vector<int32_t>& deg, const std::vector<uint8_t>& hub) {
+        Arrangement ar = arrange(deg, rec_waves, closing, &hub);
+        if (by_state && ar.num_slices <= 2 * ar.num_waves) {
+            Arrangement two = arrange(deg, rec_waves, closing, &hub, 2);
+            if (two.max_wave_slots <= std::max(ar.max_wave_slots, kTwoSliceSlots)) return two;
+        }
+        return ar;
+    };
+    Arrangement af = arranged(indeg, hub_f);
+    Arrangement ab = arranged(outdeg, hub_b);
     // A hub slice adds 63 padding rows. Row numbers of both orderings go into 16-bit
     // key fields (index * 4): when the padded rows of either no longer fit, the
     // graph is packed without hub slices (slower, never wrong).
     if (af.num_slices * kLanes > kMaxIndex || ab.num_slices * kLanes > kMaxIndex) {
         std::fill(hub_f.begin(), hub_f.end(), 0);
         std::fill(hub_b.begin(), hub_b.end(), 0);
-        af = arrange(indeg, rec_waves, closing, &hub_f);
-        ab = arrange(outdeg, rec_waves, closing, &hub_b);
+        af = arranged(indeg, hub_f);
+        ab = arranged(outdeg, hub_b);
     }
     if (af.num_slices * kLanes > kMaxIndex || ab.num_slices * kLanes > kMaxIndex)
         return "too many states";
@@ -1001,13 +1032,8 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
     }
     // ---- is the pdf-id of an arc a function of the state it enters?
     {
-        std::vector<int32_t> pdf_of(S, -1);
-        bool by_dst = true;
-        for (int64_t a = 0; a < A && by_dst; ++a) {
-            int32_t& q = pdf_of[g.dst[a]];
-            if (q < 0) q = g.pdf[a];
-            else by_dst = q == g.pdf[a];
-        }
+        const std::vector<int32_t>& pdf_of = entered_pdf;
+        const bool by_dst = by_state;
         out->pdf_by_dst = by_dst;
         for (int d = 0; d < 2; ++d) {
             out->row_pdf[d].clear();

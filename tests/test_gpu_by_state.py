@@ -101,6 +101,67 @@ def test_recursion_by_state_flags_what_it_flagged_before():
     assert torch.equal(grad[0, :39].cpu(), want)
 
 
+def regular_graph(rng, S, d_first, d_second, P, init="uniform"):
+    """States of the first half have d_first arcs in and out, all within the half, the others
+    d_second: every slice of a half is that many slots wide in both directions."""
+    src, dst = [], []
+    for at, d in ((0, d_first), (S // 2, d_second)):
+        i = np.arange(S // 2)
+        for q in range(d):
+            src.append(at + (i * 1 + q * 7) % (S // 2))
+            dst.append(at + i)
+    src, dst = np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)
+    p = rng.uniform(0.1, 1.0, S) if init == "varied" else np.ones(S)
+    return {"num_states": S, "num_pdfs": P, "src": src, "dst": dst,
+            "pdf": rng.integers(0, P, S).astype(np.int32)[dst],
+            "logw": np.log(rng.uniform(0.02, 0.2, len(src))).astype(np.float32),
+            "init_prob": (p / p.sum()).astype(np.float32), "final_prob": np.ones(S, np.float32)}
+
+
+# the straight-line recursion: every width of a wave's first slice that it is laid out for, slot
+# counts at both of its tests for the end of a wave's slots and in every number of slots it is
+# built for; lengths around the 64 steps whose totals are stored together
+@pytest.mark.parametrize("wide,narrow,slots,init", [
+    (2, 2, 16, "uniform"), (6, 2, 16, "uniform"), (10, 6, 16, "uniform"), (14, 4, 24, "uniform"),
+    (12, 10, 24, "uniform"), (12, 12, 24, "uniform"), (18, 8, 32, "uniform"), (15, 13, 32, "uniform"),
+    (16, 16, 32, "uniform"), (17, 16, 36, "uniform"), (18, 18, 36, "uniform"), (34, 2, 36, "uniform"),
+    (5, 3, 16, "varied"), (13, 9, 24, "varied"), (15, 13, 32, "varied"), (17, 17, 36, "varied"),
+])
+def test_straight_line_recursion(wide, narrow, slots, init):
+    g = regular_graph(np.random.default_rng(wide * 40 + narrow), 2048, wide, narrow, 50, init)
+    closing = 1 if init == "varied" else 0
+    even = lambda d: (d + closing + 1) // 2 * 2
+    h = binding.lfmmi_graph_pack(g)
+    for o in (0, 1):
+        c = binding.lfmmi_graph_ordering_copy(h, 0, o)
+        assert c["register_slots"] == slots and c["lds_vector_rows"] == 2048
+        widths = np.diff(c["slice_off"]).reshape(16, 2)
+        assert np.all(widths == [even(narrow), even(wide)])
+    h.close()
+    parity(g, [129, 128, 127, 66, 65, 64, 63, 2, 1, 0, 3], 129, 1e-3)
+
+
+# ... waves with one slice and with two side by side, in a handle whose graphs leave some waves
+# of the workgroup without any
+def test_straight_line_recursion_of_graphs_of_different_sizes():
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(8)
+    graphs = [by_state_graph(rng, S, k, 50) for S, k in ((1100, 12), (70, 5), (1, 0), (2000, 7))]
+    lengths = np.array([70, 65, 3, 41], np.int32)
+    x = rng.normal(0, 2, (4, 70, 50)).astype(np.float32)
+    h = binding.lfmmi_graph_create_batch(graphs)
+    assert binding.lfmmi_graph_ordering_info(h, 0, 0)["lds_vector_rows"] == 2048
+    assert [binding.lfmmi_graph_ordering_info(h, i, 0)["waves"] for i in range(4)] == [16, 2, 1, 16]
+    objf, grad, status = binding.lfmmi_forward_backward(h, torch.from_numpy(x).cuda(), lengths, 1e-4)
+    torch.cuda.synchronize()
+    h.close()
+    assert np.all(status.cpu().numpy() == 0)
+    for b, g in enumerate(graphs):
+        lz, gamma = oracle.forward_backward(g, x[b:b + 1], lengths[b:b + 1], 1e-4)
+        assert abs(objf[b].item() - lz[0]) <= 1e-4 * max(abs(lz[0]), 1.0)
+        assert np.abs(grad[b].cpu().numpy() - gamma[0]).max() <= 1e-4
+
+
 # small graphs with many arcs a state: 38 to 48 slots a wave with at most 8 waves, lengths around
 # the steps fetched ahead; one slice, three, six
 @pytest.mark.parametrize("S,k,waves,slots", [(60, 40, 1, 48), (150, 30, 3, 44), (340, 24, 6, 38)])
