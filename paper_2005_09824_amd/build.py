@@ -7,8 +7,8 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblfmmi.so")
-SOURCES = ["kernels.hip", "api.cpp", "pack.cpp"]
-HEADERS = ["kernels.h", "pack.h", "microbench.hip", os.path.join("..", "..", "include", "lfmmi.h")]
+SOURCES = ["kernels.hip", "line.hip", "api.cpp", "pack.cpp"]
+HEADERS = ["kernels.h", "device.h", "pack.h", "microbench.hip", os.path.join("..", "..", "include", "lfmmi.h")]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -42,12 +42,20 @@ def build(force=True, extra_flags=()):
     if not force and not is_stale():
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + FLAGS + list(extra_flags) + ["-o", LIB] + \
-          [os.path.join(CSRC, s) for s in SOURCES]
-    jobs = [subprocess.Popen(cmd), subprocess.Popen(microbench_command(hipcc))]
+    # every source on its own, side by side: most of the time goes into the kernels' variants
+    out = os.path.join(HERE, "_build")
+    os.makedirs(out, exist_ok=True)
+    objects = [os.path.join(out, src + ".o") for src in SOURCES]
+    compile_flags = [f for f in FLAGS if f != "-shared"] + list(extra_flags)
+    cmds = [[hipcc] + compile_flags + ["-c", "-o", obj, os.path.join(CSRC, src)]
+            for src, obj in zip(SOURCES, objects)]
+    cmds.append(microbench_command(hipcc))
+    jobs = [subprocess.Popen(c) for c in cmds]
     codes = [j.wait() for j in jobs]
-    if any(codes):
-        raise subprocess.CalledProcessError(max(codes), cmd)
+    for code, cmd in zip(codes, cmds):
+        if code:
+            raise subprocess.CalledProcessError(code, cmd)
+    subprocess.check_call([hipcc] + FLAGS + ["-o", LIB] + objects)
     return LIB
 
 

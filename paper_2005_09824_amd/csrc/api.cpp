@@ -72,8 +72,8 @@ struct lfmmi_graph {
                            // kept divided by the initial probabilities
     bool rec_grouped = false;  // every arc takes the pdf of the state it enters and the
                                // recursion runs the variant without an emission gather
-    bool rec_line = false;     // ... and its variant for waves that own one or two slices
     bool rec_short = false;    // ... and its variant for waves that own one short slice
+    int rec_line = 0;          // the recursion in a straight line: 1 without an emission gather, 2 with
     bool occ_states = false;   // ... and the occupancies are added up over states, not arcs
 
     // device copy
@@ -222,6 +222,7 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
         tune.emission_conflicts = !h->rec_yrep;
         tune.balance_banks = !h->wide && env_int("LFMMI_BALANCE", 1) != 0;
         tune.order_slots = !h->wide && env_int("LFMMI_ORDER", 1) != 0;
+        tune.two_slices = !h->wide && env_int("LFMMI_LINE", 1) != 0;
         tune.hub_slices = env_int("LFMMI_HUBS", 1) != 0;
         tune.deal_occ = env_int("LFMMI_DEAL", 1) != 0;
 
@@ -327,27 +328,35 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
                     if (!h->packed[g].pdf_by_dst) return 0;
                 return rec_grouped_slots(h->wide, h->has_wb, max_slots, waves * kLanes);
             };
-            // Such graphs with one or two slices per wave, the narrower one first: the
-            // straight-line variant (fp32), whatever their size. Time of a step, before / with it:
-            // 144 states, 648 arcs 0.54 / 0.28 us; 600, 3,900 0.62 / 0.36; 840, 5,460 0.68 / 0.43
-            // (all three with an emission gather before); 1,440, 19,440 1.04 / 0.67; 2,016, 21,168
-            // 1.02 / 0.70; 2,016, 27,216 1.04 / 0.76. LFMMI_GROUPED=2: without it.
-            auto line_slots = [&]() {
-                if (env_int("LFMMI_GROUPED", 1) != 1) return 0;
-                if (h->rec_hubs || h->wide || !h->occ_states) return 0;
-                if (std::max(h->max_rows_f, h->max_rows_b) > rec_line_max_rows()) return 0;
+            auto leak = [&]() { return !h->has_wb ? 0 : (h->over_pi ? 2 : 1); };
+            // One or two slices per wave, the narrower one first: the straight-line variants (fp32),
+            // whatever the size: no size measured slower. Time of a step, before / with them:
+            // emission by entered state, 144 states, 648 arcs 0.54 / 0.25 us; 600, 3,900 0.61 /
+            // 0.31; 840, 5,460 0.68 / 0.39 (all three with an emission gather before); 1,440, 19,440
+            // 1.13 / 0.65; 2,016, 21,168 1.04 / 0.68. By arc: 20 states 0.55 / 0.27; 600, 5,400 0.84 /
+            // 0.56; 1,000, 10,000 1.13 / 0.93 (200 pdfs), 1.06 / 0.94 (600); 2,000, 20,000 1.09 / 0.95;
+            // 2,040, 10,200 0.88 / 0.77. LFMMI_LINE=0: never.
+            auto line_possible = [&]() {
+                if (env_int("LFMMI_LINE", 1) == 0 || h->rec_hubs || h->wide) return false;
+                if (std::max(h->max_rows_f, h->max_rows_b) > rec_line_max_rows()) return false;
                 for (int32_t g = 0; g < n; ++g)
                     for (int o = 0; o < 2; ++o) {
                         const Ordering& od = h->packed[g].ord[o];
                         for (int32_t w = 0; w < od.num_waves; ++w) {
                             const int32_t s0 = od.wave_first[w], own = od.wave_first[w + 1] - s0;
-                            if (own > 2) return 0;
+                            if (own > 2) return false;
                             if (own == 2 && od.slice_off[s0 + 1] - od.slice_off[s0] >
                                                 od.slice_off[s0 + 2] - od.slice_off[s0 + 1])
-                                return 0;
+                                return false;
                         }
                     }
-                return rec_line_slots(h->has_wb, max_slots, waves * kLanes);
+                return true;
+            };
+            auto line_slots = [&](bool by_state) {
+                if (by_state ? env_int("LFMMI_GROUPED", 1) != 1 || !h->occ_states : false) return 0;
+                if (!line_possible()) return 0;
+                return rec_line_slots(by_state, h->rec_yrep, by_state ? (h->has_wb ? 1 : 0) : leak(),
+                                      num_pdfs, max_slots, waves * kLanes);
             };
             // Such graphs with at most one slice of few slots per wave (per-utterance
             // numerators): the straight-line variant.
@@ -363,18 +372,21 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
             int gslots = st == LFMMI_OK ? short_slots() : 0;
             h->rec_short = gslots > 0;
             if (st == LFMMI_OK && gslots == 0) {
-                gslots = line_slots();
-                h->rec_line = gslots > 0;
+                gslots = line_slots(true);
+                h->rec_line = gslots > 0 ? 1 : 0;
             }
             if (st == LFMMI_OK && gslots == 0) gslots = grouped_slots();
             h->rec_grouped = gslots > 0 && !h->rec_short;
             // Initial probabilities that differ: state values divided by them need no leak
             // factor per arc and take every variant that a uniform one takes, but have to leave
             // every weight an ordinary fp32 number (see leak_by_rows).
-            auto leak = [&]() { return !h->has_wb ? 0 : (h->over_pi ? 2 : 1); };
             h->over_pi = st == LFMMI_OK && gslots == 0 && h->has_wb && !h->wide && !h->rec_hubs &&
                          env_int("LFMMI_OVER_PI", 1) != 0;
             for (int32_t g = 0; g < n && h->over_pi; ++g) h->over_pi = leak_by_rows(arcs_of(g));
+            if (st == LFMMI_OK && gslots == 0) {
+                gslots = line_slots(false);
+                if (gslots > 0) h->rec_line = 2;
+            }
             auto resident = [&](int slots, int wv) {
                 return rec_register_slots(h->wide, leak(), h->rec_yrep, h->rec_hubs, slots,
                                           wv * kLanes);
@@ -803,7 +815,7 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
     shape.rec_hybrid = h->rec_hybrid;
     shape.rec_hubs = h->rec_hubs ? 1 : 0;
     shape.rec_grouped = h->rec_grouped ? 1 : 0;
-    shape.rec_line = h->rec_line ? 1 : 0;
+    shape.rec_line = h->rec_line;
     shape.rec_short = h->rec_short ? 1 : 0;
     shape.profile_rec_only = h->profile == 2 ? 1 : 0;
     shape.rec_leak = !h->has_wb ? 0 : (h->over_pi ? 2 : 1);

@@ -109,8 +109,8 @@ struct LaunchShape {
     int rec_hybrid;    // 1: only the first slots of a wave are register-resident;
                        // 2: the same, with the LDS map for up to 12288 states
     int rec_grouped = 0;  // arcs take the emission of the entered state: no emission gather
-    int rec_line = 0;     // ... and every wave owns one or two slices (RecLine)
     int rec_short = 0;    // ... and every wave owns one short slice (RecShort)
+    int rec_line = 0;     // waves own one or two slices: 1 RecLine (as rec_grouped), 2 RecLineArc
     int occ_states = 0;  // frames per workgroup of the occupancy kernel by entered state (0: by arc)
     int occ_threads;   // workgroup size of the occupancy kernel
     int occ_frames;    // frames per occupancy workgroup (frame-at-a-time kernel)
@@ -166,8 +166,9 @@ int rec_hybrid_slots(bool wide, int leak, bool yrep, bool hubs, int map /* 1: 32
 // (0: none for this shape), and the rows it stages emissions for with this many threads.
 int rec_grouped_slots(bool wide, bool has_wb, int max_wave_slots, int threads);
 int rec_grouped_max_rows(bool wide, int threads);
-// The same for its variant for workgroups whose waves own one or two slices.
-int rec_line_slots(bool has_wb, int max_wave_slots, int threads);
+// Slots of the straight-line variant (waves that own one or two slices) for this shape, 0 if there
+// is none, and the most rows it takes.
+int rec_line_slots(bool by_state, bool yrep, int leak, int num_pdfs, int max_wave_slots, int threads);
 int rec_line_max_rows();
 // Arc slots per wave of the variant for graphs as above whose waves own one slice each
 // (0: none for this shape).

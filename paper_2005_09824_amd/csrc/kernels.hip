@@ -16,35 +16,12 @@
 // Scaled quantities: alpha'_t = ahat_t * exp(sum_{tau<=t} log n_tau) * (frame
 // maxima), likewise beta; the frame maxima cancel in the occupancies and are
 // added back into log Z.
-#include "kernels.h"
+#include "device.h"
 
 #include <algorithm>
 
 namespace lfmmi {
 namespace {
-
-template <typename Real>
-__device__ __forceinline__ Real wave_sum(Real v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// Element of an LDS array addressed by the record's index * 4 field.
-template <typename Real>
-__device__ __forceinline__ Real lds_at(const Real* base, uint32_t index4)
-{
-    return *reinterpret_cast<const Real*>(reinterpret_cast<const char*>(base) +
-                                          index4 * (uint32_t)(sizeof(Real) / 4));
-}
 
 // ---------------------------------------------------------------------------
 // Emission: one wave per frame row. A row holding NaN or +inf (or nothing but
@@ -85,56 +62,6 @@ __global__ void __launch_bounds__(256) k_emit(FbParams p)
 //   leak(v) = v + eps * (a . v) * b     (alpha: a = 1, b = pi; beta: a = pi, b = 1)
 // and store vhat = leak(v) / n, n = sum(v).
 // ---------------------------------------------------------------------------
-
-// Byte offset of a record's emission value inside a Y buffer: the upper half of
-// its key. Plain rows: 4 * pdf. Rows replicated 32 times, so that lane l always
-// reads bank l % 32 (conflict-free; small pdf counts only): 128 * pdf + 4 * (l % 32),
-// which the upload writes into the device copy of lane l's records.
-__device__ __forceinline__ uint32_t y_offset(uint32_t key) { return key >> 16; }
-
-__device__ __forceinline__ float lds_f32(const float* base, uint32_t byte_off)
-{
-    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off);
-}
-
-// Arc records on the device: the records of slots 2q and 2q + 1 of a lane lie side
-// by side, {key, w, key, w}, pair q of lane l at [q * 64 + l] (a 16-byte load per
-// lane streams from L2 at twice the rate of an 8-byte one); slices start at even
-// slots. The per-arc leak factors are paired up the same way.
-__device__ __forceinline__ const uint4* rec_pairs(const FbParams& p, const OrdDesc& od, const int lane)
-{
-    return reinterpret_cast<const uint4*>(p.g.recs) + (size_t)(od.rec_at >> 1) * 64 + lane;
-}
-__device__ __forceinline__ const float2* wb_pairs(const FbParams& p, const OrdDesc& od, const int lane)
-{
-    return reinterpret_cast<const float2*>(p.g.wb) + (size_t)(od.rec_at >> 1) * 64 + lane;
-}
-__device__ __forceinline__ uint2 rec_lo(const uint4 r) { return make_uint2(r.x, r.y); }
-__device__ __forceinline__ uint2 rec_hi(const uint4 r) { return make_uint2(r.z, r.w); }
-
-// The records of slots first .. first + NSLOT - 1 (`first` even) of this lane into keys and
-// weights: all loads go out before any is waited for (one after the other they took 10 us of a
-// launch with 24 slots). Slots from `count` on are empty.
-template <int NSLOT>
-__device__ __forceinline__ void load_records(const FbParams& p, const OrdDesc& od, const int lane,
-                                             const int first, const int count, uint32_t (&key)[NSLOT],
-                                             float (&w)[NSLOT])
-{
-    const uint4* recs = rec_pairs(p, od, lane);
-    const int last = max((od.total_slots >> 1) - 1, 0);  // (a load past it fetches it again)
-    uint4 r[NSLOT / 2];
-#pragma unroll
-    for (int q = 0; q < NSLOT / 2; ++q)
-        r[q] = od.total_slots > 0 ? recs[(size_t)min((first >> 1) + q, last) * 64] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int q = 0; q < NSLOT / 2; ++q) {
-        const bool on0 = 2 * q < count, on1 = 2 * q + 1 < count;
-        key[2 * q] = on0 ? r[q].x : 0u;
-        w[2 * q] = on0 ? __uint_as_float(r[q].y) : 0.f;
-        key[2 * q + 1] = on1 ? r[q].z : 0u;
-        w[2 * q + 1] = on1 ? __uint_as_float(r[q].w) : 0.f;
-    }
-}
 
 // The recursion of one (sequence, direction).
 //
@@ -363,108 +290,6 @@ __device__ __forceinline__ void rec_run(const FbParams& p, const SeqDesc& sd, co
 }
 
 // ---------------------------------------------------------------------------
-// Wave-level sums on the DPP cross-lane path (no LDS traffic).
-// ---------------------------------------------------------------------------
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_add(float v)
-{
-    // lanes of rows outside ROW_MASK, and lanes whose source is out of range, add 0
-    const int moved =
-        __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false);
-    return v + __int_as_float(moved);
-}
-
-// fp64: the two halves of the value travel separately
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add(double v)
-{
-    const long long bits = __double_as_longlong(v);
-    // (with every row written the old value is dead: bound_ctrl lets the compiler drop the
-    // two moves that would zero it first)
-    constexpr bool kAll = ROW_MASK == 0xf;
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)bits, CTRL, ROW_MASK, 0xf, kAll);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), CTRL, ROW_MASK, 0xf, kAll);
-    return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// After this every lane holds the sum over its row of 16 lanes.
-template <typename Real>
-__device__ __forceinline__ Real row16_allsum(Real v)
-{
-    v = dpp_add<0xB1, 0xf>(v);   // quad_perm [1,0,3,2]
-    v = dpp_add<0x4E, 0xf>(v);   // quad_perm [2,3,0,1]
-    v = dpp_add<0x141, 0xf>(v);  // row_half_mirror
-    v = dpp_add<0x140, 0xf>(v);  // row_mirror
-    return v;
-}
-
-// The value lane `l` holds, as a wave-uniform value.
-__device__ __forceinline__ float lane_value(float v, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ double lane_value(double v, int l)
-{
-    const long long bits = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)bits, l);
-    const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// v with lane L holding `value` (wave-uniform) instead. By the compiler's own intrinsic, not by
-// inline assembly: a lane write that reads a scalar register two instructions or fewer behind
-// the v_readlane that wrote it needs a wait, which the compiler puts in for its own only.
-__device__ int writelane_i32(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
-template <int L>
-__device__ __forceinline__ int write_lane(const int v, const int value)
-{
-    return writelane_i32(value, L, v);
-}
-
-// Sum over the 64 lanes, returned as a wave-uniform value.
-template <typename Real>
-__device__ __forceinline__ Real wave_sum_uniform(Real v)
-{
-    v = row16_allsum(v);
-    v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-    return lane_value(v, 63);
-}
-
-// Wave sums of a and b at once: a 32-lane swap puts a[l] + a[l + 32] in the lower
-// half-wave and b[l] + b[l + 32] in the upper one, five DPP steps finish both.
-// Lane 31 returns the sum of a, lane 63 the sum of b (other lanes: partial sums).
-__device__ __forceinline__ float half_wave_sums(float a, float b)
-{
-    // lanes 0-31 of [0] keep a, lanes 32-63 of [0] take b's lanes 0-31; [1] the rest
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b),
-                                                     false, false);
-    float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    v = row16_allsum(v);
-    return dpp_add<0x142, 0xf>(v);  // row_bcast:15: row 1 gets row 0's sum, row 3 row 2's
-}
-__device__ __forceinline__ double half_wave_sums(double a, double b)
-{
-    const long long ab = __double_as_longlong(a), bb = __double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ab, (unsigned)bb, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ab >> 32), (unsigned)(bb >> 32),
-                                                     false, false);
-    double v = __longlong_as_double(((long long)hi[0] << 32) | lo[0]) +
-               __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
-    v = row16_allsum(v);
-    return dpp_add<0x142, 0xf>(v);
-}
-
-// Lane 63 returns the sum over the wave (other lanes: partial sums).
-template <typename Real>
-__device__ __forceinline__ Real wave_sum_lane63(Real v)
-{
-    v = row16_allsum(v);
-    v = dpp_add<0x142, 0xf>(v);     // row_bcast:15: rows 1 and 3 get the sums of 0 and 2
-    return dpp_add<0x143, 0xf>(v);  // row_bcast:31: row 3 gets the sum of rows 0 and 1
-}
-
-// ---------------------------------------------------------------------------
 // The recursion with the wave's arc records in registers (graphs whose waves
 // own at most NSLOT slots; state values fp32 or fp64). Fixed LDS map, so that the buffer of the
 // current parity is an immediate offset on every LDS instruction:
@@ -476,32 +301,6 @@ constexpr uint32_t kRegX1 = 32768, kRegY0 = 65536, kRegY1 = 98304, kRegPart = 13
 constexpr uint32_t kRegYZero = 32764;  // byte offset of the zero word inside a Y buffer
 
 __host__ __device__ constexpr size_t reg_lds_bytes() { return kRegPart + 4 * 32 * sizeof(double); }
-
-// LDS access by absolute byte address (the kernel's dynamic LDS starts at 0: it
-// declares no static LDS), so that the address register goes straight into the
-// ds instruction and constant parts fold into its immediate offset.
-typedef __attribute__((address_space(3))) float lds_float_t;
-__device__ __forceinline__ float lds_ld(uint32_t addr)
-{
-    return *reinterpret_cast<const lds_float_t*>(static_cast<uintptr_t>(addr));
-}
-__device__ __forceinline__ void lds_st(uint32_t addr, float v)
-{
-    *reinterpret_cast<lds_float_t*>(static_cast<uintptr_t>(addr)) = v;
-}
-typedef __attribute__((address_space(3))) double lds_double_t;
-__device__ __forceinline__ void lds_st(uint32_t addr, double v)
-{
-    *reinterpret_cast<lds_double_t*>(static_cast<uintptr_t>(addr)) = v;
-}
-template <typename Real>
-__device__ __forceinline__ Real lds_ldr(uint32_t addr)
-{
-    if constexpr (sizeof(Real) == 8)
-        return *reinterpret_cast<const lds_double_t*>(static_cast<uintptr_t>(addr));
-    else
-        return *reinterpret_cast<const lds_float_t*>(static_cast<uintptr_t>(addr));
-}
 
 // Phase timers (builds with -DLFMMI_PHASE_TIMERS only; the library as shipped carries
 // none of this). k_occ_planes: thread 0 of every workgroup adds the clocks between two
@@ -1277,24 +1076,6 @@ struct RecRegs {
 // such a graph took before (the variant with two barriers in beta held 32 slots). 60 states of 40
 // arcs (48 slots, one wave), 500 frames, B = 1: 529 us a call with an emission gather, 394 without.
 // ---------------------------------------------------------------------------
-// N: the largest power of two not above n (0 below the normal range, and nothing beyond 2^126,
-// 2^1022 in fp64); inv: its inverse, without a test for totals that are zero or not finite:
-// they leave log Z at -inf or NaN whatever the scale is, and the rows that follow at zero
-// or not finite.
-__device__ __forceinline__ void pow2_scale(const float n, float* N, float* inv)
-{
-    const uint32_t e = min(__float_as_uint(n) & 0x7f800000u, 0x7e800000u);
-    *N = __uint_as_float(e);
-    *inv = __uint_as_float(0x7f000000u - e);
-}
-__device__ __forceinline__ void pow2_scale(const double n, double* N, double* inv)
-{
-    const uint32_t hi = (uint32_t)((unsigned long long)__double_as_longlong(n) >> 32);
-    const uint32_t e = min(hi & 0x7ff00000u, 0x7fd00000u);
-    *N = __longlong_as_double((long long)((unsigned long long)e << 32));
-    *inv = __longlong_as_double((long long)((unsigned long long)(0x7fe00000u - e) << 32));
-}
-
 // LDS map: X0 [0, 32K)  X1 [32K, 64K)  EY0 [64K, 80K)  EY1 [96K, 112K)  partial sums at
 // 128K; the sums per row behind the EY buffers (in_wpi for alpha; in_w and in_wpi for beta).
 // EY[row] = e[pdf_row]: thread i fetches the values of rows i, i + threads, ... two steps
@@ -1623,332 +1404,6 @@ struct RecGrouped {
 };
 
 // ---------------------------------------------------------------------------
-// The same recursion as one straight line a step, for workgroups whose waves own one or two
-// slices. What bounds a step of such graphs is the serial stream of instructions of a wave from
-// one barrier to the next (one about every 4.6 clocks, ~20 for a branch, taken or not), not the
-// gathers: 2,016 states (442 slots a step, 920 LDS clocks) took 1.05 us a step with RecGrouped, of
-// which the tests for slice ends and what follows them were 0.19 and the staging of emissions
-// 0.15. Here the code is laid out for the width A of the wave's first slice (the packer puts the
-// narrower one first, so A is at most half the slots): no masks and no tests but two for the end
-// of the wave's slots. The emission of a lane's row goes from memory into a register two steps
-// ahead, with no stop in LDS; the sums of a row stay in registers; the totals of 64 steps collect
-// in the lanes of a register.
-// LDS map: X0 [0, 8K)  X1 [8K, 16K)  partial sums at 16K: n of wave w at value 32 * set + w, s 16
-// further; unused words behind them.
-// A step of that graph now takes 0.76 us (442 gathers of 64 lanes, 140 instructions a wave), a call
-// of 64 sequences of 100 to 500 frames 627 -> 504 us.
-// ---------------------------------------------------------------------------
-constexpr uint32_t kLineX1 = 8192, kLinePart = 16384, kLineDump = kLinePart + 256;
-constexpr int kLineRows = 2048;
-__host__ __device__ constexpr size_t line_lds_bytes() { return kLineDump + 384; }
-
-template <bool HAS_WB, int NSLOT, int NT>
-struct RecLine {
-    static_assert(NSLOT % 4 == 0 && NSLOT >= 16, "slots go in groups of four; two tests near the end");
-    static constexpr int kGroup = 4, kRing = 8;  // two groups of gathers in flight before a step's sums
-    static constexpr int kBlock = 64;            // steps whose totals collect in a register
-
-    uint32_t xa[NSLOT];  // byte address of the gathered state value inside X0
-    float wr[NSLOT];     // arc weight (0 in closing and unused slots)
-    uint32_t row4[2];    // byte offset of the lane's rows in a state vector
-    uint32_t ysrc[2];    // ... of their pdfs in an emission row
-    float r[2], g[2];    // alpha: in_wpi of the rows; beta: in_w, in_wpi
-    float e[2][2];       // [parity of the step][slice]: emissions of the rows
-    typedef const __attribute__((address_space(1))) char* global_bytes_t;
-    typedef const __attribute__((address_space(1))) float* global_in_t;
-    typedef __attribute__((address_space(1))) char* global_out_bytes_t;
-    typedef __attribute__((address_space(1))) float* global_out_t;
-    global_bytes_t e2;        // emission row of the step after the next
-    global_out_bytes_t trow;  // trellis row this step writes
-    float inv, c;             // scale and leak of the vector the last step read
-    int keep_n, keep_s;       // lane q: the totals step q of the block found
-
-    __device__ __forceinline__ float emission(const int slice) const
-    {
-        return *(global_in_t)(e2 + ysrc[slice]);
-    }
-
-    // DIR 0: alpha, 1: beta. PAR = k & 1 as in RecRegs. A: slots of the wave's first slice (0: it
-    // owns one slice). `at`: the step's lane in keep_n, keep_s. `count`: the wave's slots.
-    template <int PAR, int DIR, int A>
-    __device__ __forceinline__ void step(const int at, const float leak_by, const uint32_t read_at,
-                                         const uint32_t write_at, const int count)
-    {
-        constexpr uint32_t xc = PAR ? 0u : kLineX1, xn = PAR ? kLineX1 : 0u;
-        constexpr uint32_t pc = kLinePart + (PAR ? 0u : 128u), pn = PAR ? 128u : 0u;
-        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
-        float pv = lds_ld(pc + read_at);
-        float xv[kRing];
-#pragma unroll
-        for (int i = 0; i < kRing; ++i) xv[i] = lds_ld(xc + xa[i]);
-        asm volatile("" ::: "memory");
-        pv = row16_allsum(pv);  // every row of 16 lanes: n (of two sums, odd rows: s)
-        float nr = pv, Sd = pv;
-        if constexpr (kTwoSums) {
-            nr = lane_value(pv, 0);
-            Sd = lane_value(pv, 16);
-        }
-        const uint32_t e2n = min(__float_as_uint(nr) & 0x7f800000u, 0x7e800000u);  // see pow2_scale
-        inv = __uint_as_float(0x7f000000u - e2n);
-        c = leak_by * Sd * inv;
-        keep_n = writelane_i32(__builtin_amdgcn_readfirstlane(__float_as_int(nr)), at, keep_n);
-        if constexpr (kTwoSums) keep_s = writelane_i32(__float_as_int(Sd), at, keep_s);
-
-        float acc = 0.f, n = 0.f, s = 0.f;
-        auto close = [&](const int slice) {
-            const float em = e[PAR][slice];
-            float x, v;
-            if constexpr (DIR == 0) {
-                v = x = em * fmaf(inv, acc, c * r[slice]);
-                n += x;
-            } else {
-                v = acc;
-                x = em * fmaf(inv, acc, c);
-                n = fmaf(r[slice], x, n);
-                if constexpr (kTwoSums) s = fmaf(g[slice], x, s);
-            }
-            lds_st(xn + row4[slice], x);
-            *(global_out_t)(trow + row4[slice]) = v;
-            acc = 0.f;
-            e[PAR][slice] = emission(slice);
-        };
-#pragma unroll
-        for (int i = 0; i < NSLOT; i += kGroup) {
-            if (i >= NSLOT - 2 * kGroup) {
-                int slots = count;
-                asm volatile("" : "+s"(slots));  // compare here, in a scalar register
-                if (i >= slots) break;
-            }
-            // issue priority falls as the wave advances (see RecRegs)
-            if (i == 0) __builtin_amdgcn_s_setprio(2);
-            else if (i == (NSLOT / 12) * 4) __builtin_amdgcn_s_setprio(1);
-            else if (i == (NSLOT / 6) * 4) __builtin_amdgcn_s_setprio(0);
-            float x[kGroup];
-#pragma unroll
-            for (int q = 0; q < kGroup; ++q) x[q] = xv[(i + q) % kRing];
-            if (i + kRing < NSLOT) {
-#pragma unroll
-                for (int q = 0; q < kGroup; ++q)
-                    xv[(i + q) % kRing] = lds_ld(xc + xa[(i + kRing + q) % NSLOT]);
-            }
-            // one wait for the group
-            asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]) : "v"(x[3]));
-#pragma unroll
-            for (int q = 0; q < kGroup; ++q) {
-                acc = fmaf(wr[i + q], x[q], acc);
-                if (i + q + 1 == A) close(0);
-            }
-        }
-        close(A > 0 ? 1 : 0);
-        __builtin_amdgcn_s_setprio(3);
-        const float ns = kTwoSums ? half_wave_sums(n, s) : wave_sum_lane63(n);
-        lds_st(pn + write_at, ns);
-        __syncthreads();
-    }
-
-    template <int DIR, int A>
-    __device__ __forceinline__ void steps(const int T, const int P, const int rows, const float leak_by,
-                                          const float aconst, const uint32_t read_at,
-                                          const uint32_t write_at, const int count, float* scalN,
-                                          float* scalS, const int wave, const int lane)
-    {
-        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
-        const ptrdiff_t estep = (DIR == 0 ? 4 : -4) * (ptrdiff_t)P;
-        const ptrdiff_t tstep = (DIR == 0 ? 4 : -4) * (ptrdiff_t)rows;
-        auto advance = [&](const int k) {
-            if (k + 2 + DIR < T) e2 += estep;
-            trow += tstep;
-        };
-        for (int k0 = 1; k0 <= T; k0 += kBlock) {
-            const int end = min(k0 + kBlock - 1, T);
-            int k = k0;
-            for (; k + 1 <= end; k += 2) {
-                step<1, DIR, A>(k - k0, leak_by, read_at, write_at, count);
-                advance(k);
-                step<0, DIR, A>(k + 1 - k0, leak_by, read_at, write_at, count);
-                advance(k + 1);
-            }
-            if (k <= end) step<1, DIR, A>(k - k0, leak_by, read_at, write_at, count);
-            // alpha: of the vector that step k read; beta: the scale of the rows that it stored
-            if (wave == 0 && lane <= end - k0) {
-                const float nr = __int_as_float(keep_n);
-                float N, unused;
-                pow2_scale(nr, &N, &unused);
-                const int to = DIR == 0 ? k0 - 1 + lane : T - k0 - lane;
-                scalN[to] = N;
-                scalS[to] = kTwoSums ? __int_as_float(keep_s) : (DIR == 0 ? nr : aconst * nr);
-            }
-        }
-    }
-
-    template <int DIR>
-    __device__ __forceinline__ void run(const FbParams& p, const SeqDesc& sd, const OrdDesc& od,
-                                        const int b)
-    {
-        constexpr bool kTwoSums = DIR == 1 && HAS_WB;
-        const int tid = threadIdx.x;
-        const int lane = tid & 63;
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int nwaves = blockDim.x >> 6;
-        const int T = sd.T;
-        const int P = p.P;
-        const int rows = od.num_slices * 64;
-        float* trel = static_cast<float*>(DIR == 0 ? p.alpha : p.beta) +
-                      (DIR == 0 ? sd.alpha_at : sd.beta_at);
-        float* scalN = static_cast<float*>(p.scal) + (size_t)(DIR * 2) * p.scal_total + sd.scal_at;
-        float* scalS = scalN + p.scal_total;
-        const int32_t* so = p.g.slice_off + od.slice_off_at;
-        const float eps = p.leak;
-        const float* erows = p.emis + (size_t)b * p.T * P;
-
-        int s0 = 0, s1 = 0;  // the wave's slices: none, one or two
-        if (wave < od.num_waves) {
-            s0 = p.g.wave_first[od.wave_first_at + wave];
-            s1 = p.g.wave_first[od.wave_first_at + wave + 1];
-        }
-        const int first = so[s0];
-        const int count = so[s1] - first;
-        const int width0 = s1 - s0 == 2 ? so[s0 + 1] - first : 0;
-        load_records<NSLOT>(p, od, lane, first, count, xa, wr);
-        const int closing0 = HAS_WB ? width0 - 1 : -1, closing1 = HAS_WB ? count - 1 : -1;
-#pragma unroll
-        for (int i = 0; i < NSLOT; ++i) {
-            xa[i] = xa[i] & 0xffffu;
-            if (HAS_WB && (i == closing0 || i == closing1)) wr[i] = 0.f;  // holds no arc
-            asm volatile("" : "+v"(xa[i]), "+v"(wr[i]));
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int row = min(s0 + q, max(s1 - 1, 0)) * 64 + lane;
-            row4[q] = (uint32_t)row * 4u;
-            ysrc[q] = (uint32_t)p.g.row_pdf[od.vec_at + row] * 4u;
-            r[q] = (float)(DIR == 0 ? p.g.in_wpi : p.g.in_w)[od.vec_at + row];
-            g[q] = kTwoSums ? (float)p.g.in_wpi[od.vec_at + row] : 0.f;
-            e[0][q] = e[1][q] = 0.f;
-        }
-        keep_n = keep_s = 0;
-        if (tid < 64) lds_st(kLinePart + tid * 4, 0.f);
-        __syncthreads();
-
-        // Frame whose emissions meet the rows that step k stores, as in RecGrouped
-        auto frame_of = [&](int k) { return max(0, min(DIR == 0 ? k - 1 : T - k - 1, T - 1)); };
-        auto total = [&](float a, float bsum, const uint32_t to) {  // this wave's partial sums
-            a = wave_sum_uniform(a);
-            bsum = wave_sum_uniform(bsum);
-            if (lane == 0) {
-                lds_st(to + wave * 4, a);
-                lds_st(to + (16 + wave) * 4, bsum);
-            }
-        };
-        // ---- step 0: v_0 = init into X0, partial sums into set 0
-        {
-            float n = 0.f, s = 0.f;
-            const int ti = DIR == 0 ? 0 : T;
-            for (int sl = s0; sl < s1; ++sl) {
-                const int row = sl * 64 + lane;
-                const float v = p.g.vinit[od.vec_at + row];
-                lds_st(row * 4, v);
-                trel[(size_t)ti * rows + row] = v;
-                n += v;
-                s += p.g.va[od.vec_at + row] * v;
-            }
-            // beta: into set 1 first, the vector itself needs the totals
-            total(n, s, kLinePart + (DIR == 0 ? 0u : 128u));
-            if (T > 0) {
-#pragma unroll
-                for (int k = 1; k <= 2; ++k) {
-                    e2 = (global_bytes_t)(erows + (size_t)frame_of(k) * P);
-                    e[k & 1][0] = emission(0);
-                    e[k & 1][1] = emission(1);
-                }
-                e2 = (global_bytes_t)(erows + (size_t)frame_of(3) * P);
-            }
-            __syncthreads();
-            if constexpr (DIR == 1) {
-                const float pv = row16_allsum(lds_ld(kLinePart + (32u + (lane & 31)) * 4u));
-                const float nr = lane_value(pv, 0), Sd = lane_value(pv, 16);
-                float N;
-                pow2_scale(nr, &N, &inv);
-                c = eps * Sd * inv;
-                if (tid == 0) {
-                    scalN[T] = N;
-                    scalS[T] = Sd;
-                }
-                n = s = 0.f;
-                const float* em = erows + (size_t)max(T - 1, 0) * P;
-                for (int q = 0; q < s1 - s0 && T > 0; ++q) {
-                    const uint32_t at = (uint32_t)((s0 + q) * 64 + lane) * 4u;
-                    const int vec = od.vec_at + (s0 + q) * 64 + lane;
-                    const float u = em[p.g.row_pdf[vec]] * (inv * lds_ld(at) + c);
-                    lds_st(at, u);
-                    n += (float)p.g.in_w[vec] * u;
-                    if (kTwoSums) s += (float)p.g.in_wpi[vec] * u;
-                }
-                total(n, s, kLinePart);
-                __syncthreads();
-            }
-        }
-        trow = (global_out_bytes_t)(trel + (size_t)(DIR == 0 ? 1 : T - 1) * rows);
-        const float aconst = od.a_const;
-        const float leak_by = DIR == 0 || kTwoSums ? eps : eps * aconst;
-        const uint32_t read_at = (uint32_t)(lane & (kTwoSums ? 31 : 15)) * 4u;
-        // where the end-of-step sums go: n from lane 63; of two sums n from lane 31, s from 63
-        const bool says = kTwoSums ? (lane & 31) == 31 : lane == 63;
-        const uint32_t write_at =
-            says ? kLinePart + ((uint32_t)wave + (kTwoSums && lane == 63 ? 16u : 0u)) * 4u
-                 : kLineDump + (uint32_t)lane * 4u;
-        if (s1 > s0) {
-#define LFMMI_LINE_STEPS(A)                                                                      \
-    case A:                                                                                      \
-        if constexpr (A <= NSLOT / 2)                                                            \
-            steps<DIR, A>(T, P, rows, leak_by, aconst, read_at, write_at, count, scalN, scalS,   \
-                          wave, lane);                                                           \
-        break;
-            switch (width0) {
-                LFMMI_LINE_STEPS(0) LFMMI_LINE_STEPS(2) LFMMI_LINE_STEPS(4) LFMMI_LINE_STEPS(6)
-                LFMMI_LINE_STEPS(8) LFMMI_LINE_STEPS(10) LFMMI_LINE_STEPS(12) LFMMI_LINE_STEPS(14)
-                LFMMI_LINE_STEPS(16) LFMMI_LINE_STEPS(18)
-            }
-#undef LFMMI_LINE_STEPS
-        } else {
-            for (int k = 1; k <= T; ++k) __syncthreads();
-        }
-
-        // ---- last scalars (alpha) and the closing dot product; beta's last rows are read
-        // back from the trellis, each by the thread that stored it
-        {
-            if constexpr (DIR == 0) {
-                const uint32_t pc = kLinePart + ((T & 1) ? 128u : 0u);
-                const float nr = lane_value(row16_allsum(lds_ld(pc + (lane & 15) * 4u)), 0);
-                float N;
-                pow2_scale(nr, &N, &inv);
-                c = eps * nr * inv;
-                if (tid == 0) {
-                    scalN[T] = N;
-                    scalS[T] = nr;
-                }
-            }
-            float z = 0.f;
-            for (int sl = s0; sl < s1; ++sl) {
-                const int row = sl * 64 + lane;
-                const float raw = DIR == 0 ? lds_ld(((T & 1) ? kLineX1 : 0u) + row * 4) : trel[row];
-                const float v = raw * inv + c * p.g.vb[od.vec_at + row];
-                z += p.g.vfin[od.vec_at + row] * v;
-            }
-            z = wave_sum_uniform(z);
-            __syncthreads();
-            if (lane == 0) lds_st(kLinePart + wave * 4, z);
-            __syncthreads();
-            if (tid == 0) {
-                float Z = 0.f;
-                for (int w = 0; w < nwaves; ++w) Z += lds_ld(kLinePart + w * 4);
-                static_cast<float*>(p.zfin)[(size_t)DIR * p.B + b] = Z;
-            }
-        }
-    }
-};
-
-// ---------------------------------------------------------------------------
 // The same recursion for workgroups whose waves own at most one slice of at most NS slots
 // (per-utterance numerator graphs: a few hundred states, two or three arcs into each).
 // Such a step is bound by the instructions of one wave from a barrier to the next (a wave
@@ -2218,126 +1673,6 @@ struct RecShort {
     }
 };
 
-// ---------------------------------------------------------------------------
-// Scales of one sequence, once both of its recursions are done:
-//   log Z_b = log(zfin) + sum_t log n_t (+ the frame maxima), and the factor that
-//   turns ahat_{t-1} * w * e_t * bhat_t into an occupancy,
-//   c_t = exp(A_{t-1} + B_t - log Z'),  A, B = prefix / suffix sums of log n,
-// in fp64. Called by every thread of a workgroup (at most 256 of them work);
-// scratch: 96 bytes of LDS nobody else uses.
-// ---------------------------------------------------------------------------
-// Largest difference (nats) between the alpha-side and the beta-side log Z of a
-// sequence that counts as rounding: fp32 state vectors on the longest workloads
-// here differ by a few 1e-5.
-constexpr double kTotalsAgree = 1e-3;
-
-// The prefix sums run over lanes first (shuffles), then over the waves' totals: one thread
-// adding up 256 partial sums one after the other took 12 to 15 us at the end of every
-// sequence. A thread keeps the logarithms of its first kKeep frames.
-template <typename Real>
-__device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scratch_raw)
-{
-    constexpr int kKeep = 4;  // all of them up to 1,023 frames
-    double* tot = reinterpret_cast<double*>(scratch_raw);  // [wave][3]
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int workers = min((int)blockDim.x, 256);
-    const SeqDesc sd = p.seqs[b];
-    const int T = sd.T;
-    const int n = T + 1;
-    const Real* na = static_cast<const Real*>(p.scal) + sd.scal_at;
-    const Real* nb = static_cast<const Real*>(p.scal) + 2 * p.scal_total + sd.scal_at;
-    Real* cfac = static_cast<Real*>(p.cfac) + sd.scal_at;
-    const int chunk = (n + workers - 1) / workers;
-    const bool work = tid < workers;
-    const int i0 = work ? min(tid * chunk, n) : n, i1 = min(i0 + chunk, n);
-    double la = 0.0, lb = 0.0, lm = 0.0;
-    double ka[kKeep], kb[kKeep];
-    if (work)
-        for (int t = tid; t < T; t += workers) lm += (double)p.rowmax[(size_t)b * p.T + t];
-#pragma unroll
-    for (int q = 0; q < kKeep; ++q) {
-        const bool on = i0 + q < i1;
-        ka[q] = on ? log((double)na[i0 + q]) : 0.0;
-        kb[q] = on ? log((double)nb[i0 + q]) : 0.0;
-        la += ka[q];
-        lb += kb[q];
-    }
-    for (int i = i0 + kKeep; i < i1; ++i) {
-        la += log((double)na[i]);
-        lb += log((double)nb[i]);
-    }
-    double ra = la, rb = lb;  // inclusive sums over the wave's lanes
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const double xa = __shfl_up(ra, o, 64), xb = __shfl_up(rb, o, 64);
-        lm += __shfl_xor(lm, o, 64);
-        if (lane >= o) {
-            ra += xa;
-            rb += xb;
-        }
-    }
-    if (work && lane == 63) {
-        double* w = tot + 3 * (tid >> 6);
-        w[0] = ra;
-        w[1] = rb;
-        w[2] = lm;
-    }
-    __syncthreads();
-    double totA = 0.0, totB = 0.0, msum = 0.0;
-    ra = __shfl_up(ra, 1, 64);  // exclusive
-    rb = __shfl_up(rb, 1, 64);
-    if (lane == 0) ra = rb = 0.0;
-    for (int w = 0; w < workers >> 6; ++w) {
-        if (w == tid >> 6) {
-            ra += totA;
-            rb += totB;
-        }
-        totA += tot[3 * w];
-        totB += tot[3 * w + 1];
-        msum += tot[3 * w + 2];
-    }
-    const double lz = log((double)static_cast<const Real*>(p.zfin)[b]) + totA;
-    // the same total from the beta side: pi . beta'_0. The two agree up to rounding
-    // unless a pass lost mass to underflow (a state whose alpha is below the range
-    // of Real next to the frame's total while its beta is that much above, or the
-    // other way round): such a sequence is flagged, not returned silently wrong
-    const double lz_beta = log((double)static_cast<const Real*>(p.zfin)[p.B + b]) + totB;
-    const bool nonfinite_in = !(msum == msum);
-    const bool dead = !(lz > -INFINITY && lz < INFINITY) || nonfinite_in;
-    const bool lossy = !dead && !(fabs(lz - lz_beta) <= kTotalsAgree);
-    auto scale = [&](const int i) {
-        if (i >= 1) cfac[i] = dead ? (Real)0 : (Real)exp(ra + (totB - rb) - lz);
-    };
-#pragma unroll
-    for (int q = 0; q < kKeep; ++q)
-        if (i0 + q < i1) {
-            scale(i0 + q);
-            ra += ka[q];
-            rb += kb[q];
-        }
-    for (int i = i0 + kKeep; i < i1; ++i) {
-        scale(i);
-        ra += log((double)na[i]);
-        rb += log((double)nb[i]);
-    }
-    if (tid == 0) {
-        int st = 0;
-        if (nonfinite_in) st |= 2;
-        if (dead) st |= 1;
-        if (lossy) st |= 4;
-        const float val = nonfinite_in ? __builtin_nanf("") : (float)(lz + msum);
-        const float out = p.grad_scale * val;
-        if (p.objf_late) {  // k_occ adds them, see add_late_objective
-            p.objf_late[b] = out;
-            p.status_late[b] = st;
-            return;
-        }
-        p.objf[b] = p.accumulate ? p.objf[b] + out : out;
-        if (p.status_out) p.status_out[b] = p.accumulate ? (p.status_out[b] | st) : st;
-    }
-}
-
 template <typename Real, int NSLOT, bool YREP, int LEAK, int NT, bool HYBRID = false,
           bool BIG = false, bool HUBS = false, int BY_STATE = 0>
 __global__ void __launch_bounds__(NT) k_rec(FbParams p)
@@ -2355,10 +1690,6 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
         RecGrouped<Real, LEAK == 1, NSLOT, NT> r;
         if (dir == 0) r.template run<0>(p, sd, od, b);
         else r.template run<1>(p, sd, od, b);
-    } else if constexpr (BY_STATE == 3) {
-        RecLine<LEAK == 1, NSLOT, NT> r;
-        if (dir == 0) r.template run<0>(p, sd, od, b);
-        else r.template run<1>(p, sd, od, b);
     } else if constexpr (BY_STATE == 2) {
         RecShort<Real, NSLOT, NT> r;
         if (dir == 0) r.template run<0>(p, sd, od, b);
@@ -2369,16 +1700,7 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
     } else {
         rec_run<Real, YREP, LEAK == 1, NT, HUBS>(p, sd, od, b, dir, lds_raw);
     }
-    // The workgroup that finishes a sequence second (alpha or beta) computes its
-    // scales: no launch of their own, and no wait for the other sequences.
-    __threadfence();   // this thread's trellis rows and scalars are visible device-wide
-    __syncthreads();   // ... and so are everybody's; LDS is free from here on
-    int* ticket = reinterpret_cast<int*>(lds_raw);
-    if (threadIdx.x == 0) *ticket = atomicAdd(p.done + b, 1);
-    __syncthreads();
-    if (*ticket != 1) return;  // workgroup-uniform
-    __threadfence();           // read the other workgroup's results from memory
-    scan_sequence<Real>(p, b, lds_raw + 64);
+    finish_sequence<Real>(p, b, lds_raw);
 }
 
 // ---------------------------------------------------------------------------
@@ -3075,21 +2397,11 @@ __global__ void __launch_bounds__(NT) k_occ_states(FbParams p)
 }
 
 // ---- kernel variants ---------------------------------------------------------
-using RecKernel = void (*)(FbParams);
 constexpr int kHybridSlots = 36;
 
-struct RecVariant {
-    int wide, nslot, yrep, leak, max_threads;
-    RecKernel fn;
-    int hybrid = 0;  // 1: hybrid, 2: hybrid with the large LDS map
-    int hubs = 0;    // handles hub slices
-    int grouped = 0; // emission by entered state: 1 RecGrouped, 2 RecShort, 3 RecLine
-};
 #define LFMMI_REC_GROUPED(REAL, WIDE, NSLOT, WB, NT)                                          \
     {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, WB, NT, false, false, false, 1>, \
      0, 0, 1}
-#define LFMMI_REC_LINE(NSLOT, WB, NT) \
-    {0, NSLOT, 0, WB, NT, k_rec<float, NSLOT, false, WB, NT, false, false, false, 3>, 0, 0, 3}
 #define LFMMI_REC_SHORT(REAL, WIDE, NS, NT) \
     {WIDE, NS, 0, 0, NT, k_rec<REAL, NS, false, 0, NT, false, false, false, 2>, 0, 0, 2}
 
@@ -3148,11 +2460,6 @@ const RecVariant kRecVariants[] = {
     LFMMI_REC_GROUPED(float, 0, 32, 1, 1024), LFMMI_REC_GROUPED(float, 0, 36, 1, 1024),
     LFMMI_REC_GROUPED(double, 1, 16, 1, 1024),
     LFMMI_REC_GROUPED(double, 1, 16, 0, 1024),
-    // ... one or two slices per wave
-    LFMMI_REC_LINE(16, 0, 1024), LFMMI_REC_LINE(24, 0, 1024), LFMMI_REC_LINE(32, 0, 1024),
-    LFMMI_REC_LINE(36, 0, 1024), LFMMI_REC_LINE(48, 0, 512),
-    LFMMI_REC_LINE(16, 1, 1024), LFMMI_REC_LINE(24, 1, 1024), LFMMI_REC_LINE(32, 1, 1024),
-    LFMMI_REC_LINE(36, 1, 1024), LFMMI_REC_LINE(48, 1, 512),
     // ... one short slice per wave
     LFMMI_REC_SHORT(float, 0, 4, 512), LFMMI_REC_SHORT(float, 0, 8, 512),
     LFMMI_REC_SHORT(double, 1, 4, 512), LFMMI_REC_SHORT(double, 1, 8, 512),
@@ -3163,7 +2470,6 @@ const RecVariant kRecVariants[] = {
 #undef LFMMI_REC_ROWS
 #undef LFMMI_REC_GROUPED
 #undef LFMMI_REC_SHORT
-#undef LFMMI_REC_LINE
 
 const RecVariant* find_rec(bool wide, int nslot, bool yrep, int leak, int hybrid, bool hubs,
                            int grouped, int threads)
@@ -3200,18 +2506,6 @@ int rec_grouped_slots(bool wide, bool has_wb, int max_wave_slots, int threads)
             best = v.nslot;
     return best;
 }
-
-int rec_line_slots(bool has_wb, int max_wave_slots, int threads)
-{
-    int best = 0;
-    for (const RecVariant& v : kRecVariants)
-        if (v.grouped == 3 && v.leak == (has_wb ? 1 : 0) && v.nslot >= max_wave_slots &&
-            threads <= v.max_threads && (best == 0 || v.nslot < best))
-            best = v.nslot;
-    return best;
-}
-
-int rec_line_max_rows() { return kLineRows; }
 
 int rec_grouped_max_rows(bool wide, int threads)
 {
@@ -3250,13 +2544,18 @@ hipError_t configure_kernels()
         if (e != hipSuccess) return e;
         return attr.sharedSizeBytes == 0 ? hipSuccess : hipErrorInvalidConfiguration;
     };
-    for (const RecVariant& v : kRecVariants) {
+    auto configure = [&](const RecVariant& v) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(v.fn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        if (v.nslot > 0 && (e = no_static_lds(reinterpret_cast<const void*>(v.fn))) != hipSuccess)
-            return e;
-    }
+        if (e == hipSuccess && v.nslot > 0) e = no_static_lds(reinterpret_cast<const void*>(v.fn));
+        return e;
+    };
+    for (const RecVariant& v : kRecVariants)
+        if (const hipError_t e = configure(v); e != hipSuccess) return e;
+    int lines = 0;
+    const RecVariant* line = line_variants(&lines);
+    for (int i = 0; i < lines; ++i)
+        if (const hipError_t e = configure(line[i]); e != hipSuccess) return e;
     const void* fns[] = {reinterpret_cast<const void*>(k_occ<float>),
                          reinterpret_cast<const void*>(k_occ<double>),
                          reinterpret_cast<const void*>(k_occ_states<float, 1, 512>),
@@ -3355,9 +2654,11 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
     hipError_t e;
     const bool wide = sizeof(Real) == 8;
     const RecVariant* rv =
-        find_rec(wide, shape.rec_nslot, shape.rec_yrep != 0, shape.rec_leak,
-                 shape.rec_hybrid, shape.rec_hubs != 0,
-                 shape.rec_short ? 2 : (shape.rec_line ? 3 : shape.rec_grouped), shape.rec_threads);
+        shape.rec_line ? find_line(shape.rec_line == 1, shape.rec_yrep != 0, shape.rec_leak, p.P,
+                                   shape.rec_nslot, shape.rec_threads)
+                       : find_rec(wide, shape.rec_nslot, shape.rec_yrep != 0, shape.rec_leak,
+                                  shape.rec_hybrid, shape.rec_hubs != 0,
+                                  shape.rec_short ? 2 : shape.rec_grouped, shape.rec_threads);
     if (!rv || shape.rec_threads > rv->max_threads) return hipErrorInvalidConfiguration;
     if (bk.n > 1 && (e = hipEventRecord(bk.fork, stream)) != hipSuccess) return e;
 
@@ -3366,14 +2667,14 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
         // enough threads to stage one emission row in the variant's passes; waves
         // beyond the graph's own hold no arcs
         const int units = shape.rec_yrep ? p.P * 8 : p.P;
-        const int passes = stage_passes(shape.rec_yrep != 0, rv->max_threads);
+        const int passes = rv->ypass ? rv->ypass : stage_passes(shape.rec_yrep != 0, rv->max_threads);
         const int need = ((units + passes - 1) / passes + 63) / 64 * 64;
         rec_threads = std::max(rec_threads, need);
         if (rec_threads > rv->max_threads) return hipErrorInvalidConfiguration;
     }
     // at least the scan's scratch
     const size_t rec_lds =
-        std::max<size_t>(shape.rec_line ? line_lds_bytes()
+        std::max<size_t>(shape.rec_line ? line_lds_bytes(*rv)
                          : shape.rec_nslot > 0
                              ? reg_lds_bytes()
                              : rec_lds_bytes(p.lds_rows, p.P, wide, shape.rec_yrep != 0),

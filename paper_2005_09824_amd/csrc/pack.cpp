@@ -923,15 +923,16 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
         return hub;
     };
     std::vector<uint8_t> hub_f = hubs_of(indeg), hub_b = hubs_of(outdeg);
-    // Where the emission of an arc is that of the state it enters, waves own at most two slices
-    // where that leaves their slots in registers: the straight-line recursion asks for it.
+    // Waves own at most two slices, the narrower one first, where that leaves their slots in the
+    // registers of the straight-line recursion.
     std::vector<int32_t> entered_pdf;
     const bool by_state = pdf_of_entered_state(g, &entered_pdf);
     auto arranged = [&](const std::vector<int32_t>& deg, const std::vector<uint8_t>& hub) {
         Arrangement ar = arrange(deg, rec_waves, closing, &hub);
-        if (by_state && ar.num_slices <= 2 * ar.num_waves) {
+        if (tune.two_slices && ar.num_slices <= 2 * ar.num_waves) {
             Arrangement two = arrange(deg, rec_waves, closing, &hub, 2);
-            if (two.max_wave_slots <= std::max(ar.max_wave_slots, kTwoSliceSlots)) return two;
+            const int32_t most = by_state ? kLineSlotsByState : kLineSlotsByArc;
+            if (two.max_wave_slots <= std::max(ar.max_wave_slots, most)) return two;
         }
         return ar;
     };

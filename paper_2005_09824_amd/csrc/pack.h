@@ -21,7 +21,8 @@ namespace lfmmi {
 constexpr int kLanes = 64;
 constexpr int kHeavyPdfRows = 24;  // OCC: more rows than this and a wave adds them up
 constexpr int kMaxWaves = 16;
-constexpr int kTwoSliceSlots = 36;  // what a wave of the straight-line recursion holds (RecLine)
+// what a wave of the straight-line recursion holds
+constexpr int kLineSlotsByState = 36, kLineSlotsByArc = 28;
 constexpr int kMaxIndex = 16384;  // x / y index * 4 must fit 16 bits
 
 struct Ordering {
@@ -111,6 +112,7 @@ struct PackTuning {
     bool order_slots = true;          // order each row's arcs over its slots
     bool emission_conflicts = true;   // the emission gather can conflict (row not replicated)
     bool hub_slices = true;           // rows with far more arcs than the others get a slice each
+    bool two_slices = true;           // at most two slices a wave where that costs no registers
     bool deal_occ = true;             // OCC ordering: arcs dealt to rows and slots jointly
 };
 
