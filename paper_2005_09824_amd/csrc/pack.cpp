@@ -1101,9 +1101,14 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
         // few: k slices per wave, i.e. waves * 64 * k rows, handed to the pdfs one
         // at a time, always to the pdf whose pieces are longest at that moment. A
         // pdf's pieces then differ by at most one arc, and sorting rows by length
-        // leaves little padding. k: the smallest whose fullest wave is within 8 %
-        // of the best over all k tried (rows cost LDS: fewer of them can let a
-        // second workgroup share the compute unit).
+        // leaves little padding. k: the least slots of the fullest wave, a slice counted as
+        // kSliceCost slots: its sums are stored, added up again and take LDS, of which a second
+        // workgroup of the compute unit needs half. By the fullest wave alone (within 8 %) 1,000
+        // states, 10,000 arcs, 200 pdfs were cut into 80 slices of two slots, not 8 of 26: a call
+        // of 32 sequences of 400 frames 858 us, 475 now; 500 states, 6,000 arcs, 150 pdfs, B = 128
+        // 1,001 / 589; 2,000 states, 20,000 arcs, 600 pdfs, B = 64 988 / 803 (24 slices, 16 now;
+        // with 1 or 2 slots a slice still 24); 300 states, 84 pdfs 325 / 278.
+        constexpr int64_t kSliceCost = 4;
         const int waves_o = std::max(1, occ_waves);
         int64_t nonempty = 0;
         for (int32_t d = 0; d < num_pdfs; ++d) nonempty += count[d] > 0;
@@ -1154,8 +1159,14 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
                 if (k * per_k >= A) break;  // one arc per piece
             }
             int64_t k_pick = k_min;
-            for (const auto& t : tried)
-                if ((double)t.second <= 1.08 * (double)best) { k_pick = t.first; break; }
+            int64_t least = INT64_MAX;
+            for (const auto& t : tried) {
+                const int64_t cost = t.second + kSliceCost * t.first;
+                if (cost < least) {
+                    least = cost;
+                    k_pick = t.first;
+                }
+            }
             allot(k_pick * per_k, &pieces);
             lengths_of(pieces, &len, &pdf_of);
         }

@@ -420,3 +420,14 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+# few rows for the occupancies: each row's sum is stored and added up again in every frame
+@pytest.mark.parametrize("S,k,P,slices", [(1000, 9, 200, 8), (500, 11, 150, 8), (2000, 9, 84, 8), (300, 9, 84, 6), (100, 5, 10, 2)])
+def test_occupancy_rows_are_few(S, k, P, slices):
+    g = workloads.random_den_graph(np.random.default_rng(3), S, k, P, 0.5)
+    h = binding.lfmmi_graph_pack(g)
+    o = binding.lfmmi_graph_ordering_copy(h, 0, binding.ORD_OCC)
+    h.close()
+    assert o["slices"] == slices
+    assert np.count_nonzero(o["w"]) == len(g["src"])
