@@ -7,7 +7,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblfmmi.so")
-SOURCES = ["kernels.hip", "line.hip", "api.cpp", "pack.cpp"]
+SOURCES = ["kernels.hip", "line.hip", "hybrid.hip", "api.cpp", "pack.cpp"]
 HEADERS = ["kernels.h", "device.h", "pack.h", "microbench.hip", os.path.join("..", "..", "include", "lfmmi.h")]
 
 FLAGS = [

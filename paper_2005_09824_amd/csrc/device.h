@@ -370,7 +370,7 @@ struct RecVariant {
     int hybrid = 0;  // 1: hybrid, 2: hybrid with the large LDS map
     int hubs = 0;    // handles hub slices
     int grouped = 0; // emission by entered state: 1 RecGrouped, 2 RecShort, 3 RecLine; 4 RecLineArc
-    int ypass = 0;   // RecLineArc: staging passes
+    int ypass = 0;   // RecLineArc, RecHybrid: staging passes
 };
 // The straight-line recursion (line.hip): its variants, their number in *n; the one for a kind of
 // graph; the LDS one takes.
@@ -378,5 +378,9 @@ const RecVariant* line_variants(int* n);
 const RecVariant* find_line(bool by_state, bool yrep, int leak, int num_pdfs, int max_wave_slots,
                             int threads);
 size_t line_lds_bytes(const RecVariant& v);
+// The same for the hybrid recursion without hub slices (hybrid.hip); map 1: 32 KB state vectors, 2: 48 KB.
+constexpr int kHybridSlots = 36;  // resident slots of a wave
+const RecVariant* hybrid_variants(int* n);
+const RecVariant* find_hybrid(bool yrep, int leak, int num_pdfs, int map);
 
 }  // namespace lfmmi

@@ -2397,8 +2397,6 @@ __global__ void __launch_bounds__(NT) k_occ_states(FbParams p)
 }
 
 // ---- kernel variants ---------------------------------------------------------
-constexpr int kHybridSlots = 36;
-
 #define LFMMI_REC_GROUPED(REAL, WIDE, NSLOT, WB, NT)                                          \
     {WIDE, NSLOT, 0, WB, NT, k_rec<REAL, NSLOT, false, WB, NT, false, false, false, 1>, \
      0, 0, 1}
@@ -2440,15 +2438,8 @@ const RecVariant kRecVariants[] = {
     LFMMI_REC(double, 1, 16, 0, 1024), LFMMI_REC(double, 1, 32, 0, 512),
     LFMMI_REC_ROWS(16, 1024), LFMMI_REC_ROWS(20, 1024), LFMMI_REC_ROWS(24, 1024),
     LFMMI_REC_ROWS(26, 1024), LFMMI_REC_ROWS(36, 768), LFMMI_REC_ROWS(48, 512),
-    {0, kHybridSlots, 0, 2, 1024, k_rec<float, kHybridSlots, false, 2, 1024, true>, 1},
-    {0, kHybridSlots, 1, 2, 1024, k_rec<float, kHybridSlots, true, 2, 1024, true>, 1},
-    {0, kHybridSlots, 0, 2, 1024, k_rec<float, kHybridSlots, false, 2, 1024, true, true>, 2},
-    // hybrid: kHybridSlots slots of a wave in registers, its other slices streamed
-    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true>, 1},
-    {0, kHybridSlots, 1, 0, 1024, k_rec<float, kHybridSlots, true, 0, 1024, true>, 1},
-    // ... with the LDS map for up to 12288 states
-    {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true, true>, 2},
-    // ... and the three for graphs with hub slices
+    // hybrid (kHybridSlots slots of a wave in registers, its other slices streamed), graphs with hub
+    // slices; the others: hybrid.hip
     // (with a replicated emission row the hub code would spill a register: plain rows)
     {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true, false, true>, 1, 1},
     {0, kHybridSlots, 0, 0, 1024, k_rec<float, kHybridSlots, false, 0, 1024, true, true, true>, 2, 1},
@@ -2526,6 +2517,7 @@ uint32_t rec_zero_word(int hybrid) { return hybrid == 2 ? 16380u : kRegYZero; }
 
 int rec_hybrid_slots(bool wide, int leak, bool yrep, bool hubs, int map)
 {
+    if (!hubs) return !wide && leak != 1 && find_hybrid(yrep, leak, 1, map) ? kHybridSlots : 0;
     for (const RecVariant& v : kRecVariants)
         if (v.hybrid == map && v.wide == (wide ? 1 : 0) && v.leak == leak &&
             v.yrep == (yrep ? 1 : 0) && v.hubs == (hubs ? 1 : 0))
@@ -2552,10 +2544,12 @@ hipError_t configure_kernels()
     };
     for (const RecVariant& v : kRecVariants)
         if (const hipError_t e = configure(v); e != hipSuccess) return e;
-    int lines = 0;
-    const RecVariant* line = line_variants(&lines);
-    for (int i = 0; i < lines; ++i)
-        if (const hipError_t e = configure(line[i]); e != hipSuccess) return e;
+    for (auto more : {&line_variants, &hybrid_variants}) {
+        int count = 0;
+        const RecVariant* v = more(&count);
+        for (int i = 0; i < count; ++i)
+            if (const hipError_t e = configure(v[i]); e != hipSuccess) return e;
+    }
     const void* fns[] = {reinterpret_cast<const void*>(k_occ<float>),
                          reinterpret_cast<const void*>(k_occ<double>),
                          reinterpret_cast<const void*>(k_occ_states<float, 1, 512>),
@@ -2656,6 +2650,8 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
     const RecVariant* rv =
         shape.rec_line ? find_line(shape.rec_line == 1, shape.rec_yrep != 0, shape.rec_leak, p.P,
                                    shape.rec_nslot, shape.rec_threads)
+        : shape.rec_hybrid && !shape.rec_hubs
+            ? find_hybrid(shape.rec_yrep != 0, shape.rec_leak, p.P, shape.rec_hybrid)
                        : find_rec(wide, shape.rec_nslot, shape.rec_yrep != 0, shape.rec_leak,
                                   shape.rec_hybrid, shape.rec_hubs != 0,
                                   shape.rec_short ? 2 : shape.rec_grouped, shape.rec_threads);

@@ -84,3 +84,24 @@ def test_straight_line_recursion_by_arc_of_graphs_of_different_sizes():
         lz, gamma = oracle.forward_backward(g, x[b:b + 1], lengths[b:b + 1], 1e-4)
         assert abs(objf[b].item() - lz[0]) <= 1e-4 * max(abs(lz[0]), 1.0)
         assert np.abs(grad[b].cpu().numpy() - gamma[0]).max() <= 1e-4
+
+
+# the hybrid recursion: one and two staging passes of a replicated emission row, plain rows, both
+# LDS maps, waves that stream a few pairs and many; uniform and other initial probabilities
+@pytest.mark.parametrize("S,k,P,init", [
+    (2100, 17, 40, "uniform"), (2100, 24, 128, "varied"), (3000, 13, 129, "uniform"), (2500, 15, 255, "varied"),
+    (2500, 16, 256, "uniform"), (2200, 22, 1500, "varied"), (8300, 5, 300, "uniform"), (8300, 5, 3072, "varied"),
+])
+def test_hybrid_recursion_by_arc(S, k, P, init):
+    rng = np.random.default_rng(S + P)
+    g = workloads.random_den_graph(rng, S, k, P, 0.5)
+    if init == "varied":
+        p = rng.uniform(0.1, 1.0, S)
+        g["init_prob"] = (p / p.sum()).astype(np.float32)
+    h = binding.lfmmi_graph_pack(g)
+    info = binding.lfmmi_graph_ordering_info(h, 0, 0)
+    h.close()
+    assert info["register_slots"] == 36 < info["max_wave_slots"]
+    assert info["emission_replicated"] == (1 if P <= 255 else 0)
+    assert info["lds_vector_rows"] == (8192 if S <= 8192 else 12288)
+    parity(g, LENGTHS[3:], 66, 1e-4)
