@@ -804,6 +804,7 @@ void fill_params(lfmmi_graph* h, const CallLayout& lay, unsigned char* ws,
     p.lds_rows_occ_b = h->max_rows_b;
     p.lds_rows_occ = h->max_rows_occ;
     p.accumulate = accumulate ? 1 : 0;
+    p.one_graph = h->num_graphs == 1 ? 1 : 0;
     p.alpha_over_pi = h->over_pi ? 1 : 0;
     p.leak = leak;
     p.grad_scale = grad_scale;
@@ -1233,7 +1234,8 @@ lfmmi_status lfmmi_forward_backward_static(const lfmmi_graph* graph, const float
     hipError_t e;
     // descriptors and launch order are written on the device, from the lengths
     // passed as a kernel argument (no host-to-device copy to stage)
-    if ((e = launch_describe(p, lengths, h->num_graphs, stream)) != hipSuccess)
+    shape.emitted = 1;
+    if ((e = launch_describe_emit(p, lengths, h->num_graphs, stream)) != hipSuccess)
         return fail_hip(e, "kernel launch");
     if ((e = launch_forward_backward(p, shape, stream, nullptr, bk)) != hipSuccess)
         return fail_hip(e, "kernel launch");

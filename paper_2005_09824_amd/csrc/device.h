@@ -344,19 +344,43 @@ __device__ void scan_sequence(const FbParams& p, const int b, unsigned char* scr
     }
 }
 
+// What a workgroup of a recursion kernel works on. Entries 2i, 2i + 1 of the launch order are the
+// two directions of a sequence; a handle's only graph is read without a wait for the sequence.
+struct RecWork {
+    int b, dir;
+    SeqDesc sd;
+    OrdDesc od;
+};
+__device__ __forceinline__ RecWork rec_work(const FbParams& p)
+{
+    RecWork w;
+    w.dir = blockIdx.x & 1;
+    if (p.one_graph) w.od = p.g.ords[w.dir];
+    w.b = p.order[2 * p.seq_first + blockIdx.x] >> 1;
+    w.sd = p.seqs[w.b];
+    if (!p.one_graph) w.od = p.g.ords[w.sd.graph * 3 + w.dir];
+    return w;
+}
+
 // At the end of a recursion kernel, by every thread.
 template <typename Real>
 __device__ __forceinline__ void finish_sequence(const FbParams& p, const int b, unsigned char* lds_raw)
 {
     // The workgroup that finishes a sequence second (alpha or beta) computes its
     // scales: no launch of their own, and no wait for the other sequences.
-    __threadfence();   // this thread's trellis rows and scalars are visible device-wide
-    __syncthreads();   // ... and so are everybody's; LDS is free from here on
+    // Every wave waits for its trellis rows and scalars to have reached the L2; one thread's fences
+    // on either side of the ticket then make them visible device-wide and the other workgroup's
+    // visible here (fences by every wave wrote back and invalidated the caches once per wave).
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();  // ... LDS is free from here on
     int* ticket = reinterpret_cast<int*>(lds_raw);
-    if (threadIdx.x == 0) *ticket = atomicAdd(p.done + b, 1);
+    if (threadIdx.x == 0) {
+        __threadfence();
+        *ticket = atomicAdd(p.done + b, 1);
+        __threadfence();
+    }
     __syncthreads();
     if (*ticket != 1) return;  // workgroup-uniform
-    __threadfence();           // read the other workgroup's results from memory
     scan_sequence<Real>(p, b, lds_raw + 64);
 }
 

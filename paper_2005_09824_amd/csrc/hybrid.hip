@@ -404,10 +404,10 @@ template <bool YREP, int YPASS, int LEAK, int NSLOT, bool BIG>
 __global__ void __launch_bounds__(1024) k_rec_hybrid(FbParams p)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int code = p.order[2 * p.seq_first + blockIdx.x];
-    const int b = code >> 1, dir = code & 1;
-    const SeqDesc sd = p.seqs[b];
-    const OrdDesc od = p.g.ords[sd.graph * 3 + dir];
+    const RecWork work = rec_work(p);
+    const int b = work.b, dir = work.dir;
+    const SeqDesc& sd = work.sd;
+    const OrdDesc& od = work.od;
     RecHybrid<YREP, YPASS, LEAK, NSLOT, BIG> r;
     r.run(p, sd, od, b, dir);
     finish_sequence<float>(p, b, lds_raw);

@@ -94,6 +94,7 @@ struct FbParams {
     int32_t wide;           // 1: state vectors, trellis and scales in fp64
     int32_t emis_ready;     // 1: emis / rowmax already hold this batch's values (the other
                             // pass of a full-loss call computed them): k_emit skips them
+    int32_t one_graph;      // 1: the handle holds one graph, which all sequences share
     int32_t alpha_over_pi;  // 1: alpha is kept divided by the initial probabilities
     float leak, grad_scale;
 };
@@ -108,6 +109,7 @@ struct LaunchShape {
     int profile_rec_only;  // of the four events per bucket record only those around k_rec
     int rec_hybrid;    // 1: only the first slots of a wave are register-resident;
                        // 2: the same, with the LDS map for up to 12288 states
+    int emitted = 0;      // the emission rows have been launched already
     int rec_grouped = 0;  // arcs take the emission of the entered state: no emission gather
     int rec_short = 0;    // ... and every wave owns one short slice (RecShort)
     int rec_line = 0;     // waves own one or two slices: 1 RecLine (as rec_grouped), 2 RecLineArc
@@ -149,10 +151,10 @@ constexpr size_t kStaticWorkspaceBytes = (size_t)64 << 20;
 constexpr int kStaticMaxBatch = 256;
 hipError_t find_static_workspace(int device);
 void* static_workspace(int device);
-// Writes the per-sequence descriptors and the launch order of a call (p.seqs,
-// p.order, both inside the workspace) on the device, from the host array
-// lengths[p.B] passed by value; p.B <= kStaticMaxBatch.
-hipError_t launch_describe(const FbParams& p, const int32_t* lengths, int num_graphs,
+// Writes the per-sequence descriptors and the launch order of a call (p.seqs, p.order, both inside
+// the workspace) on the device, from the host array lengths[p.B] passed by value; p.B <=
+// kStaticMaxBatch. In the same launch the emission rows: LaunchShape::emitted for what follows.
+hipError_t launch_describe_emit(const FbParams& p, const int32_t* lengths, int num_graphs,
                            hipStream_t stream);
 // Dynamic LDS the recursion / occupancy kernels need.
 size_t rec_lds_bytes(int lds_rows, int P, bool wide, bool yrep);

@@ -27,15 +27,14 @@ namespace {
 // Emission: one wave per frame row. A row holding NaN or +inf (or nothing but
 // -inf) is flagged by a NaN row maximum and an all-zero emission row.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_emit(FbParams p)
+__device__ __forceinline__ void emit_rows(const FbParams& p, const int b, const int T)
 {
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int b = p.order[2 * (p.seq_first + blockIdx.y)] >> 1;
     if (blockIdx.x == 0 && threadIdx.x == 0) p.done[b] = 0;  // see k_rec
     if (t >= p.T) return;
     const size_t at = ((size_t)b * p.T + t) * p.P;
-    if (t >= p.seqs[b].T) {  // a padding frame: its gradient row is zero
+    if (t >= T) {  // a padding frame: its gradient row is zero
         if (!p.accumulate)
             for (int d = lane; d < p.P; d += 64) p.grad[at + d] = 0.f;
         return;
@@ -54,6 +53,12 @@ __global__ void __launch_bounds__(256) k_emit(FbParams p)
     bad = __any(bad) || !(fabsf(m) < INFINITY);
     for (int d = lane; d < p.P; d += 64) e[d] = bad ? 0.f : expf(x[d] - m);
     if (lane == 0) p.rowmax[(size_t)b * p.T + t] = bad ? __builtin_nanf("") : m;
+}
+
+__global__ void __launch_bounds__(256) k_emit(FbParams p)
+{
+    const int b = p.order[2 * (p.seq_first + blockIdx.y)] >> 1;
+    emit_rows(p, b, p.seqs[b].T);
 }
 
 // ---------------------------------------------------------------------------
@@ -1678,13 +1683,10 @@ template <typename Real, int NSLOT, bool YREP, int LEAK, int NT, bool HYBRID = f
 __global__ void __launch_bounds__(NT) k_rec(FbParams p)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int code = p.order[2 * p.seq_first + blockIdx.x];
-    const int b = code >> 1, dir = code & 1;
-#ifdef LFMMI_ONLY_DIR  // timing builds only: one of the two recursions (results are not valid)
-    if (dir != LFMMI_ONLY_DIR) return;
-#endif
-    const SeqDesc sd = p.seqs[b];
-    const OrdDesc od = p.g.ords[sd.graph * 3 + dir];
+    const RecWork work = rec_work(p);
+    const int b = work.b, dir = work.dir;
+    const SeqDesc& sd = work.sd;
+    const OrdDesc& od = work.od;
     if constexpr (BY_STATE == 1) {
         static_assert(NSLOT > 0 && !YREP && !HYBRID && !BIG && !HUBS, "grouped: resident arcs only");
         RecGrouped<Real, LEAK == 1, NSLOT, NT> r;
@@ -2690,7 +2692,7 @@ static hipError_t launch_typed(const FbParams& p, const LaunchShape& shape, hipS
         if (e != hipSuccess) return e; \
     }
         LFMMI_EVQ(0)
-        {  // also when T == 0: it resets the per-sequence tickets of k_rec
+        if (!shape.emitted) {  // also when T == 0: it resets the per-sequence tickets of k_rec
             dim3 grid(std::max(1, (p.T + 3) / 4), nb);
             hipLaunchKernelGGL(k_emit, grid, dim3(256), 0, on, pq);
             if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -2766,12 +2768,19 @@ struct StaticLengths {
     int32_t T[kStaticMaxBatch];
 };
 
-// One workgroup: what the host writes for the allocating entry point, computed
-// here. Sequences are launched longest first (by frames times arc slots).
-__global__ void __launch_bounds__(kStaticMaxBatch) k_describe(FbParams p, StaticLengths len,
-                                                              int num_graphs)
+// The emission rows of all sequences, and in one workgroup more (blockIdx.y == B) what the host
+// writes for the allocating entry point: descriptors, and the launch order, longest first (by frames
+// times arc slots). One launch: on a toy graph (2 sequences of 30 frames) a launch of its own for the
+// descriptors took 3 of the call's 28 us.
+__global__ void __launch_bounds__(256) k_describe_emit(FbParams p, StaticLengths len, int num_graphs)
 {
+    static_assert(kStaticMaxBatch == 256, "one thread a sequence");
     __shared__ long long work[kStaticMaxBatch];
+    if ((int)blockIdx.y < p.B) {
+        emit_rows(p, blockIdx.y, len.T[blockIdx.y]);
+        return;
+    }
+    if (blockIdx.x > 0) return;
     SeqDesc* seqs = const_cast<SeqDesc*>(p.seqs);
     int32_t* order = const_cast<int32_t*>(p.order);
     const int b = threadIdx.x;
@@ -2827,13 +2836,14 @@ void* static_workspace(int device)
     return device >= 0 && device < kMaxDevices ? g_scratch_ptr[device] : nullptr;
 }
 
-hipError_t launch_describe(const FbParams& p, const int32_t* lengths, int num_graphs,
+hipError_t launch_describe_emit(const FbParams& p, const int32_t* lengths, int num_graphs,
                            hipStream_t stream)
 {
     if (p.B < 1 || p.B > kStaticMaxBatch) return hipErrorInvalidValue;
     StaticLengths len;
     for (int b = 0; b < kStaticMaxBatch; ++b) len.T[b] = b < p.B ? lengths[b] : 0;
-    hipLaunchKernelGGL(k_describe, dim3(1), dim3(kStaticMaxBatch), 0, stream, p, len, num_graphs);
+    const dim3 grid(std::max(1, (p.T + 3) / 4), p.B + 1);
+    hipLaunchKernelGGL(k_describe_emit, grid, dim3(256), 0, stream, p, len, num_graphs);
     return hipGetLastError();
 }
 
