@@ -355,10 +355,11 @@ __device__ __forceinline__ RecWork rec_work(const FbParams& p)
 {
     RecWork w;
     w.dir = blockIdx.x & 1;
-    if (p.one_graph) w.od = p.g.ords[w.dir];
+    int graph = 0;
+    if (!p.one_graph) graph = p.seqs[p.order[2 * p.seq_first + blockIdx.x] >> 1].graph;
+    w.od = p.g.ords[graph * 3 + w.dir];
     w.b = p.order[2 * p.seq_first + blockIdx.x] >> 1;
     w.sd = p.seqs[w.b];
-    if (!p.one_graph) w.od = p.g.ords[w.sd.graph * 3 + w.dir];
     return w;
 }
 

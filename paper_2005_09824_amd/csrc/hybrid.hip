@@ -76,7 +76,11 @@ struct RecHybrid {
     __device__ __forceinline__ void load_y()
     {
 #pragma unroll
-        for (int i = 0; i < YPASS; ++i) yreg[i] = *(global_in_t)(e2 + here(ysrc[i]));
+        for (int i = 0; i < YPASS; ++i) {
+            // (two passes of copies: out of the other address, or two registers too many)
+            if constexpr (YREP && YPASS > 1) yreg[i] = *(global_in_t)(e2 + ((here(ydst[i]) >> 7) << 2));
+            else yreg[i] = *(global_in_t)(e2 + here(ysrc[i]));
+        }
     }
     template <uint32_t BUF>
     __device__ __forceinline__ void store_y()
@@ -406,8 +410,8 @@ __global__ void __launch_bounds__(1024) k_rec_hybrid(FbParams p)
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const RecWork work = rec_work(p);
     const int b = work.b, dir = work.dir;
-    const SeqDesc& sd = work.sd;
-    const OrdDesc& od = work.od;
+    const SeqDesc sd = work.sd;
+    const OrdDesc od = work.od;
     RecHybrid<YREP, YPASS, LEAK, NSLOT, BIG> r;
     r.run(p, sd, od, b, dir);
     finish_sequence<float>(p, b, lds_raw);

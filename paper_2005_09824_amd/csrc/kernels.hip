@@ -355,7 +355,7 @@ __host__ __device__ constexpr int stage_passes(bool yrep, int nt)
 
 // HYBRID: a wave keeps in registers only the first of its slices that fit NSLOT
 // slots and streams the records of the others from L2 every frame (graphs too
-// large for the registers: less record traffic than streaming everything).
+// large for the registers, with hub slices; those without: hybrid.hip).
 // BIG: state vectors of 48 KB and emission rows of 16 KB (graphs of up to 12288
 // states) instead of 32 KB each.
 // HUBS: the graph has hub slices (64 lanes that share one row's arcs, added up where
@@ -365,17 +365,17 @@ __host__ __device__ constexpr int stage_passes(bool yrep, int nt)
 // the leak target is 1 on every state in both directions, so that arcs need no factor of
 // their own: an arc of alpha carries w * pi[from] / pi[to] (folded in at upload), the total
 // s = sum pi u takes a row's pi from its closing slot, and s is also what a step is scaled by.
-// Two registers and a multiply-add less per slot than 1, so the hybrid has room for it: 5,000
-// states, 50,000 arcs, B = 32, 5.88 -> 1.82 ms a call (1 had to stream every arc); 1,237
-// states in registers, B = 17: 289 -> 238 us. 1 stays for fp64, for hub slices, for graphs that
-// leave the range of fp32 that way and where nothing stays in registers.
+// Two registers and a multiply-add less per slot than 1, so the hybrid (hybrid.hip) has room for
+// it: 5,000 states, 50,000 arcs, B = 32, 5.88 -> 1.68 ms a call (1 had to stream every arc). 1
+// stays for fp64, for hub slices, for graphs that leave the range of fp32 that way and where
+// nothing stays in registers.
 template <typename Real, bool YREP, int LEAK, int NSLOT, int NT, bool HYBRID = false,
           bool BIG = false, bool HUBS = false>
 struct RecRegs {
     static constexpr bool HAS_WB = LEAK == 1;
     static constexpr bool ROWS = LEAK == 2;
     static_assert(!ROWS || !HUBS, "row weights: no hub slices");
-    static_assert(!HYBRID || (!HAS_WB && sizeof(Real) == 4), "hybrid: fp32, no factors per arc");
+    static_assert(!HYBRID || (!HAS_WB && !ROWS && HUBS && sizeof(Real) == 4), "hybrid: fp32, hub slices");
     static_assert(!BIG || (HYBRID && !YREP), "the large map: hybrid, plain emission rows");
     // this variant's LDS map (the names hide the 32 KB map's constants)
     static constexpr uint32_t kRegX1 = BIG ? 49152u : lfmmi::kRegX1;
@@ -681,7 +681,7 @@ struct RecRegs {
                                                : so[at + 1];
                 };
                 int o1 = slice_end(sl);
-                auto close = [&](const uint32_t closing_w) {  // w of the slice's last slot
+                auto close = [&]() {
                     const bool hub_slice =
                         HUBS && (sl - sl_stream < 64 ? ((hub_bits >> (sl - sl_stream)) & 1) != 0
                                                      : hub[sl] != 0);
@@ -694,7 +694,7 @@ struct RecRegs {
                     const uint32_t at = (uint32_t)(sl * 64 + lane) * kRB;
                     lds_st(xn + at, v);
                     *reinterpret_cast<Real*>(tr + at) = v;
-                    n += ROWS ? (Real)__uint_as_float(closing_w) * v : v;
+                    n += v;
                     a1 = 0;
                     a2 = 0;
                     ++sl;
@@ -722,12 +722,12 @@ struct RecRegs {
                     add_arc(__uint_as_float(qa.y), e0, x0, a1, a2);
                     add_arc(__uint_as_float(qa.w), e1, x1, a1, a2);
                     i += 2;
-                    if (i == o1) close(qa.w);
+                    if (i == o1) close();
                     if (b_valid) {
                         add_arc(__uint_as_float(qb.y), e2, x2, a1, a2);
                         add_arc(__uint_as_float(qb.w), e3, x3, a1, a2);
                         i += 2;
-                        if (i == o1) close(qb.w);
+                        if (i == o1) close();
                     }
                 };
                 uint4 q0 = pair_at(0);
@@ -1685,8 +1685,8 @@ __global__ void __launch_bounds__(NT) k_rec(FbParams p)
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const RecWork work = rec_work(p);
     const int b = work.b, dir = work.dir;
-    const SeqDesc& sd = work.sd;
-    const OrdDesc& od = work.od;
+    const SeqDesc sd = work.sd;
+    const OrdDesc od = work.od;
     if constexpr (BY_STATE == 1) {
         static_assert(NSLOT > 0 && !YREP && !HYBRID && !BIG && !HUBS, "grouped: resident arcs only");
         RecGrouped<Real, LEAK == 1, NSLOT, NT> r;

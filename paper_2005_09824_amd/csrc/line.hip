@@ -671,8 +671,8 @@ __global__ void __launch_bounds__(NT) k_rec_line(FbParams p)
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const RecWork work = rec_work(p);
     const int b = work.b, dir = work.dir;
-    const SeqDesc& sd = work.sd;
-    const OrdDesc& od = work.od;
+    const SeqDesc sd = work.sd;
+    const OrdDesc od = work.od;
     RecLine<HAS_WB, NSLOT, NT> r;
     if (dir == 0) r.template run<0>(p, sd, od, b);
     else r.template run<1>(p, sd, od, b);
@@ -685,8 +685,8 @@ __global__ void __launch_bounds__(NT) k_rec_line_arc(FbParams p)
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const RecWork work = rec_work(p);
     const int b = work.b, dir = work.dir;
-    const SeqDesc& sd = work.sd;
-    const OrdDesc& od = work.od;
+    const SeqDesc sd = work.sd;
+    const OrdDesc od = work.od;
     RecLineArc<YREP, YPASS, LEAK, NSLOT, NT> r;
     r.run(p, sd, od, b, dir);
     finish_sequence<float>(p, b, lds_raw);
