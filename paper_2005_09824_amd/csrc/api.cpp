@@ -367,26 +367,47 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
                         if (h->packed[g].ord[o].num_slices > waves) return 0;
                 return rec_short_slots(h->wide, max_slots - (h->has_wb ? 1 : 0), waves * kLanes);
             };
-            h->occ_states = st == LFMMI_OK && env_int("LFMMI_GROUPED", 1) != 0;
-            for (int32_t g = 0; g < n && h->occ_states; ++g) h->occ_states = h->packed[g].pdf_by_dst;
-            int gslots = st == LFMMI_OK ? short_slots() : 0;
-            h->rec_short = gslots > 0;
-            if (st == LFMMI_OK && gslots == 0) {
-                gslots = line_slots(true);
-                h->rec_line = gslots > 0 ? 1 : 0;
+            int gslots = 0;
+            auto choose = [&]() {
+                h->occ_states = env_int("LFMMI_GROUPED", 1) != 0;
+                for (int32_t g = 0; g < n && h->occ_states; ++g) h->occ_states = h->packed[g].pdf_by_dst;
+                h->rec_line = 0;
+                gslots = short_slots();
+                h->rec_short = gslots > 0;
+                if (gslots == 0) {
+                    gslots = line_slots(true);
+                    h->rec_line = gslots > 0 ? 1 : 0;
+                }
+                if (gslots == 0) gslots = grouped_slots();
+                h->rec_grouped = gslots > 0 && !h->rec_short;
+                // Initial probabilities that differ: state values divided by them need no leak
+                // factor per arc and take every variant that a uniform one takes, but have to leave
+                // every weight an ordinary fp32 number (see leak_by_rows).
+                h->over_pi = gslots == 0 && h->has_wb && !h->wide && !h->rec_hubs &&
+                             env_int("LFMMI_OVER_PI", 1) != 0;
+                for (int32_t g = 0; g < n && h->over_pi; ++g) h->over_pi = leak_by_rows(arcs_of(g));
+                if (gslots == 0) {
+                    gslots = line_slots(false);
+                    if (gslots > 0) h->rec_line = 2;
+                }
+            };
+            if (st == LFMMI_OK) choose();
+            // Graphs dealt to waves for the straight line that cannot run it after all (another
+            // graph of the handle cannot, more pdfs than it stages, a leak factor per arc): once
+            // more without, as their fullest wave holds more slots that way than it has to. Dealt in
+            // twos / freely, a call of 32 sequences of 400 frames: 1,600 states, 13,792 arcs, initial
+            // probabilities from 1 to 1e-30 (26 slots, streamed / 40 on half the waves, resident)
+            // 1,612 / 740 us. Graphs with hub slices are not dealt so to begin with: 1,980 states,
+            // 11,396 arcs, varied initial probabilities (streamed / resident) 1,739 / 786 us; 20,108
+            // arcs by entered state (32 slots, hybrid / 26, resident) 848 / 624; 17,237 by arc 650 / 620.
+            if (st == LFMMI_OK && h->rec_line == 0 &&
+                std::any_of(h->packed.begin(), h->packed.end(),
+                            [](const PackedGraph& pg) { return pg.two_slices; })) {
+                tune.two_slices = false;
+                st = pack_with(waves, &max_slots);
+                if (st == LFMMI_OK) choose();
             }
-            if (st == LFMMI_OK && gslots == 0) gslots = grouped_slots();
-            h->rec_grouped = gslots > 0 && !h->rec_short;
-            // Initial probabilities that differ: state values divided by them need no leak
-            // factor per arc and take every variant that a uniform one takes, but have to leave
-            // every weight an ordinary fp32 number (see leak_by_rows).
-            h->over_pi = st == LFMMI_OK && gslots == 0 && h->has_wb && !h->wide && !h->rec_hubs &&
-                         env_int("LFMMI_OVER_PI", 1) != 0;
-            for (int32_t g = 0; g < n && h->over_pi; ++g) h->over_pi = leak_by_rows(arcs_of(g));
-            if (st == LFMMI_OK && gslots == 0) {
-                gslots = line_slots(false);
-                if (gslots > 0) h->rec_line = 2;
-            }
+            tune.two_slices = false;  // (packing for half the waves: not for the straight line)
             auto resident = [&](int slots, int wv) {
                 return rec_register_slots(h->wide, leak(), h->rec_yrep, h->rec_hubs, slots,
                                           wv * kLanes);

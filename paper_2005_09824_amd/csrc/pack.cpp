@@ -923,16 +923,23 @@ std::string pack_graph(const ArcList& g, int32_t num_pdfs, int rec_waves, int oc
         return hub;
     };
     std::vector<uint8_t> hub_f = hubs_of(indeg), hub_b = hubs_of(outdeg);
-    // Waves own at most two slices, the narrower one first, where that leaves their slots in the
-    // registers of the straight-line recursion.
+    // Waves own at most two slices, the narrower one first, where the straight-line recursion then
+    // holds their slots. It takes no hub slices in either direction.
     std::vector<int32_t> entered_pdf;
     const bool by_state = pdf_of_entered_state(g, &entered_pdf);
+    const bool hubs = std::count(hub_f.begin(), hub_f.end(), 1) + std::count(hub_b.begin(), hub_b.end(), 1) > 0;
+    out->two_slices = false;
     auto arranged = [&](const std::vector<int32_t>& deg, const std::vector<uint8_t>& hub) {
         Arrangement ar = arrange(deg, rec_waves, closing, &hub);
-        if (tune.two_slices && ar.num_slices <= 2 * ar.num_waves) {
+        if (tune.two_slices && !hubs && ar.num_slices > ar.num_waves && ar.num_slices <= 2 * ar.num_waves) {
             Arrangement two = arrange(deg, rec_waves, closing, &hub, 2);
-            const int32_t most = by_state ? kLineSlotsByState : kLineSlotsByArc;
-            if (two.max_wave_slots <= std::max(ar.max_wave_slots, most)) return two;
+            const int32_t most = !by_state       ? kLineSlotsByArc
+                                 : rec_waves > 8 ? kLineSlotsByState
+                                                 : kLineSlotsByStateFewWaves;
+            if (two.max_wave_slots <= most) {
+                out->two_slices = true;
+                return two;
+            }
         }
         return ar;
     };

@@ -23,6 +23,7 @@ constexpr int kHeavyPdfRows = 24;  // OCC: more rows than this and a wave adds t
 constexpr int kMaxWaves = 16;
 // what a wave of the straight-line recursion holds
 constexpr int kLineSlotsByState = 36, kLineSlotsByArc = 28;
+constexpr int kLineSlotsByStateFewWaves = 48;  // workgroups of up to 8 waves
 constexpr int kMaxIndex = 16384;  // x / y index * 4 must fit 16 bits
 
 struct Ordering {
@@ -61,6 +62,7 @@ struct PackedGraph {
     int32_t num_states = 0;
     int64_t num_arcs = 0;
     Ordering ord[3];
+    bool two_slices = false;  // slices dealt to waves as the straight-line recursion needs it
     // Per-direction vectors in that direction's row numbering, padded with 0:
     //   init: start vector (FWD pi, BWD final)      fin: closing dot (FWD final, BWD pi)
     //   a:    leak dot weights (FWD 1, BWD pi)      b:   leak target (FWD pi, BWD 1)
@@ -112,7 +114,7 @@ struct PackTuning {
     bool order_slots = true;          // order each row's arcs over its slots
     bool emission_conflicts = true;   // the emission gather can conflict (row not replicated)
     bool hub_slices = true;           // rows with far more arcs than the others get a slice each
-    bool two_slices = true;           // at most two slices a wave where that costs no registers
+    bool two_slices = true;           // at most two slices a wave, for the straight-line recursion
     bool deal_occ = true;             // OCC ordering: arcs dealt to rows and slots jointly
 };
 

@@ -431,3 +431,69 @@ def test_occupancy_rows_are_few(S, k, P, slices):
     h.close()
     assert o["slices"] == slices
     assert np.count_nonzero(o["w"]) == len(g["src"])
+
+
+def _graded_graph(S, high, low, share, P=84, by_state=False, hub=0, init="uniform"):
+    """The first `share` of the states have `high` arcs in and out, all among themselves, the others
+    `low`; `hub` arcs more lead into the last state."""
+    rng = np.random.default_rng(1)
+    n, src, dst = int(S * share), [], []
+    for at, m, d in ((0, n, high), (n, S - n, low)):
+        i = np.arange(m)
+        for q in range(d):
+            src.append(at + (i + q * 7) % m)
+            dst.append(at + i)
+    if hub:
+        src.append(rng.choice(S, hub, replace=False))
+        dst.append(np.full(hub, S - 1))
+    src, dst = np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)
+    p = np.ones(S) if init == "uniform" else rng.uniform(0.1, 1.0, S)
+    if init == "wide":  # beyond what state values over initial probabilities can hold
+        p[::3] *= 1e-30
+    pdf = rng.integers(0, P, S)[dst] if by_state else rng.integers(0, P, len(src))
+    return {"num_states": S, "num_pdfs": P, "src": src, "dst": dst, "pdf": pdf.astype(np.int32),
+            "logw": np.log(rng.uniform(0.02, 0.2, len(src))).astype(np.float32),
+            "init_prob": (p / p.sum()).astype(np.float32), "final_prob": np.ones(S, np.float32)}
+
+
+# At most two slices a wave costs balance: only handles that run the straight line are dealt so. The
+# others keep the slots and the kernel that they have without it (LFMMI_LINE=0).
+@pytest.mark.parametrize("graphs,slots,registers,waves", [
+    ([(1980, 24, 6, 0.2, 84, True, 1100)], [(24, 26)], 26, 16),
+    ([(1980, 12, 5, 0.45, 84, False, 1100)], [(18, 20)], 20, 16),
+    ([(1980, 10, 4, 0.2, 84, False, 1100, "varied")], [(36, 30)], 48, 8),
+    ([(1600, 18, 4, 0.33, 84, False, 0, "wide")], [(40, 40)], 48, 8),
+    ([(2040, 18, 4, 0.2, 4000)], [(18, 18)], 0, 16),
+    # beside the graph that would take the straight line: another kind, a hub, too many rows
+    ([(1980, 24, 6, 0.2, 84, True), (1000, 5, 4, 0.5)], [(24, 24), (6, 6)], 24, 16),
+    ([(2040, 18, 4, 0.2), (1000, 5, 4, 0.5, 84, False, 600)], [(18, 18), (10, 6)], 20, 16),
+    ([(2040, 18, 4, 0.2), (3000, 4, 4, 0.5)], [(18, 18), (12, 12)], 20, 16),
+])
+def test_two_slices_a_wave_only_for_the_straight_line(graphs, slots, registers, waves, monkeypatch):
+    graphs = [_graded_graph(*g) for g in graphs]
+    taken = []
+    for line in ("1", "0"):
+        monkeypatch.setenv("LFMMI_LINE", line)
+        h = binding.lfmmi_graph_pack_batch(graphs)
+        info = [[binding.lfmmi_graph_ordering_info(h, g, o) for o in (0, 1)] for g in range(len(graphs))]
+        assert all(i["lds_vector_rows"] != 2048 for pair in info for i in pair)
+        assert [(f["max_wave_slots"], b["max_wave_slots"]) for f, b in info] == slots
+        assert info[0][0]["register_slots"] == registers
+        assert binding.lfmmi_graph_info(h)["rec_waves"] == waves
+        taken.append(info)
+        if line == "1":  # dealing anew has lost no arc
+            for g, graph in enumerate(graphs):
+                got, want, _ = _unpack(h, g, graph)
+                assert all(a == want for a in got)
+        h.close()
+    assert taken[0] == taken[1]
+
+
+def test_two_slices_a_wave_for_the_straight_line():
+    h = binding.lfmmi_graph_pack(_graded_graph(2040, 18, 4, 0.2))
+    for o in (0, 1):
+        c = binding.lfmmi_graph_ordering_copy(h, 0, o)
+        assert c["lds_vector_rows"] == 2048 and c["max_wave_slots"] == 22
+        widths = np.diff(c["slice_off"]).reshape(16, 2)
+        assert np.all(widths[:, 0] <= widths[:, 1])
+    h.close()
