@@ -433,6 +433,24 @@ def test_occupancy_rows_are_few(S, k, P, slices):
     assert np.count_nonzero(o["w"]) == len(g["src"])
 
 
+# ... and in large graphs no more of them for the few slots that one more a wave then saves: beyond 42
+# slices the kernel's LDS map holds one frame a record, not two
+@pytest.mark.parametrize("S,k,P,skew,slices", [(4160, 26, 1600, 2.5, 32), (4160, 25, 161, 1.0, 16)])
+def test_occupancy_rows_of_large_graphs_are_few(S, k, P, skew, slices):
+    rng = np.random.default_rng(1)
+    src = np.repeat(np.arange(S), k).astype(np.int32)
+    h = binding.lfmmi_graph_pack({
+        "num_states": S, "num_pdfs": P, "src": src,
+        "dst": ((src + 1 + np.tile(np.arange(k), S) * 37) % S).astype(np.int32),
+        "pdf": (P * rng.random(len(src)) ** skew).astype(np.int32),
+        "logw": np.full(len(src), -3, np.float32), "init_prob": np.full(S, 1 / S, np.float32),
+        "final_prob": np.ones(S, np.float32)})
+    o = binding.lfmmi_graph_ordering_copy(h, 0, binding.ORD_OCC)
+    h.close()
+    assert o["slices"] == slices
+    assert np.count_nonzero(o["w"]) == len(src)
+
+
 def _graded_graph(S, high, low, share, P=84, by_state=False, hub=0, init="uniform"):
     """The first `share` of the states have `high` arcs in and out, all among themselves, the others
     `low`; `hub` arcs more lead into the last state."""
