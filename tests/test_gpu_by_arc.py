@@ -105,3 +105,36 @@ def test_hybrid_recursion_by_arc(S, k, P, init):
     assert info["emission_replicated"] == (1 if P <= 255 else 0)
     assert info["lds_vector_rows"] == (8192 if S <= 8192 else 12288)
     parity(g, LENGTHS[3:], 66, 1e-4)
+
+
+# a handle of such graphs of different sizes, among them one whose waves stream nothing and one that
+# leaves most waves without a slice; a dead and a NaN sequence beside sound ones
+@pytest.mark.parametrize("init", ["uniform", "varied"])
+def test_hybrid_recursion_by_arc_of_graphs_of_different_sizes(init):
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(11)
+    graphs = [workloads.random_den_graph(rng, S, k, 50, 0.5)
+              for S, k in ((2500, 16), (300, 4), (2100, 20), (3000, 6), (2500, 15), (2200, 17))]
+    for g in graphs:
+        g["num_pdfs"] = 51  # the last is on no arc
+        if init == "varied":
+            p = rng.uniform(0.1, 1.0, g["num_states"])
+            g["init_prob"] = (p / p.sum()).astype(np.float32)
+    lengths = np.array([66, 65, 30, 64, 50, 2], np.int32)
+    x = rng.normal(0, 2, (6, 66, 51)).astype(np.float32)
+    x[2, 11, :50] = -np.inf
+    x[4, 20, 7] = np.nan
+    h = binding.lfmmi_graph_create_batch(graphs)
+    info = [binding.lfmmi_graph_ordering_info(h, i, 0) for i in range(6)]
+    assert all(i["register_slots"] == 36 and i["lds_vector_rows"] == 8192 for i in info)
+    assert info[1]["waves"] == 5 and info[3]["max_wave_slots"] < 36 < info[0]["max_wave_slots"]
+    objf, grad, status = binding.lfmmi_forward_backward(h, torch.from_numpy(x).cuda(), lengths, 1e-4)
+    torch.cuda.synchronize()
+    h.close()
+    assert status.tolist() == [0, 0, 1, 0, 3, 0]
+    assert objf[2].item() == -np.inf and np.isnan(objf[4].item())
+    assert torch.all(grad[2] == 0) and torch.all(grad[4] == 0)
+    for b in (0, 1, 3, 5):
+        lz, gamma = oracle.forward_backward(graphs[b], x[b:b + 1], lengths[b:b + 1], 1e-4)
+        assert abs(objf[b].item() - lz[0]) <= 1e-4 * max(abs(lz[0]), 1.0)
+        assert np.abs(grad[b].cpu().numpy() - gamma[0]).max() <= 1e-4
