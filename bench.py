@@ -33,9 +33,23 @@ REC_TRAFFIC_BYTES = {"wsj_mono_2k": 362.4e6, "biphone_10k": 4245.5e6, "long_uneq
                      "e2e_num_den": 641.8e6, "hmm_den_2k": 345.6e6, "wsj_den_7398": 2347.2e6}
 
 
+def rec_kernel(binding, h):
+    """Name of the recursion kernel that a handle's passes launch."""
+    handle = binding.lfmmi_graph_info(h)
+    o = binding.lfmmi_graph_ordering_info(h, 0, 0)
+    if o["register_slots"] and o["lds_vector_rows"] == 2048:
+        return "k_rec_line" if handle["emission_by_state"] else "k_rec_line_arc"
+    hubs = any(binding.lfmmi_graph_ordering_info(h, g, d)["hub_slices"]
+               for g in range(handle["num_graphs"]) for d in (0, 1))
+    # (of the kernels for 13 to 16 waves and an emission gather only the hybrid holds 36 slots)
+    if o["register_slots"] == 36 and handle["rec_waves"] > 12 and not handle["emission_by_state"] and not hubs:
+        return "k_rec_hybrid"
+    return "k_rec"
+
+
 def phase_timers(config, torch, binding, workloads):
-    """Clocks per phase of k_occ_planes (thread 0 of every workgroup, s_memtime), from the
-    counters a library built with -DLFMMI_PHASE_TIMERS keeps."""
+    """Clocks per phase of k_occ_planes (thread 0 of every workgroup, s_memtime), and of k_rec
+    where the workload runs it with arcs in registers, from the counters a library built with -DLFMMI_PHASE_TIMERS keeps."""
     import ctypes
     lib = ctypes.CDLL(binding.LIB_PATH)
     if not hasattr(lib, "lfmmi_phase_timers_read"):
@@ -79,6 +93,9 @@ def phase_timers(config, torch, binding, workloads):
             c = [v[16 + 4 * w + q] / steps for q in range(4)]
             print("  %4d %6.0f %6.0f %6.0f %6.0f %21.0f   %d/%d" %
                   (w, c[0], c[1], c[2], c[3], sum(c), slots[0][w], slots[1][w]))
+    else:
+        print("%s, this workload's recursion, keeps no phase timers (k_rec does, with arcs in registers)"
+              % rec_kernel(binding, h))
     h.close()
     return 0
 
@@ -98,7 +115,8 @@ def main():
     ap.add_argument("--phase-timers", action="store_true",
                     help="one call with the whole batch as one launch on a library built with "
                          "-DLFMMI_PHASE_TIMERS: where a frame group of the occupancy kernel "
-                         "spends its clocks; prints a table and exits")
+                         "(and a step of k_rec, where that is the recursion) spends its "
+                         "clocks; prints a table and exits")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on one GPU only; sequences are independent, so "
@@ -237,7 +255,7 @@ def main():
         "config": {"workload": wl["name"], "states": S, "arcs": A, "pdfs": P, "batch": B,
                    "frames": frames, "max_len": T, "leak": leak,
                    "numerators": num is not None},
-        "roofline": {"bound": "lds", "kernel": "k_rec", "achieved": achieved,
+        "roofline": {"bound": "lds", "kernel": rec_kernel(binding, den), "achieved": achieved,
                      "peak": LDS_PEAK_GBPS, "unit": "GB/s", "frac": achieved / LDS_PEAK_GBPS,
                      "peak_measured": LDS_PEAK_MEASURED_GBPS,
                      "frac_of_measured_peak": achieved / LDS_PEAK_MEASURED_GBPS,

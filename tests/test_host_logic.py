@@ -422,6 +422,26 @@ def test_bench_refuses_more_than_one_gpu():
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
 
 
+# the recursion kernel that the benchmark names is the one its workload runs
+@pytest.mark.parametrize("S,k,by_state,hub,name", [
+    (2000, 9, False, 0, "k_rec_line_arc"), (2000, 9, True, 0, "k_rec_line"), (2000, 14, False, 0, "k_rec_hybrid"),
+    (5000, 9, False, 0, "k_rec_hybrid"), (2000, 9, False, 1500, "k_rec"), (16000, 3, False, 0, "k_rec"),
+])
+def test_bench_names_the_recursion_kernel(S, k, by_state, hub, name):
+    import bench
+    rng = np.random.default_rng(4)
+    g = workloads.random_den_graph(rng, S, k, 84, 0.5)
+    if by_state:
+        g["pdf"] = rng.integers(0, 84, S).astype(np.int32)[g["dst"]]
+    if hub:
+        g["src"] = np.concatenate([g["src"], rng.choice(S, hub, replace=False).astype(np.int32)])
+        for key, v in (("dst", 0), ("pdf", 0), ("logw", -3.0)):
+            g[key] = np.concatenate([g[key], np.full(hub, v, g[key].dtype)])
+    h = binding.lfmmi_graph_pack(g)
+    assert bench.rec_kernel(binding, h) == name
+    h.close()
+
+
 # few rows for the occupancies: each row's sum is stored and added up again in every frame
 @pytest.mark.parametrize("S,k,P,slices", [(1000, 9, 200, 8), (500, 11, 150, 8), (2000, 9, 84, 8), (300, 9, 84, 6), (100, 5, 10, 2)])
 def test_occupancy_rows_are_few(S, k, P, slices):
