@@ -992,21 +992,26 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
     bk.before_occ = beside;
     {
         // One bucket where the longest recursion is too short for other sequences' occupancy
-        // pass to hide behind it: every further bucket costs 10 to 20 us in launches and events.
-        // The estimate of a step follows the kernels' times from 20 to 5,000 states. 1 / 4
-        // buckets, B = 32: 20 states, 200 frames 158 / 168 us; 600 states, 120 frames 130 / 154;
-        // 2,000 states, 120 frames 184 / 201, 400 frames 535 / 507; 5,000 states, 60 frames
-        // 266 / 273, 120 frames 472 / 445. Small graphs reach 330 frames within that estimate,
-        // and from about 240 on several buckets win where there is much to hide: occupancies by
-        // arc of many sequences, or of fewer with many pdfs, while the longest are well above the
-        // mean (lengths from T / 3 to T: 0.67 T). 20 states, 84 pdfs, T = 280: B = 24 208 / 214,
-        // 64 248 / 230, 128 311 / 297; T = 230, B = 128 267 / 264. 1,000 pdfs, T = 280: B = 8 262 / 288,
-        // 16 306 / 280, 64 517 / 485. Mean length 0.75 T: 84 pdfs 324 / 329 (B = 128, T = 280), 2,000
-        // pdfs 534 / 500 (600 states, B = 48); 0.8 T: 337 / 356 and 551 / 534; all of length T: 372 /
-        // 410 and 616 / 660. By state one bucket stays the better one: 300 states, 1,000 pdfs, B = 64
-        // 288 / 293, 128 384 / 427, and beside another pass, whose end every occupancy kernel waits
-        // for: 449 states, 2,350 pdfs, B = 52, full loss of up to 285 frames 625 / 652. LFMMI_BUCKETS
-        // set: as many as it says.
+        // pass to hide behind it: every further bucket costs launches and events, 10 to 20 us and
+        // what the host needs for them, of which a call of up to 100 us sees 50 to 80. The estimate
+        // of a step lies well above the straight-line kernels' times (20 states 0.27 us, 600 states
+        // by state 0.31, 2,000 states by arc 1.0, 5,000 states 2.8): small graphs take several
+        // buckets from 325 frames on, where a call was as long as the estimate says before those
+        // kernels. 1 / 4 buckets, lengths from T / 3 to T, 84 pdfs, by arc, B = 32: 20 states, 200
+        // frames 94 / 130 us, 400 168 / 167; 600 states (5,400 arcs), 120 frames 101 / 135, 400 285 /
+        // 274; 2,000 states (20,000), 120 frames 166 / 173, 200 257 / 254, 400 484 / 461; 5,000 states
+        // (50,000), 60 frames 235 / 235, 120 434 / 403. B = 8: 300 states, 400 frames 213 / 228; 2,000
+        // states, 200 frames 232 / 248, 400 441 / 446. B = 128: 2,000 states, 120 frames 223 / 214,
+        // 400 696 / 606.
+        // Small graphs reach 330 frames within the estimate, and from about 240 on several buckets win
+        // where there is much to hide: occupancies by arc of many sequences, or of fewer with many
+        // pdfs, while the longest are well above the mean (lengths from T / 3 to T: 0.67 T). T = 280,
+        // B = 128: 300 states 249 / 240, 600 states 288 / 272, but 20 states 209 / 222; 1,000 states,
+        // 1,000 pdfs, B = 32 270 / 249, 128 508 / 475, but B = 8 229 / 240. By state one bucket stays
+        // the better one, up to 400 frames where the rule takes four: 144 states, B = 8, 32, 128 122 /
+        // 151, 133 / 154, 170 / 197; 600 states 153 / 178, 169 / 187, 216 / 226; only 2,016 states at
+        // B = 128 gain, 511 / 486. Nothing beside another pass, whose end every occupancy kernel
+        // waits for. LFMMI_BUCKETS set: as many as it says.
         double longest_us = 0.0, frames = 0.0;
         int32_t longest = 0;
         for (int32_t b = 0; b < B; ++b) {
