@@ -6,6 +6,7 @@ import pytest
 from oracle import lfmmi_oracle as oracle
 from paper_2005_09824_amd import binding, workloads
 from tests.test_gpu_by_state import parity, regular_graph
+from tests.test_host_logic import graded_graph
 
 pytestmark = pytest.mark.gpu
 
@@ -138,3 +139,18 @@ def test_hybrid_recursion_by_arc_of_graphs_of_different_sizes(init):
         lz, gamma = oracle.forward_backward(graphs[b], x[b:b + 1], lengths[b:b + 1], 1e-4)
         assert abs(objf[b].item() - lz[0]) <= 1e-4 * max(abs(lz[0]), 1.0)
         assert np.abs(grad[b].cpu().numpy() - gamma[0]).max() <= 1e-4
+
+
+# graphs that two slices a wave would suit but for a hub, or for initial probabilities that keep a
+# leak factor per arc: slices dealt freely, every arc in registers
+@pytest.mark.parametrize("graph,registers", [
+    ((1980, 24, 6, 0.2, 84, True, 1100), 26), ((1980, 12, 5, 0.45, 84, False, 1100), 20),
+    ((1980, 10, 4, 0.2, 84, False, 1100, "varied"), 48), ((1600, 18, 4, 0.33, 84, False, 0, "wide"), 48),
+])
+def test_recursion_of_graphs_that_nearly_take_the_straight_line(graph, registers):
+    g = graded_graph(*graph)
+    h = binding.lfmmi_graph_pack(g)
+    info = binding.lfmmi_graph_ordering_info(h, 0, 0)
+    h.close()
+    assert info["register_slots"] == registers and info["lds_vector_rows"] == 8192
+    parity(g, LENGTHS[3:], 66, 1e-4)

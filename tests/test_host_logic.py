@@ -471,7 +471,7 @@ def test_occupancy_rows_of_large_graphs_are_few(S, k, P, skew, slices):
     assert np.count_nonzero(o["w"]) == len(src)
 
 
-def _graded_graph(S, high, low, share, P=84, by_state=False, hub=0, init="uniform"):
+def graded_graph(S, high, low, share, P=84, by_state=False, hub=0, init="uniform"):
     """The first `share` of the states have `high` arcs in and out, all among themselves, the others
     `low`; `hub` arcs more lead into the last state."""
     rng = np.random.default_rng(1)
@@ -508,7 +508,7 @@ def _graded_graph(S, high, low, share, P=84, by_state=False, hub=0, init="unifor
     ([(2040, 18, 4, 0.2), (3000, 4, 4, 0.5)], [(18, 18), (12, 12)], 20, 16),
 ])
 def test_two_slices_a_wave_only_for_the_straight_line(graphs, slots, registers, waves, monkeypatch):
-    graphs = [_graded_graph(*g) for g in graphs]
+    graphs = [graded_graph(*g) for g in graphs]
     taken = []
     for line in ("1", "0"):
         monkeypatch.setenv("LFMMI_LINE", line)
@@ -528,7 +528,7 @@ def test_two_slices_a_wave_only_for_the_straight_line(graphs, slots, registers, 
 
 
 def test_two_slices_a_wave_for_the_straight_line():
-    h = binding.lfmmi_graph_pack(_graded_graph(2040, 18, 4, 0.2))
+    h = binding.lfmmi_graph_pack(graded_graph(2040, 18, 4, 0.2))
     for o in (0, 1):
         c = binding.lfmmi_graph_ordering_copy(h, 0, o)
         assert c["lds_vector_rows"] == 2048 and c["max_wave_slots"] == 22
