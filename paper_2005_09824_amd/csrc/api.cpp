@@ -330,12 +330,12 @@ lfmmi_status pack_all(int32_t n, int32_t num_pdfs, const int64_t* state_off,
             };
             auto leak = [&]() { return !h->has_wb ? 0 : (h->over_pi ? 2 : 1); };
             // One or two slices per wave, the narrower one first: the straight-line variants (fp32),
-            // whatever the size: no size measured slower. Time of a step, before / with them:
-            // emission by entered state, 144 states, 648 arcs 0.54 / 0.25 us; 600, 3,900 0.61 /
-            // 0.31; 840, 5,460 0.68 / 0.39 (all three with an emission gather before); 1,440, 19,440
-            // 1.13 / 0.65; 2,016, 21,168 1.04 / 0.68. By arc: 20 states 0.55 / 0.27; 600, 5,400 0.84 /
-            // 0.56; 1,000, 10,000 1.13 / 0.93 (200 pdfs), 1.06 / 0.94 (600); 2,000, 20,000 1.09 / 0.95;
-            // 2,040, 10,200 0.88 / 0.77. LFMMI_LINE=0: never.
+            // whatever the size: no size measured slower. Time of a step, without / with them, one
+            // sequence: emission by entered state, 144 states, 648 arcs 0.54 / 0.25 us; 600, 3,900 0.70 /
+            // 0.41; 840, 5,460 0.76 / 0.50 (all three with an emission gather without them); 1,440,
+            // 19,440 1.14 / 0.66; 2,016, 21,168 1.08 / 0.67; 2,016, 27,216 1.07 / 0.72. By arc: 20 states
+            // 0.55 / 0.27; 300, 3,000 0.67 / 0.45; 600, 5,400 0.83 / 0.59; 1,000, 10,000 (200 pdfs) 1.13 /
+            // 0.99; 2,000, 20,000 1.08 / 0.98, 1.27 / 1.17 (300 pdfs). LFMMI_LINE=0: never.
             auto line_possible = [&]() {
                 if (env_int("LFMMI_LINE", 1) == 0 || h->rec_hubs || h->wide) return false;
                 if (std::max(h->max_rows_f, h->max_rows_b) > rec_line_max_rows()) return false;
@@ -1095,15 +1095,15 @@ lfmmi_status run_pass(const lfmmi_graph* graph, const float* logits, const int32
 // passes' recursion workgroups fit the chip, every sequence has frames (its occupancy kernel
 // does the adding), no events are being collected, which would overlap, and the call is long
 // or its batch large enough. In turn / beside each other, calls that follow one another: 8
-// sequences of up to 60 frames 83 to 128 / 67 to 108 us, 64 of up to 150 frames 182 to 428 / 137
-// to 371 (20 to 2,000 states), only below 40 frames on a few hundred states 60 / 76. What it costs
-// is host time, 25 / 64 us a call, in events and waits of the second stream. A program whose
-// host runs ahead of its device does not see that; one that waits for the host does: training
-// steps with no model around them, 20 states, B = 8, up to 59 frames 123 / 218, 120 frames 163 /
-// 221, 176 frames 214 / 222, 218 frames 251 / 222; 2,016 states, B = 32, up to 57 frames 170 / 165, 98
-// frames 228 / 202. Smaller batches of short sequences have less to gain and need longer passes to
-// win that back (training step, B = 2, 45 frames: 153 / 226; calls, B = 2, 280 frames: 290 to 446 /
-// 201 to 353).
+// sequences of up to 60 frames 70 to 103 / 64 to 85 us, 64 of up to 150 frames 158 to 273 / 126
+// to 222 (20 to 2,000 states), only below 40 frames on the smallest graphs 60 / 68. What it costs
+// is host time, in events and waits of the second stream. A program whose host runs ahead of its
+// device does not see that; one that waits for the host does: training steps with no model around
+// them, 20 states, B = 8, up to 55 frames 168 / 216, 110 frames 120 / 164, 161 frames 145 / 166, 202
+// frames 167 / 163; 2,016 states by state, B = 32, up to 56 frames 125 / 170, 92 frames 168 / 162; B = 64
+// of up to 150 frames 179 to 292 / 168 to 251. Smaller batches of short sequences have less to gain
+// and need longer passes to win that back (2,016 states, B = 2, 269 frames: calls 317 / 231, training
+// steps 334 / 258).
 // A call of fewer than four sequences uses no stream of the library's by itself and stays so
 // under capture: other threads' eager calls use those streams at the same time.
 bool beside_each_other(const lfmmi_graph* num, const lfmmi_graph* den, const int32_t* lengths,

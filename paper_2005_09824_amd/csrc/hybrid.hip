@@ -15,10 +15,11 @@ namespace {
 //   - every wave stages an equal share of the next emission row, with no branches;
 //   - n is the power of two below the total, and the totals of 64 steps are stored together;
 //   - memory is addressed by a scalar base and a 32-bit offset.
-// Calls with the hybrid form of RecRegs / this one: 5,000 states, 50,000 arcs, 32 sequences of 200 to
-// 1,600 frames 4,975 / 4,639 us (a step 3.0 -> 2.8 us); of 100 to 500, initial probabilities that
-// differ 1,828 / 1,700; 7,398 states, B = 128 3,175 / 3,072; 10,000 states, 3,000 pdfs, B = 128 as
-// before (6,255: streamed slots and occupancies keep every compute unit busy).
+// Calls with the hybrid form of RecRegs and the fences of every wave / with this one and one thread's:
+// 5,000 states, 50,000 arcs, 32 sequences of 200 to 1,600 frames 4,961 / 4,648 us (a step 3.0 -> 2.75 us);
+// of 100 to 500, initial probabilities that differ 1,827 / 1,684; 7,398 states, B = 128 3,179 / 2,811;
+// 10,000 states, 3,000 pdfs, B = 128 6,083 / 5,765 (5,765 to 6,060 on other cards: streamed slots and
+// occupancies keep every compute unit busy).
 // ---------------------------------------------------------------------------
 template <bool YREP, int YPASS, int LEAK, int NSLOT, bool BIG>
 struct RecHybrid {

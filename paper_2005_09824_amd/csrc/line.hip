@@ -21,8 +21,8 @@ namespace {
 // LDS map: X0 [0, 8K)  X1 [8K, 16K)  partial sums at 16K: n of wave w at value 32 * set + w, s 16
 // further; unused words behind them. RecLineArc: emission rows Y0 [32K, 64K)  Y1 [64K, 96K), the
 // last word of each 0.
-// A step of that graph now takes 0.74 us (442 gathers of 64 lanes, 140 instructions a wave), a call
-// of 64 sequences of 100 to 500 frames 624 -> 488 us; 144 states, 648 arcs: 0.54 -> 0.25 us a step.
+// A step of that graph now takes 0.72 us (442 gathers of 64 lanes, 140 instructions a wave), a call
+// of 64 sequences of 100 to 500 frames 629 -> 452 us; 144 states, 648 arcs: 0.54 -> 0.25 us a step.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kLineX1 = 8192, kLinePart = 16384, kLineDump = kLinePart + 256;
 constexpr uint32_t kLineY0 = 32768, kLineY1 = 65536, kLineYZero = 32764;
@@ -351,9 +351,9 @@ struct RecLine {
 // emission row, and the branches of that staging: every wave stages an equal share of the row.
 // n is the power of two below the total, as in RecGrouped (its inverse needs no reciprocal).
 // Time of a step with RecRegs / here, one sequence: 20 states 0.55 / 0.27 us; 300 states, 3,000 arcs
-// 0.68 / 0.47; 600, 5,400 0.84 / 0.56; 1,237, 8,659 (initial probabilities that differ) 0.82 / 0.64;
-// 2,000, 20,000 1.09 / 0.95 (there the waves' 22 slots of three vector instructions bound it); 300
-// pdfs, plain rows 1.26 / 1.17. A call of 64 sequences of 100 to 500 frames, 2,000 states: 640 -> 583.
+// 0.67 / 0.45; 600, 5,400 0.83 / 0.59; 1,237, 8,659 (initial probabilities that differ) 0.87 / 0.80;
+// 2,000, 20,000 1.08 / 0.98 (there the waves' 22 slots of three vector instructions bound it); 300
+// pdfs, plain rows 1.27 / 1.17. A call of 64 sequences of 100 to 500 frames, 2,000 states: 653 -> 588.
 // YPASS: staging passes (YREP: quads of copies, else values).
 // ---------------------------------------------------------------------------
 template <bool YREP, int YPASS, int LEAK, int NSLOT, int NT>
